@@ -28,6 +28,9 @@ constexpr int kWave = 64;
 constexpr int kTileW = kWave - 2;     // output columns per wavefront strip
 constexpr int kPairTileW = 2 * kWave - 4;  // output columns per wavefront, two columns per lane
 constexpr int kMrTileW = kWave - 4;   // output columns per wavefront, 24-site stencil (two halo lanes a side)
+constexpr int kTwoTileW = kWave - 6;  // output columns per wavefront, two time steps per launch
+constexpr int kTwoWaves = 4;          // wavefronts per workgroup, two time steps per launch
+constexpr int kTwoWavesWide = 8;      // the same on lattices with many strips per compute unit
 constexpr int kPairWaves = 4;         // wavefronts per workgroup, two columns per lane
 constexpr int kWavesPerBlock = 16;    // wavefronts (strips) per workgroup: FP32 step, FP32 batch
 constexpr int kBatchWaves = 16;       // wavefronts per workgroup (= per lattice) of the persistent batch
@@ -54,6 +57,17 @@ enum : int { kModeStep = 0, kModeMoments = 1, kModeDiag = 2 };
 enum : int { kFlagUnstable = 1, kFlagBadInput = 2 };
 enum : int { kPsiCS = 0, kPsiSS = 1 };  // psi of Eq. (24) from Eq. (30), or of Eq. (23)
 enum : int { kStencilNearest = 0, kStencilMultirange = 1 };  // interaction stencil of Eq. (7)
+
+// Wave priorities (s_setprio) while a wavefront issues loads: the prologue of a
+// strip (its first rows) above the prefetch of the next row inside the walk,
+// both above everything else (arithmetic and stores).  A wave that has just
+// started then gets its first requests out ahead of the resident waves, and
+// those issue their prefetches ahead of other waves' arithmetic.  Measured on
+// the 8192 x 4096 splash, FP32: 78.6k MLUPS against 76.1k without priorities,
+// 77.4k with the prologue raised alone and 77.4k with both raised to the same
+// level.
+constexpr short kPrioPrologue = 2;
+constexpr short kPrioPrefetch = 1;
 
 // Per-launch constants (FP32 copies of FP64 host-derived values).
 struct StepConst {

@@ -18,20 +18,10 @@
 //   copy_probe        plain streaming copy: attainable-bandwidth reference
 #include "d2q9_core.hpp"
 #include "d2q9_launch.hpp"
+#include "d2q9_two.hpp"
 
 namespace lbmp {
 
-
-// Wave priorities (s_setprio) while a wavefront issues loads: the prologue of a
-// strip (its first rows) above the prefetch of the next row inside the walk,
-// both above everything else (arithmetic and stores).  A wave that has just
-// started then gets its first requests out ahead of the resident waves, and
-// those issue their prefetches ahead of other waves' arithmetic.  Measured on
-// the 8192 x 4096 splash, FP32: 78.6k MLUPS against 76.1k without priorities,
-// 77.4k with the prologue raised alone and 77.4k with both raised to the same
-// level.
-constexpr short kPrioPrologue = 2;
-constexpr short kPrioPrefetch = 1;
 
 
 // rho and the Eq. (6) velocity of site (xci, y) into the [ny][nx] output fields.
@@ -620,6 +610,19 @@ __attribute__((amdgpu_waves_per_eu(1))) void d2q9_pair(
     pair_tile<WALLS, PSI>(fin, fout, k, tile, lane, flag);
 }
 
+// ---------------------------------------------------------------- two time steps per launch
+template <bool WALLS, int PSI, int WPB>
+__global__ __launch_bounds__(kWave * WPB)
+__attribute__((amdgpu_waves_per_eu(4))) void d2q9_two(
+    const float* __restrict__ fin, float* __restrict__ fout, StepConst k, int* __restrict__ flag)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tile = logical_block(blockIdx.x, gridDim.x) * WPB + wave;
+    if (tile >= k.tiles_x * k.tiles_y) return;  // whole wavefront leaves together
+    two_tile<WALLS, PSI>(fin, fout, k, tile, lane, flag);
+}
+
 // ---------------------------------------------------------------- 24-site stencil
 // Time step, moments or diagnostics with the interaction stencil of nearest and
 // next-nearest neighbours (FP32 storage).  One wavefront walks a strip of 60 output
@@ -1096,6 +1099,30 @@ int pair_blocks_per_cu(bool walls)
         walls ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, d2q9_pair<true, kPsiCS>, kWave * kPairWaves, 0)
               : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, d2q9_pair<false, kPsiCS>, kWave * kPairWaves, 0);
     return e == hipSuccess ? nb : 0;
+}
+
+template <bool WALLS, int PSI>
+static hipError_t launch_two_psi(const void* fin, void* fout, const StepConst& k, int waves, int* flag, hipStream_t s)
+{
+    const float* in = static_cast<const float*>(fin);
+    float* out = static_cast<float*>(fout);
+    if (waves == kTwoWavesWide)
+        hipLaunchKernelGGL((d2q9_two<WALLS, PSI, kTwoWavesWide>), dim3(strip_blocks(k, waves)), dim3(kWave * waves), 0, s,
+                           in, out, k, flag);
+    else
+        hipLaunchKernelGGL((d2q9_two<WALLS, PSI, kTwoWaves>), dim3(strip_blocks(k, waves)), dim3(kWave * waves), 0, s, in,
+                           out, k, flag);
+    return hipGetLastError();
+}
+
+hipError_t launch_two(bool walls, const void* fin, void* fout, const StepConst& k, int waves, int* flag, hipStream_t s)
+{
+    if (waves != kTwoWaves && waves != kTwoWavesWide) return hipErrorInvalidValue;
+    if (walls)
+        return k.psi_form == kPsiSS ? launch_two_psi<true, kPsiSS>(fin, fout, k, waves, flag, s)
+                                    : launch_two_psi<true, kPsiCS>(fin, fout, k, waves, flag, s);
+    return k.psi_form == kPsiSS ? launch_two_psi<false, kPsiSS>(fin, fout, k, waves, flag, s)
+                                : launch_two_psi<false, kPsiCS>(fin, fout, k, waves, flag, s);
 }
 
 // The 24-site stencil (FP32 storage; the host validates that): step, moments or

@@ -13,6 +13,11 @@ namespace lbmp {
 hipError_t launch_step(int store, bool walls, const void* fin, void* fout, const StepConst& k,
                        int* flag, hipStream_t s);
 
+// Two time steps: pull from `fin`, store the state two steps later into `fout` (FP32,
+// nearest-neighbour stencil, nx, ny >= 8; k.tiles_x counts kTwoTileW-column tiles).
+// waves: wavefronts per workgroup, kTwoWaves or kTwoWavesWide (results do not depend on it).
+hipError_t launch_two(bool walls, const void* fin, void* fout, const StepConst& k, int waves, int* flag, hipStream_t s);
+
 // Whether launch_step runs the two-columns-per-lane kernel for this store type
 // and lattice width (destination-scaled FP16, even nx).
 bool pair_step(int store, int nx);

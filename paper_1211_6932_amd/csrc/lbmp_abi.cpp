@@ -70,6 +70,16 @@ size_t density_plane_bytes(int store)
 // encodings round to an even count so that their FP32 density row stays 4-byte aligned.
 int pitch_of(int nx, int store) { return local_density(store) ? (nx + 1) / 2 * 2 : nx; }
 
+// Whether lb_step advances this lattice two steps per launch (an odd last step is a single
+// one).  FP32 with the nearest-neighbour stencil, at every size: 8192 x 4096 428 -> 248 us
+// per step, 2048 x 1024 28 -> 16 us, 600 x 250 7.2 -> 5.3 us, 128 x 128 7.6 -> 4.2 us.  The
+// walk pulls up to four rows beyond a strip and wraps a row or column index once, hence the
+// least size.
+bool two_step(const lb_params& p)
+{
+    return p.store == LB_STORE_F32 && p.stencil == LB_STENCIL_NEAREST && p.nx >= 8 && p.ny >= 8;
+}
+
 // Output columns per wavefront strip of the one-column kernels for this stencil.
 int tile_width(const lb_params& p) { return p.stencil == LB_STENCIL_MULTIRANGE ? lbmp::kMrTileW : lbmp::kTileW; }
 
@@ -190,6 +200,59 @@ lbmp::StepConst derive(const lb_params& p, int strip_rows, int band = 1)
     return k;
 }
 
+// Constants of a launch of two steps: 58-column tiles.
+lbmp::StepConst derive_two(const lb_params& p, int strip_rows, int band = 1)
+{
+    lbmp::StepConst k = derive(p, strip_rows, band);
+    k.tiles_x = (p.nx + lbmp::kTwoTileW - 1) / lbmp::kTwoTileW;
+    return k;
+}
+
+int compute_units()
+{
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu <= 0)
+        return 256;
+    return ncu;
+}
+
+// Wavefronts per workgroup of the two-step launches: 8 pace a wider stretch of a row
+// (8192 x 4096: 250 us per step against 256 us with 4), 4 fill the chip more evenly when
+// there are few strips per compute unit (2048 x 1024: 16.0 us against 16.5 us at the best
+// height of each, 18.2 us against 21.6 us at 16 rows).
+int two_waves(const lb_params& p, int rows)
+{
+    const lbmp::StepConst k = derive_two(p, rows);
+    return (long long)k.tiles_x * k.tiles_y >= 16LL * 4 * compute_units() ? lbmp::kTwoWavesWide : lbmp::kTwoWaves;
+}
+
+// Strip height of the two-step launches.  A strip of h rows costs about h + 5 rows of work;
+// a SIMD that holds w of its strips (at most four at once) needs about 0.36 + 0.17 w per
+// row, in microseconds (fitted on 2048 x 1024 at heights 4-24: 16.0 us per step at 10 rows,
+// where every strip is resident at once, 18.2 us at 8 rows, 19.9 us at 4 rows, 20.5 us at
+// 24 rows).  On large lattices the cost falls slowly with h and the stride of the resident
+// strips decides: 8192 x 4096 at 8 / 12 / 16 / 22 / 36 rows 255 / 248 / 247 / 248 / 268 us.
+// On small ones the walk itself is the time: 128 x 128 at 2 / 3 / 4 / 8 rows 4.1 / 4.9 /
+// 5.2 / 7.8 us.
+int auto_two_rows(const lb_params& p)
+{
+    const int ncu = compute_units();
+    int best = 2;
+    double least = 1e300;
+    for (int h = 2; h <= 18 && h <= p.ny; ++h) {
+        const lbmp::StepConst k = derive_two(p, h);
+        const long long groups = ((long long)k.tiles_x * k.tiles_y + lbmp::kTwoWaves - 1) / lbmp::kTwoWaves;
+        const double load = (double)((groups + ncu - 1) / ncu);  // waves per SIMD
+        const double cost = (h + 5) * (0.36 * std::ceil(load / 4.0) + 0.17 * load);
+        if (cost < least) {
+            least = cost;
+            best = h;
+        }
+    }
+    return best;
+}
+
 // Strip height for the step kernel.  Short strips are fastest on large grids
 // even though they re-read two halo rows per strip: the tiles are numbered
 // row-band by row-band, so the resident wavefronts work on a narrow band of
@@ -240,6 +303,9 @@ struct lb_ctx {
     lb_params p;
     Layout L;
     lbmp::StepConst k;   // step launches
+    lbmp::StepConst k2;  // launches of two steps (two == true)
+    int waves2;          // wavefronts per workgroup of those launches
+    bool two;
     lbmp::StepConst kd;  // moments / diagnostics launches
     char* ws;
     void* f[2];
@@ -252,6 +318,7 @@ struct lb_ctx {
     int graph_chunk;
     hipGraph_t graph[2];
     hipGraphExec_t exec[2];
+    int graph_end[2];    // buffer that holds the state after the graph captured from each buffer
     bool poisoned;
 };
 
@@ -267,17 +334,28 @@ void drop_graphs(lb_ctx* c)
     }
 }
 
+// One launch from buffer `cur` into the other one: two steps where the lattice is stepped
+// that way and `left` allows it, else one.  *steps receives the number of steps taken.
+hipError_t launch_some(lb_ctx* c, int cur, int64_t left, int* steps)
+{
+    const bool walls = c->p.bc == LB_BC_WALLS_Y;
+    *steps = c->two && left >= 2 ? 2 : 1;
+    if (*steps == 2) return lbmp::launch_two(walls, c->f[cur], c->f[cur ^ 1], c->k2, c->waves2, c->flag, c->stream);
+    return lbmp::launch_step(c->p.store, walls, c->f[cur], c->f[cur ^ 1], c->k, c->flag, c->stream);
+}
+
 lb_status step_direct(lb_ctx* c, int64_t n)
 {
-    for (int64_t i = 0; i < n; ++i) {
-        hipError_t e = lbmp::launch_step(c->p.store, c->p.bc == LB_BC_WALLS_Y, c->f[c->cur],
-                                         c->f[c->cur ^ 1], c->k, c->flag, c->stream);
+    while (n > 0) {
+        int steps = 0;
+        const hipError_t e = launch_some(c, c->cur, n, &steps);
         if (e != hipSuccess) {
             c->poisoned = true;
             return hip_fail(e, "step launch");
         }
         c->cur ^= 1;
-        c->t += 1;
+        c->t += steps;
+        n -= steps;
     }
     return LB_OK;
 }
@@ -288,9 +366,10 @@ lb_status build_graph(lb_ctx* c, int from)
     if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
     int cur = from;
     hipError_t le = hipSuccess;
-    for (int i = 0; i < c->graph_chunk && le == hipSuccess; ++i) {
-        le = lbmp::launch_step(c->p.store, c->p.bc == LB_BC_WALLS_Y, c->f[cur], c->f[cur ^ 1], c->k,
-                               c->flag, c->stream);
+    for (int left = c->graph_chunk; left > 0 && le == hipSuccess;) {
+        int steps = 0;
+        le = launch_some(c, cur, left, &steps);
+        left -= steps;
         cur ^= 1;
     }
     hipGraph_t g = nullptr;
@@ -308,6 +387,7 @@ lb_status build_graph(lb_ctx* c, int from)
     }
     c->graph[from] = g;
     c->exec[from] = x;
+    c->graph_end[from] = cur;
     return LB_OK;
 }
 
@@ -364,6 +444,9 @@ lb_status init_ctx(lb_ctx** out, const lb_params* p, void* workspace, size_t wor
     c->p = *p;
     c->L = L;
     c->k = derive(*p, auto_strip_rows(*p), kDefaultBand);
+    c->two = two_step(*p);
+    c->k2 = derive_two(*p, auto_two_rows(*p), kDefaultBand);
+    c->waves2 = two_waves(*p, c->k2.strip_rows);
     c->kd = derive(*p, kDiagStripRows);
     c->ws = static_cast<char*>(workspace);
     c->flag = reinterpret_cast<int*>(c->ws + L.flag_off);
@@ -432,7 +515,8 @@ lb_status lb_step(lb_ctx* c, int64_t n)
                 return hip_fail(e, "hipGraphLaunch");
             }
             n -= c->graph_chunk;
-            c->t += c->graph_chunk;  // chunk is even: the state returns to buffer cur
+            c->t += c->graph_chunk;
+            c->cur = c->graph_end[c->cur];
         }
     }
     return step_direct(c, n);
@@ -568,12 +652,17 @@ lb_status lb_set_launch(lb_ctx* c, int32_t strip_rows, int32_t band, int32_t gra
     if (graph_chunk != 0 && (graph_chunk < 2 || graph_chunk % 2))
         return fail(LB_EINVAL, "graph_chunk must be even and >= 2");
     drop_graphs(c);
-    int rows = c->k.strip_rows, bd = c->k.band;
-    if (strip_rows > 0) rows = strip_rows;
-    if (strip_rows == -1) rows = auto_strip_rows(c->p);
+    int rows = c->k.strip_rows, rows2 = c->k2.strip_rows, bd = c->k.band;
+    if (strip_rows > 0) rows = rows2 = strip_rows;
+    if (strip_rows == -1) {
+        rows = auto_strip_rows(c->p);
+        rows2 = auto_two_rows(c->p);
+    }
     if (band > 0) bd = band;
     if (band == -1) bd = kDefaultBand;
     c->k = derive(c->p, rows, bd);
+    c->k2 = derive_two(c->p, rows2, bd);
+    c->waves2 = two_waves(c->p, rows2);
     if (graph_chunk > 0) c->graph_chunk = graph_chunk;
     return LB_OK;
 }
