@@ -266,7 +266,8 @@ lb_status lb_batch_times(lb_batch* b, double* seconds);
  *                       lattices together (captured in graphs); best throughput;
  *                       lb_batch_times reports the same elapsed time for all.
  *                       Destination-scaled FP16 lattices with an even nx are
- *                       stepped two columns per lane in a second launch.
+ *                       stepped two columns per lane in a second launch.  FP32
+ *                       lattices, each at least 8 x 8, are stepped twice per launch.
  *   LB_BATCH_PERSISTENT one launch per lb_batch_step call, one workgroup per
  *                       lattice for all steps; per-lattice completion times.
  * strip_rows: rows per wavefront strip for every lattice, in [1, 64]; 0 = the
@@ -285,7 +286,9 @@ lb_status lb_batch_set_launch(lb_batch* b, int32_t mode, int32_t strip_rows);
  * overwrites in full, so the state and the time are unchanged; a lattice that is
  * already unstable may set its unstable flag, as its next step would.  Clears a
  * fixed strip height set by lb_batch_set_launch.  rows_out (host array of n, may be
- * NULL) receives each lattice's height.  Stepwise mode only; needs a stream other
+ * NULL) receives each lattice's height.  For FP32 batches stepped twice per launch the
+ * height of those launches is then chosen the same way among eight heights from 4 to 20
+ * (rows_out keeps the height of single steps).  Stepwise mode only; needs a stream other
  * than the legacy one; synchronises it. */
 lb_status lb_batch_tune(lb_batch* b, int32_t trial_steps, int32_t* rows_out);
 

@@ -694,6 +694,13 @@ namespace {
 constexpr int kMaxStripRows = 64;
 constexpr int kTuneMaxRows = 8;
 
+// Two-step launches (FP32), the same sweep, by strip rows: 4: 101k  6: 114k  8: 119k
+// 10: 121k  12: 122k  16: 120k  24: 119k  48: 111k (73.5k with the best single-step height);
+// 96 lattices of 256 x 256: 8: 108k  12: 108k  16: 109k  48: 104k (57k).  One height serves
+// every width.
+constexpr int kBatchTwoRows = 12;
+constexpr int kTuneTwoRows[] = {4, 6, 8, 10, 12, 14, 16, 20};
+
 int default_batch_rows(int store)
 {
     if (store == LB_STORE_F16_DEST) return 8;
@@ -715,6 +722,13 @@ struct lb_batch {
     // its workgroup table at wg_first + wg_off[g].
     int gfirst[2], gcount[2], ntotal[2];
     size_t wg_off[2];
+    // FP32 lattices (all of them group 0) of at least 8 x 8 are stepped two at a time in the
+    // stepwise mode, with descriptors and tables of their own (same dispatch order).
+    bool two;
+    int two_rows, two_ntotal;
+    lbmp::BatchInstance* two_desc;
+    int *two_start, *two_first;
+    size_t two_capacity;
     int* tile_start;                 // device, n + 2 entries
     int* wg_first;                   // device, lattice of each workgroup's first tile
     size_t wg_capacity;              // entries available in wg_first
@@ -746,9 +760,32 @@ size_t batch_wg_capacity(const lb_params* p, int n)
     return tiles / wpb + 4;
 }
 
+// Whether the stepwise batch advances two steps per launch.
+bool batch_two(const lb_params* p, int n)
+{
+    for (int i = 0; i < n; ++i)
+        if (!two_step(p[i])) return false;
+    return true;
+}
+
+// Upper bound of the workgroups of the two-step launch (one-row strips).
+size_t batch_two_capacity(const lb_params* p, int n)
+{
+    size_t tiles = 0;
+    for (int i = 0; i < n; ++i) tiles += (size_t)((p[i].nx + lbmp::kTwoTileW - 1) / lbmp::kTwoTileW) * p[i].ny;
+    return tiles / lbmp::kTwoWavesBatch + 1;
+}
+
+size_t batch_two_bytes(const lb_params* p, int n)
+{
+    if (!batch_two(p, n)) return 0;
+    return align_up((size_t)n * sizeof(lbmp::BatchInstance), kAlign) + align_up((size_t)(n + 1) * sizeof(int), kAlign) +
+           align_up(batch_two_capacity(p, n) * sizeof(int), kAlign);
+}
+
 size_t batch_header_bytes(const lb_params* p, int n)
 {
-    return align_up((size_t)n * sizeof(lbmp::BatchInstance), kAlign) + align_up((size_t)n * 16, kAlign) +
+    return batch_two_bytes(p, n) + align_up((size_t)n * sizeof(lbmp::BatchInstance), kAlign) + align_up((size_t)n * 16, kAlign) +
            align_up((size_t)(n + 2) * sizeof(int), kAlign) + align_up(batch_wg_capacity(p, n) * sizeof(int), kAlign);
 }
 
@@ -831,12 +868,36 @@ hipError_t write_batch_descriptors(lb_batch* b)
         woff += (size_t)blocks;
     }
     if (woff > b->wg_capacity) return hipErrorInvalidValue;
+    std::vector<lbmp::BatchInstance> host2;
+    std::vector<int> start2, first2;
+    if (b->two && b->mode == LB_BATCH_STEPWISE) {
+        host2 = host;
+        start2.assign(n + 1, 0);
+        for (int j = 0; j < n; ++j) {
+            const int rows = b->fixed_rows > 0 ? b->fixed_rows : b->two_rows;
+            host2[j].k = derive_two(b->inst[b->order[j]]->p, rows);
+            start2[j + 1] = start2[j] + host2[j].k.tiles_x * host2[j].k.tiles_y;
+        }
+        b->two_ntotal = start2[n];
+        for (int t = 0, i = 0; t < b->two_ntotal; t += lbmp::kTwoWavesBatch) {
+            while (t >= start2[i + 1]) ++i;
+            first2.push_back(i);
+        }
+        if (first2.size() > b->two_capacity) return hipErrorInvalidValue;
+    }
     hipError_t e = hipMemcpyAsync(b->desc, host.data(), n * sizeof(lbmp::BatchInstance), hipMemcpyHostToDevice,
                                   b->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->tile_start, start.data(), start.size() * sizeof(int), hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess && !first.empty())
         e = hipMemcpyAsync(b->wg_first, first.data(), first.size() * sizeof(int), hipMemcpyHostToDevice, b->stream);
+    if (e == hipSuccess && !host2.empty()) {
+        e = hipMemcpyAsync(b->two_desc, host2.data(), n * sizeof(lbmp::BatchInstance), hipMemcpyHostToDevice, b->stream);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(b->two_start, start2.data(), start2.size() * sizeof(int), hipMemcpyHostToDevice, b->stream);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(b->two_first, first2.data(), first2.size() * sizeof(int), hipMemcpyHostToDevice, b->stream);
+    }
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     return e;
 }
@@ -854,12 +915,28 @@ hipError_t batch_flat_launch(lb_batch* b, int parity)
     return e;
 }
 
+// One launch reading buffer `parity`: two steps where the batch is stepped that way and
+// `left` allows it, else one.  *steps receives the number of steps taken.
+hipError_t batch_launch_some(lb_batch* b, int parity, int64_t left, int* steps)
+{
+    *steps = b->two && left >= 2 ? 2 : 1;
+    if (*steps == 1) return batch_flat_launch(b, parity);
+    return lbmp::launch_batch_two(b->bc == LB_BC_WALLS_Y, b->psi, b->two_desc, b->two_start, b->two_first, b->two_ntotal,
+                                  parity, b->stream);
+}
+
 lb_status build_batch_graph(lb_batch* b, int from)
 {
     hipError_t e = hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
     hipError_t le = hipSuccess;
-    for (int i = 0; i < kDefaultGraphChunk && le == hipSuccess; ++i) le = batch_flat_launch(b, from ^ (i & 1));
+    static_assert(kDefaultGraphChunk % 4 == 0, "a graph returns to the buffer it starts from");
+    int parity = from;
+    for (int left = kDefaultGraphChunk; left > 0 && le == hipSuccess; parity ^= 1) {
+        int steps = 0;
+        le = batch_launch_some(b, parity, left, &steps);
+        left -= steps;
+    }
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(b->stream, &g);
     if (le != hipSuccess) {
@@ -934,6 +1011,17 @@ lb_status lb_batch_init(lb_batch** out, const lb_params* p, int32_t n, void* wor
     hoff += align_up((size_t)(n + 2) * sizeof(int), kAlign);
     b->wg_first = reinterpret_cast<int*>(ws + hoff);
     b->wg_capacity = batch_wg_capacity(p, n);
+    hoff += align_up(b->wg_capacity * sizeof(int), kAlign);
+    b->two = batch_two(p, n);
+    if (b->two) {
+        b->two_rows = kBatchTwoRows;
+        b->two_desc = reinterpret_cast<lbmp::BatchInstance*>(ws + hoff);
+        hoff += align_up((size_t)n * sizeof(lbmp::BatchInstance), kAlign);
+        b->two_start = reinterpret_cast<int*>(ws + hoff);
+        hoff += align_up((size_t)(n + 1) * sizeof(int), kAlign);
+        b->two_first = reinterpret_cast<int*>(ws + hoff);
+        b->two_capacity = batch_two_capacity(p, n);
+    }
     b->mode = LB_BATCH_STEPWISE;
     hipError_t ee = hipEventCreate(&b->ev[0]);
     if (ee == hipSuccess) ee = hipEventCreate(&b->ev[1]);
@@ -988,6 +1076,7 @@ lb_status lb_batch_step(lb_batch* b, int64_t nsteps)
     if (b->mode == LB_BATCH_PERSISTENT) {
         e = lbmp::launch_batch(b->store, b->bc == LB_BC_WALLS_Y, b->psi, b->desc, b->n, (int)nsteps, parity, b->clocks,
                                b->stream);
+        parity ^= (int)(nsteps & 1);
     } else {
         e = hipEventRecord(b->ev[0], b->stream);
         int64_t left = nsteps;
@@ -1000,11 +1089,12 @@ lb_status lb_batch_step(lb_batch* b, int64_t nsteps)
                 }
             }
             e = hipGraphLaunch(b->exec[parity], b->stream);
-            left -= kDefaultGraphChunk;  // even: the parity is unchanged
+            left -= kDefaultGraphChunk;  // an even number of launches: the parity is unchanged
         }
-        for (; e == hipSuccess && left > 0; --left) {
-            e = batch_flat_launch(b, parity);
-            parity ^= 1;
+        for (; e == hipSuccess && left > 0; parity ^= 1) {
+            int steps = 0;
+            e = batch_launch_some(b, parity, left, &steps);
+            left -= steps;
         }
         if (e == hipSuccess) e = hipEventRecord(b->ev[1], b->stream);
     }
@@ -1013,7 +1103,7 @@ lb_status lb_batch_step(lb_batch* b, int64_t nsteps)
         return hip_fail(e, "batch launch");
     }
     for (lb_ctx* c : b->inst) {
-        c->cur ^= (int)(nsteps & 1);
+        c->cur = parity;
         c->t += nsteps;
     }
     return LB_OK;
@@ -1153,13 +1243,15 @@ lb_status lb_batch_tune(lb_batch* b, int32_t trial_steps, int32_t* rows_out)
     // Seconds of `trial_steps` launches that all read buffer `parity` and write the
     // other one: the state (buffer parity) is unchanged, and the other buffer is
     // overwritten in full by the next step.  The least of three repetitions.
-    auto time_launches = [&](double& sec) -> hipError_t {
+    // at_once = 1: single-step launches, 2: two-step launches.
+    auto time_launches = [&](int at_once, double& sec) -> hipError_t {
+        int steps = 0;
         hipError_t e = write_batch_descriptors(b);
-        for (int w = 0; w < 2 && e == hipSuccess; ++w) e = batch_flat_launch(b, parity);
+        for (int w = 0; w < 2 && e == hipSuccess; ++w) e = batch_launch_some(b, parity, at_once, &steps);
         sec = 1e30;
         for (int rep = 0; rep < 3 && e == hipSuccess; ++rep) {
             e = hipEventRecord(b->ev[0], b->stream);
-            for (int t = 0; t < trial_steps && e == hipSuccess; ++t) e = batch_flat_launch(b, parity);
+            for (int t = 0; t < trial_steps && e == hipSuccess; ++t) e = batch_launch_some(b, parity, at_once, &steps);
             if (e == hipSuccess) e = hipEventRecord(b->ev[1], b->stream);
             if (e == hipSuccess) e = hipEventSynchronize(b->ev[1]);
             float ms = 0.0f;
@@ -1180,7 +1272,7 @@ lb_status lb_batch_tune(lb_batch* b, int32_t trial_steps, int32_t* rows_out)
         for (int cand = 1; cand <= kTuneMaxRows && e == hipSuccess; ++cand) {
             b->group_rows[g] = cand;
             double sec = 0.0;
-            e = time_launches(sec);
+            e = time_launches(1, sec);
             if (e == hipSuccess && sec < best) {
                 best = sec;
                 best_r = cand;
@@ -1191,6 +1283,24 @@ lb_status lb_batch_tune(lb_batch* b, int32_t trial_steps, int32_t* rows_out)
             b->poisoned = true;
             return hip_fail(e, "lb_batch_tune trial launches");
         }
+    }
+    if (b->two) {
+        int best_r = b->two_rows;
+        double best = 1e30;
+        for (const int cand : kTuneTwoRows) {
+            b->two_rows = cand;
+            double sec = 0.0;
+            const hipError_t e = time_launches(2, sec);
+            if (e != hipSuccess) {
+                b->poisoned = true;
+                return hip_fail(e, "lb_batch_tune trial launches");
+            }
+            if (sec < best) {
+                best = sec;
+                best_r = cand;
+            }
+        }
+        b->two_rows = best_r;
     }
     hipError_t e = write_batch_descriptors(b);
     if (e != hipSuccess) return hip_fail(e, "batch descriptors");

@@ -67,3 +67,31 @@ def test_graphs_of_any_even_length_end_in_the_right_buffer(chunk):
     b.step(33).step(3).step(39)
     assert np.array_equal(state(a), state(b))
     a.close(), b.close()
+
+
+@pytest.mark.parametrize("bc", [0, 1])
+def test_batch_two_steps_per_launch(bc):
+    """Lattices of 8 to 174 columns in one batch, odd and even step counts across calls and a
+    captured graph, default and fixed heights, against single steps of each lattice alone; a
+    batch with a lattice below 8 x 8 (stepped one at a time) gives the same states."""
+    sizes = [(8, 8), (58, 9), (174, 65), (61, 40)]
+    ls = [lattice(nx, ny, bc) for nx, ny in sizes]
+    refs = []
+    for p, rho, ux, uy in ls:
+        s = B.Sim(p, rho, ux, uy)
+        for _ in range(42):
+            s.step(1)
+        refs.append(state(s))
+        s.close()
+    for rows, extra in ((0, False), (1, False), (5, False), (64, False), (0, True)):
+        print(f"[gpu-case] batch two steps bc={bc} rows={rows} small={extra}", flush=True)
+        more = [lattice(7, 7, bc)] if extra else []
+        b = B.Batch([l[0] for l in ls + more], [l[1] for l in ls + more], [l[2] for l in ls + more],
+                    [l[3] for l in ls + more])
+        if rows:
+            b.set_launch(B.LB_BATCH_STEPWISE, rows)
+        b.step(3).step(4).step(35)
+        assert b.check() == (B.LB_OK, 0)
+        for i, (l, ref) in enumerate(zip(ls, refs)):
+            assert np.array_equal(b.get_state(i, B.lb_state_bytes(B.make_params(l[0], "f32"))).cpu().numpy(), ref), (rows, i)
+        b.close()
