@@ -42,6 +42,7 @@ constexpr int kBatchWaves = 16;       // wavefronts per workgroup (= per lattice
 constexpr int kBatchWavesDest = 4;
 constexpr int kNumXcd = 8;            // MI355X: 8 accelerator complex dies, one L2 each
 constexpr int kDiagFields = 10;       // doubles per wave partial in the diagnostics pass
+constexpr int kDiagOut = kDiagFields + 1;  // doubles per finished diagnostics: the sums, then the flag word
 
 enum : int { kStoreF32 = 0, kStoreF16 = 1, kStoreBF16 = 2, kStoreF16Local = 3, kStoreBF16Local = 4, kStoreF16Dest = 5 };
 
@@ -55,6 +56,11 @@ constexpr int step_waves_per_block(int store)
     return store == kStoreF16Dest ? 4 : kWavesPerBlock;
 }
 enum : int { kModeStep = 0, kModeMoments = 1, kModeDiag = 2 };
+// Moments and diagnostics passes: small workgroups, which spread a small lattice over the
+// chip and leave the FP64 diagnostics the registers they need (with 16 waves per workgroup
+// the 128-register limit makes them spill).
+constexpr int kPassWaves = 4;
+constexpr int waves_per_block(int store, int mode) { return mode == kModeStep ? step_waves_per_block(store) : kPassWaves; }
 enum : int { kFlagUnstable = 1, kFlagBadInput = 2 };
 enum : int { kPsiCS = 0, kPsiSS = 1 };  // psi of Eq. (24) from Eq. (30), or of Eq. (23)
 enum : int { kStencilNearest = 0, kStencilMultirange = 1 };  // interaction stencil of Eq. (7)
@@ -123,6 +129,14 @@ struct DiagConst {
     double out_cx, out_cy, out_r0, out_r1;
     PsiConst psi;  // FP64 copies for the bulk pressure
     int periodic_y;
+};
+
+// One lattice of a batched diagnostics pass.
+struct DiagInstance {
+    StepConst k;
+    const void* f[2];
+    int* flag;
+    double* partial;  // one record of kDiagFields per tile of k
 };
 
 // ---------------------------------------------------------------- storage codecs

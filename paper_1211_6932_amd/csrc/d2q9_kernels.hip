@@ -279,7 +279,7 @@ __device__ __forceinline__ void strip_tile(
 }
 
 template <int S, bool WALLS, int MODE, int PSI>
-__global__ __launch_bounds__(kWave * step_waves_per_block(S))
+__global__ __launch_bounds__(kWave * waves_per_block(S, MODE))
 __attribute__((amdgpu_waves_per_eu(1))) void d2q9_strip(
     const typename Codec<S>::T* __restrict__ fin, typename Codec<S>::T* __restrict__ fout,
     StepConst k, int* __restrict__ flag, float* __restrict__ rho_out, float* __restrict__ ux_out,
@@ -289,7 +289,7 @@ __attribute__((amdgpu_waves_per_eu(1))) void d2q9_strip(
     // the wave index is uniform across the wave: keep it (and every row address
     // derived from it) in scalar registers
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int tile = logical_block(blockIdx.x, gridDim.x) * step_waves_per_block(S) + wave;
+    const int tile = logical_block(blockIdx.x, gridDim.x) * waves_per_block(S, MODE) + wave;
     if (tile >= k.tiles_x * k.tiles_y) return;  // whole wavefront leaves together
     strip_tile<S, WALLS, MODE, PSI>(fin, fout, k, tile, lane, flag, rho_out, ux_out, uy_out, dg, partial);
 }
@@ -728,14 +728,14 @@ __device__ __forceinline__ void mr_walk(const float* __restrict__ fin, float* __
 }
 
 template <bool WALLS, int MODE, int PSI>
-__global__ __launch_bounds__(kWave * kWavesPerBlock) void d2q9_mr(
+__global__ __launch_bounds__(kWave * waves_per_block(kStoreF32, MODE)) void d2q9_mr(
     const float* __restrict__ fin, float* __restrict__ fout, StepConst k, int* __restrict__ flag,
     float* __restrict__ rho_out, float* __restrict__ ux_out, float* __restrict__ uy_out, DiagConst dg,
     double* __restrict__ partial)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int tile = logical_block(blockIdx.x, gridDim.x) * kWavesPerBlock + wave;
+    const int tile = logical_block(blockIdx.x, gridDim.x) * waves_per_block(kStoreF32, MODE) + wave;
     if (tile >= k.tiles_x * k.tiles_y) return;  // whole wavefront leaves together
     // tiles in bands of `band` strips, as strip_tile (k.tiles_x counts 60-column tiles)
     const int band0 = (tile / (k.tiles_x * k.band)) * k.band;
@@ -790,8 +790,8 @@ __global__ __launch_bounds__(kWave * kBatchWaves) void d2q9_batch(
 // wg_first[b] is the lattice of workgroup b's first tile, so each wavefront
 // finds its lattice by a short forward scan.  WPB wavefronts (strips) per
 // workgroup, XCD-aware renumbering as the single-lattice step.
-template <int WPB>
-__device__ __forceinline__ const BatchInstance* flat_lattice(const BatchInstance* __restrict__ inst,
+template <int WPB, class Inst>
+__device__ __forceinline__ const Inst* flat_lattice(const Inst* __restrict__ inst,
                                                              const int* __restrict__ tile_start,
                                                              const int* __restrict__ wg_first, int ntotal, int& g)
 {
@@ -852,9 +852,30 @@ __attribute__((amdgpu_waves_per_eu(4))) void d2q9_batch_two(
                          threadIdx.x & (kWave - 1), I->flag);
 }
 
-// Single-block, fixed-order reduction of per-wave partials (deterministic).
-__global__ __launch_bounds__(256) void diag_finalize(const double* __restrict__ partial, int ntiles,
-                                                     double* __restrict__ out)
+// Diagnostics of every lattice of a batch in one launch; each wavefront writes the partial of
+// one strip, as the single-lattice pass does for the same lattice.  Bound by FP64 arithmetic
+// (pressure and two distances per site): 727 us for the 512-lattice sweep (51.8 M sites),
+// where one pass and two copies per lattice took 42 ms.
+template <int S, bool WALLS, int PSI>
+__global__ __launch_bounds__(kWave * kPassWaves)
+__attribute__((amdgpu_waves_per_eu(1))) void d2q9_batch_diag(
+    const DiagInstance* __restrict__ inst, const DiagConst* __restrict__ regions, const int* __restrict__ tile_start,
+    const int* __restrict__ wg_first, int ntotal, int parity)
+{
+    int g;
+    const DiagInstance* I = flat_lattice<kPassWaves>(inst, tile_start, wg_first, ntotal, g);
+    if (!I) return;
+    const StepConst k = I->k;
+    const DiagConst dg = regions[I - inst];
+    using T = typename Codec<S>::T;
+    strip_tile<S, WALLS, kModeDiag, PSI>(reinterpret_cast<const T*>(I->f[parity]), nullptr, k, g,
+                                         threadIdx.x & (kWave - 1), I->flag, nullptr, nullptr, nullptr, dg, I->partial);
+}
+
+// Fixed-order reduction of per-wave partials by one workgroup (deterministic); the last entry
+// of `out` is the lattice's flag word.
+__device__ __forceinline__ void diag_reduce(const double* __restrict__ partial, int ntiles, const int* __restrict__ flag,
+                                            double* __restrict__ out)
 {
     __shared__ double sh[256][kDiagFields];
     double acc[kDiagFields];
@@ -873,6 +894,27 @@ __global__ __launch_bounds__(256) void diag_finalize(const double* __restrict__ 
         __syncthreads();
     }
     if (threadIdx.x < kDiagFields) out[threadIdx.x] = sh[0][threadIdx.x];
+    if (threadIdx.x == kDiagFields) out[kDiagFields] = (double)flag[0];
+}
+
+__global__ __launch_bounds__(256) void diag_finalize(const double* __restrict__ partial, int ntiles,
+                                                     const int* __restrict__ flag, double* __restrict__ out)
+{
+    diag_reduce(partial, ntiles, flag, out);
+}
+
+// The same for every lattice of a batch, one workgroup each.
+__global__ __launch_bounds__(256) void batch_diag_finalize(const DiagInstance* __restrict__ inst, double* __restrict__ out)
+{
+    const DiagInstance& I = inst[blockIdx.x];
+    diag_reduce(I.partial, I.k.tiles_x * I.k.tiles_y, I.flag, out + (long long)blockIdx.x * kDiagOut);
+}
+
+// The flag words of a batch's lattices, gathered.
+__global__ void batch_flags(const DiagInstance* __restrict__ inst, int n, int* __restrict__ out)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) out[i] = inst[i].flag[0];
 }
 
 // Initial state.  Slot (z, b) of the stored (pre-streamed) buffer holds the
@@ -1022,8 +1064,8 @@ static hipError_t launch_mode(const void* fin, void* fout, const StepConst& k, i
                               double* partial, hipStream_t s)
 {
     using T = typename Codec<S>::T;
-    constexpr int wpb = step_waves_per_block(S);
-    const size_t lds = occupancy_cap_lds(S == kStoreF16Dest ? kDestBlocksPerCu : 0);
+    constexpr int wpb = waves_per_block(S, MODE);
+    const size_t lds = occupancy_cap_lds(S == kStoreF16Dest && MODE == kModeStep ? kDestBlocksPerCu : 0);
     hipLaunchKernelGGL((d2q9_strip<S, WALLS, MODE, PSI>), dim3(strip_blocks(k, wpb)),
                        dim3(kWave * wpb), lds, s, static_cast<const T*>(fin),
                        static_cast<T*>(fout), k, flag, rho, ux, uy, dg, partial);
@@ -1148,7 +1190,8 @@ template <int MODE>
 static hipError_t launch_mr(bool walls, const void* fin, void* fout, const StepConst& k, int* flag, float* rho,
                             float* ux, float* uy, const DiagConst& dg, double* partial, hipStream_t s)
 {
-    const dim3 grid(strip_blocks(k, kWavesPerBlock)), block(kWave * kWavesPerBlock);
+    constexpr int wpb = waves_per_block(kStoreF32, MODE);
+    const dim3 grid(strip_blocks(k, wpb)), block(kWave * wpb);
     const float* in = static_cast<const float*>(fin);
     float* out = static_cast<float*>(fout);
 #define LBMP_MR(W_, P_)                                                                            \
@@ -1286,7 +1329,41 @@ hipError_t launch_diag(int store, bool walls, const void* fin, const StepConst& 
     else
         e = dispatch<kModeDiag>(store, walls, fin, nullptr, k, flag, nullptr, nullptr, nullptr, dg, partial, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(diag_finalize, dim3(1), dim3(256), 0, s, partial, k.tiles_x * k.tiles_y, out);
+    hipLaunchKernelGGL(diag_finalize, dim3(1), dim3(256), 0, s, partial, k.tiles_x * k.tiles_y, flag, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_diag(int store, bool walls, int psi, const DiagInstance* inst, const DiagConst* regions, int n,
+                             const int* tile_start, const int* wg_first, int ntotal, int parity, double* out,
+                             hipStream_t s)
+{
+    if (n <= 0 || ntotal <= 0) return hipErrorInvalidValue;
+    const dim3 grid((ntotal + kPassWaves - 1) / kPassWaves), block(kWave * kPassWaves);
+#define LBMP_DIAGB(S_, W_)                                                                          \
+    do {                                                                                            \
+        if (psi == kPsiSS)                                                                          \
+            hipLaunchKernelGGL((d2q9_batch_diag<S_, W_, kPsiSS>), grid, block, 0, s, inst, regions, \
+                               tile_start, wg_first, ntotal, parity);                               \
+        else                                                                                        \
+            hipLaunchKernelGGL((d2q9_batch_diag<S_, W_, kPsiCS>), grid, block, 0, s, inst, regions, \
+                               tile_start, wg_first, ntotal, parity);                               \
+    } while (0)
+    switch (store) {
+    case kStoreF32: if (walls) LBMP_DIAGB(kStoreF32, true); else LBMP_DIAGB(kStoreF32, false); break;
+    case kStoreF16Local: if (walls) LBMP_DIAGB(kStoreF16Local, true); else LBMP_DIAGB(kStoreF16Local, false); break;
+    case kStoreF16Dest: if (walls) LBMP_DIAGB(kStoreF16Dest, true); else LBMP_DIAGB(kStoreF16Dest, false); break;
+    default: return hipErrorInvalidValue;
+    }
+#undef LBMP_DIAGB
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(batch_diag_finalize, dim3(n), dim3(256), 0, s, inst, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_flags(const DiagInstance* inst, int n, int* out, hipStream_t s)
+{
+    hipLaunchKernelGGL(batch_flags, dim3((n + 255) / 256), dim3(256), 0, s, inst, n, out);
     return hipGetLastError();
 }
 

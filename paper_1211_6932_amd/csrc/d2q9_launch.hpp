@@ -57,9 +57,18 @@ hipError_t launch_moments(int store, bool walls, const void* fin, const StepCons
                           float* rho, float* ux, float* uy, hipStream_t s);
 
 // FP64 reductions of the state in `fin`: per-wave partials, then a fixed-order
-// single-block pass into out[kDiagFields].
+// single-block pass into out[kDiagOut] (the sums and the flag word).
 hipError_t launch_diag(int store, bool walls, const void* fin, const StepConst& k, int* flag,
                        const DiagConst& dg, double* partial, double* out, hipStream_t s);
+
+// The same for n lattices in two launches: regions[i], out[i][kDiagOut]; tile_start and
+// wg_first as for launch_batch_flat with kPassWaves tiles per workgroup.
+hipError_t launch_batch_diag(int store, bool walls, int psi, const DiagInstance* inst, const DiagConst* regions, int n,
+                             const int* tile_start, const int* wg_first, int ntotal, int parity, double* out,
+                             hipStream_t s);
+
+// out[i] = flag word of lattice i.
+hipError_t launch_batch_flags(const DiagInstance* inst, int n, int* out, hipStream_t s);
 
 // Equilibrium initial state into `fout`; flag[0] = kFlagBadInput on invalid input.
 hipError_t launch_init(int store, bool walls, const float* rho0, const float* ux0,

@@ -33,7 +33,6 @@ lb_status hip_fail(hipError_t e, const char* what)
 }
 
 constexpr size_t kAlign = 256;
-constexpr int kDiagStripRows = 32;
 constexpr int kMinStripRows = 3;
 constexpr int kBatchPersistentRows = 24;  // measured best (one workgroup walks a whole lattice)
 constexpr int kDefaultBand = 1;
@@ -83,6 +82,17 @@ bool two_step(const lb_params& p)
 // Output columns per wavefront strip of the one-column kernels for this stencil.
 int tile_width(const lb_params& p) { return p.stencil == LB_STENCIL_MULTIRANGE ? lbmp::kMrTileW : lbmp::kTileW; }
 
+// Strip height of the diagnostics and moments passes, a function of the lattice alone (the
+// diagnostics' sums are reduced strip by strip): about 4000 strips where the lattice has
+// them, since a short walk is short in time (128 x 128: diagnostics 48 us at 32 rows, 7.3 us
+// at 4; moments of 200 x 200 30 us and 5 us), and not more than that, since one workgroup
+// sums up the strips.
+int pass_rows(const lb_params& p)
+{
+    const int tx = (p.nx + tile_width(p) - 1) / tile_width(p);
+    return (int)std::min<long long>(32, std::max<long long>(4, (long long)tx * p.ny / 4096));
+}
+
 struct Layout {
     size_t flag_off, dout_off, partial_off, f_off[2], total, buf_bytes;
     int diag_tiles;
@@ -95,7 +105,8 @@ Layout layout_of(const lb_params& p)
     L.buf_bytes = align_up((size_t)row_slots(p.store) * p.ny * pitch * elem_bytes(p.store), kAlign);
     const int tw = tile_width(p);
     const int tx = (p.nx + tw - 1) / tw;
-    const int ty = (p.ny + kDiagStripRows - 1) / kDiagStripRows;
+    const int rows = pass_rows(p);
+    const int ty = (p.ny + rows - 1) / rows;
     L.diag_tiles = tx * ty;
     L.flag_off = 0;
     L.dout_off = kAlign;
@@ -447,7 +458,7 @@ lb_status init_ctx(lb_ctx** out, const lb_params* p, void* workspace, size_t wor
     c->two = two_step(*p);
     c->k2 = derive_two(*p, auto_two_rows(*p), kDefaultBand);
     c->waves2 = two_waves(*p, c->k2.strip_rows);
-    c->kd = derive(*p, kDiagStripRows);
+    c->kd = derive(*p, pass_rows(*p));
     c->ws = static_cast<char*>(workspace);
     c->flag = reinterpret_cast<int*>(c->ws + L.flag_off);
     c->dout = reinterpret_cast<double*>(c->ws + L.dout_off);
@@ -540,9 +551,10 @@ static lbmp::DiagConst diag_const(const lb_ctx* c, const lb_region* in, const lb
 }
 
 // Host lb_diag from the finalised sums [mass, mom_x, mom_y, sum p_in, sum p_out,
-// sum rho_in, sum rho_out, n_in, n_out, max|u|] and the device flag word.
-static void fill_diag(const lb_ctx* c, const double* h, int hf, lb_diag* d)
+// sum rho_in, sum rho_out, n_in, n_out, max|u|, flag word].
+static void fill_diag(const lb_ctx* c, const double* h, lb_diag* d)
 {
+    const int hf = (int)h[lbmp::kDiagFields];
     std::memset(d, 0, sizeof(*d));
     d->mass = h[0];
     d->mom_x = h[1];
@@ -565,17 +577,15 @@ lb_status lb_diagnostics(lb_ctx* c, const lb_region* in, const lb_region* outr, 
     if (c->poisoned) return fail(LB_ESTATE, "context poisoned by an earlier failure");
     hipError_t e = lbmp::launch_diag(c->p.store, c->p.bc == LB_BC_WALLS_Y, c->f[c->cur], c->kd, c->flag,
                                      diag_const(c, in, outr), c->partial, c->dout, c->stream);
-    double h[lbmp::kDiagFields];
-    int hf = 0;
+    double h[lbmp::kDiagOut];
     if (e == hipSuccess)
         e = hipMemcpyAsync(h, c->dout, sizeof(h), hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(&hf, c->flag, sizeof(int), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) {
         c->poisoned = true;
         return hip_fail(e, "diagnostics");
     }
-    fill_diag(c, h, hf, d);
+    fill_diag(c, h, d);
     if (d->unstable) {
         c->poisoned = true;
         return fail(LB_EUNSTABLE, "unstable site (non-finite rho or psi^2 <= 0) since init");
@@ -740,6 +750,13 @@ struct lb_batch {
     std::vector<int> rows;           // strip height per lattice (current launch mode)
     lbmp::BatchInstance* desc;       // device descriptors in dispatch order
     unsigned long long* clocks;      // device, 2 per workgroup
+    // diagnostics of all lattices together (in lattice order)
+    lbmp::DiagInstance* diag;        // device, n
+    lbmp::DiagConst* regions;        // device, n
+    double* diag_out;                // device, n records of kDiagOut
+    int *diag_start, *diag_first;    // device, tile prefix sums (n + 1) and workgroup table
+    int* flags;                      // device, n
+    int diag_ntotal;
     hipStream_t stream;
     int store, bc, psi;
     bool poisoned;
@@ -783,9 +800,30 @@ size_t batch_two_bytes(const lb_params* p, int n)
            align_up(batch_two_capacity(p, n) * sizeof(int), kAlign);
 }
 
+int batch_diag_tiles(const lb_params* p, int n)
+{
+    long long tiles = 0;
+    for (int i = 0; i < n; ++i) tiles += layout_of(p[i]).diag_tiles;
+    return (int)std::min<long long>(tiles, 0x7fffffff);
+}
+
+// Sections of the diagnostics part of the header, in order: instances, regions, results,
+// tile prefix sums, workgroup table, flags.
+size_t batch_diag_sections(const lb_params* p, int n, size_t off[7])
+{
+    const size_t bytes[6] = {(size_t)n * sizeof(lbmp::DiagInstance), (size_t)n * sizeof(lbmp::DiagConst),
+                             (size_t)n * lbmp::kDiagOut * sizeof(double), (size_t)(n + 1) * sizeof(int),
+                             ((size_t)batch_diag_tiles(p, n) / lbmp::kPassWaves + 1) * sizeof(int),
+                             (size_t)n * sizeof(int)};
+    off[0] = 0;
+    for (int i = 0; i < 6; ++i) off[i + 1] = off[i] + align_up(bytes[i], kAlign);
+    return off[6];
+}
+
 size_t batch_header_bytes(const lb_params* p, int n)
 {
-    return batch_two_bytes(p, n) + align_up((size_t)n * sizeof(lbmp::BatchInstance), kAlign) + align_up((size_t)n * 16, kAlign) +
+    size_t off[7];
+    return batch_diag_sections(p, n, off) + batch_two_bytes(p, n) + align_up((size_t)n * sizeof(lbmp::BatchInstance), kAlign) + align_up((size_t)n * 16, kAlign) +
            align_up((size_t)(n + 2) * sizeof(int), kAlign) + align_up(batch_wg_capacity(p, n) * sizeof(int), kAlign);
 }
 
@@ -898,6 +936,42 @@ hipError_t write_batch_descriptors(lb_batch* b)
         if (e == hipSuccess)
             e = hipMemcpyAsync(b->two_first, first2.data(), first2.size() * sizeof(int), hipMemcpyHostToDevice, b->stream);
     }
+    if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
+    return e;
+}
+
+// Copy the descriptors of the diagnostics passes to the device.
+hipError_t write_diag_descriptors(lb_batch* b)
+{
+    const int n = b->n;
+    std::vector<lbmp::DiagInstance> host(n);
+    std::vector<int> start(n + 1, 0), first;
+    for (int i = 0; i < n; ++i) {
+        const lb_ctx* c = b->inst[i];
+        host[i] = lbmp::DiagInstance{c->kd, {c->f[0], c->f[1]}, c->flag, c->partial};
+        start[i + 1] = start[i] + c->kd.tiles_x * c->kd.tiles_y;
+    }
+    b->diag_ntotal = start[n];
+    for (int t = 0, i = 0; t < b->diag_ntotal; t += lbmp::kPassWaves) {
+        while (t >= start[i + 1]) ++i;
+        first.push_back(i);
+    }
+    hipError_t e = hipMemcpyAsync(b->diag, host.data(), host.size() * sizeof(host[0]), hipMemcpyHostToDevice, b->stream);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(b->diag_start, start.data(), start.size() * sizeof(int), hipMemcpyHostToDevice, b->stream);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(b->diag_first, first.data(), first.size() * sizeof(int), hipMemcpyHostToDevice, b->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
+    return e;
+}
+
+// The flag words of all lattices; synchronises.
+hipError_t read_batch_flags(lb_batch* b, std::vector<int>& flags)
+{
+    flags.assign(b->n, 0);
+    hipError_t e = lbmp::launch_batch_flags(b->diag, b->n, b->flags, b->stream);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(flags.data(), b->flags, flags.size() * sizeof(int), hipMemcpyDeviceToHost, b->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     return e;
 }
@@ -1021,7 +1095,16 @@ lb_status lb_batch_init(lb_batch** out, const lb_params* p, int32_t n, void* wor
         hoff += align_up((size_t)(n + 1) * sizeof(int), kAlign);
         b->two_first = reinterpret_cast<int*>(ws + hoff);
         b->two_capacity = batch_two_capacity(p, n);
+        hoff += align_up(b->two_capacity * sizeof(int), kAlign);
     }
+    size_t sec[7];
+    batch_diag_sections(p, n, sec);
+    b->diag = reinterpret_cast<lbmp::DiagInstance*>(ws + hoff + sec[0]);
+    b->regions = reinterpret_cast<lbmp::DiagConst*>(ws + hoff + sec[1]);
+    b->diag_out = reinterpret_cast<double*>(ws + hoff + sec[2]);
+    b->diag_start = reinterpret_cast<int*>(ws + hoff + sec[3]);
+    b->diag_first = reinterpret_cast<int*>(ws + hoff + sec[4]);
+    b->flags = reinterpret_cast<int*>(ws + hoff + sec[5]);
     b->mode = LB_BATCH_STEPWISE;
     hipError_t ee = hipEventCreate(&b->ev[0]);
     if (ee == hipSuccess) ee = hipEventCreate(&b->ev[1]);
@@ -1045,20 +1128,17 @@ lb_status lb_batch_init(lb_batch** out, const lb_params* p, int32_t n, void* wor
     b->group_rows[0] = b->group_rows[1] = default_batch_rows(b->store);
     order_batch(b);
     hipError_t e = write_batch_descriptors(b);
+    if (e == hipSuccess) e = write_diag_descriptors(b);
+    std::vector<int> flags;
+    if (e == hipSuccess) e = read_batch_flags(b, flags);
     if (e != hipSuccess) {
         lb_batch_destroy(b);
         return hip_fail(e, "batch descriptors");
     }
     for (int i = 0; i < n; ++i) {
-        int hf = 0;
-        st = read_flag(b->inst[i], &hf);
-        if (st == LB_OK && (hf & lbmp::kFlagBadInput))
-            st = fail(LB_EINVAL, "lattice " + std::to_string(i) + ": rho0/u0 out of range");
-        if (st != LB_OK) {
-            const std::string msg = g_last_error;
-            lb_batch_destroy(b);
-            return fail(st, msg);
-        }
+        if (!(flags[i] & lbmp::kFlagBadInput)) continue;
+        lb_batch_destroy(b);
+        return fail(LB_EINVAL, "lattice " + std::to_string(i) + ": rho0/u0 out of range");
     }
     *out = b;
     g_last_error.clear();
@@ -1134,22 +1214,15 @@ lb_status lb_batch_diagnostics_all(lb_batch* b, const lb_region* in, const lb_re
     if (!b || !in || !outr || !d) return fail(LB_EINVAL, "NULL argument");
     if (b->poisoned) return fail(LB_ESTATE, "batch poisoned by an earlier failure");
     const int n = b->n;
-    std::vector<double> h((size_t)n * lbmp::kDiagFields, 0.0);
-    std::vector<int> hf(n, 0);
-    hipError_t e = hipSuccess;
-    for (int i = 0; i < n && e == hipSuccess; ++i) {
-        lb_ctx* c = b->inst[i];
-        if (!c->poisoned)
-            e = lbmp::launch_diag(c->p.store, c->p.bc == LB_BC_WALLS_Y, c->f[c->cur], c->kd, c->flag,
-                                  diag_const(c, in + i, outr + i), c->partial, c->dout, b->stream);
-    }
-    for (int i = 0; i < n && e == hipSuccess; ++i) {
-        lb_ctx* c = b->inst[i];
-        if (c->poisoned) continue;
-        e = hipMemcpyAsync(&h[(size_t)i * lbmp::kDiagFields], c->dout, lbmp::kDiagFields * sizeof(double),
-                           hipMemcpyDeviceToHost, b->stream);
-        if (e == hipSuccess) e = hipMemcpyAsync(&hf[i], c->flag, sizeof(int), hipMemcpyDeviceToHost, b->stream);
-    }
+    std::vector<double> h((size_t)n * lbmp::kDiagOut, 0.0);
+    std::vector<lbmp::DiagConst> dg(n);
+    for (int i = 0; i < n; ++i) dg[i] = diag_const(b->inst[i], in + i, outr + i);
+    hipError_t e = hipMemcpyAsync(b->regions, dg.data(), dg.size() * sizeof(dg[0]), hipMemcpyHostToDevice, b->stream);
+    if (e == hipSuccess)
+        e = lbmp::launch_batch_diag(b->store, b->bc == LB_BC_WALLS_Y, b->psi, b->diag, b->regions, n, b->diag_start,
+                                    b->diag_first, b->diag_ntotal, b->inst[0]->cur, b->diag_out, b->stream);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(h.data(), b->diag_out, h.size() * sizeof(double), hipMemcpyDeviceToHost, b->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     if (e != hipSuccess) {
         b->poisoned = true;
@@ -1158,7 +1231,9 @@ lb_status lb_batch_diagnostics_all(lb_batch* b, const lb_region* in, const lb_re
     int bad = 0;
     for (int i = 0; i < n; ++i) {
         lb_ctx* c = b->inst[i];
-        fill_diag(c, &h[(size_t)i * lbmp::kDiagFields], hf[i], d + i);
+        double* hi = &h[(size_t)i * lbmp::kDiagOut];
+        if (c->poisoned) std::fill(hi, hi + lbmp::kDiagOut, 0.0);  // its fields are meaningless
+        fill_diag(c, hi, d + i);
         if (c->poisoned || d[i].unstable) {
             d[i].unstable = 1;
             c->poisoned = true;
@@ -1178,14 +1253,17 @@ lb_status lb_batch_get_state(lb_batch* b, int32_t i, void* dst)
 lb_status lb_batch_check(lb_batch* b, int32_t* unstable)
 {
     if (!b) return fail(LB_EINVAL, "batch is NULL");
+    std::vector<int> flags;
+    const hipError_t e = read_batch_flags(b, flags);
+    if (e != hipSuccess) {
+        for (lb_ctx* c : b->inst) c->poisoned = true;
+        return hip_fail(e, "reading the device flags");
+    }
     int count = 0;
-    for (lb_ctx* c : b->inst) {
-        int hf = 0;
-        lb_status st = read_flag(c, &hf);
-        if (st != LB_OK) return st;
-        if (hf & lbmp::kFlagUnstable) {
+    for (int i = 0; i < b->n; ++i) {
+        if (flags[i] & lbmp::kFlagUnstable) {
             ++count;
-            c->poisoned = true;
+            b->inst[i]->poisoned = true;
         }
     }
     if (unstable) *unstable = count;
