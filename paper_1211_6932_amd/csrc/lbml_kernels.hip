@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "lbml_launch.hpp"
@@ -255,76 +256,158 @@ __device__ __forceinline__ void hat_of(double d, double r0, int& j, double& t)
     t = s - j;
 }
 
-// Least-squares fit, stage 1: row y's contributions to the normal equations
-// (H^T H) L = H^T log rho.  Thread k accumulates, in x order, the diagonal
-// (k, k), the upper off-diagonal (k, k+1) and the right-hand side of sample k
-// over the sites of the row.  part: [3][ny][128] doubles.
-__global__ __launch_bounds__(kOut) void profile_rows(const float* __restrict__ rho, int nx, int ny, double cx,
-                                                     double cy, double r0, double* __restrict__ part)
+// Least-squares fit, stage 1: the contributions of a pair of rows to the normal equations
+// (H^T H) L = H^T log rho: of each sample k the diagonal (k, k), the upper off-diagonal
+// (k, k+1) and the right-hand side.  part: [3][(ny + 1) / 2][128] doubles.
+// The sites of a row are evaluated once each (one square root and one logarithm), 256 at a
+// time, into LDS; then four threads per sample and row each go through a quarter of them, in
+// x order, adding the sites whose hat functions reach the sample (a site reaches two samples;
+// the weights of the others are zero, without branches).  256 x 256: 152 us when every
+// sample's thread evaluated every site of its row, 13 us now.  Two rows per workgroup
+// halve what the single workgroup of stage 2 has to read.
+constexpr int kFitRows = 2;
+constexpr int kFitThreads = 4 * kOut * kFitRows;
+constexpr int kFitSites = 256;
+constexpr int fit_groups(int ny) { return (ny + kFitRows - 1) / kFitRows; }
+
+__global__ __launch_bounds__(kFitThreads) void profile_rows(const float* __restrict__ rho, int nx, int ny, double cx,
+                                                            double cy, double r0, double* __restrict__ part)
 {
-    const int k = threadIdx.x;
-    const int y = blockIdx.x;
+    __shared__ double st[kFitRows][kFitSites], sv[kFitRows][kFitSites];
+    __shared__ int sj[kFitRows][kFitSites];
+    __shared__ double sum[4 * kFitRows][3][kOut];
+    const int k = threadIdx.x & (kOut - 1), eighth = threadIdx.x / kOut;
+    const int which = eighth / 4, quarter = eighth % 4;
+    const int in_row = threadIdx.x % (4 * kOut);
+    const int y = blockIdx.x * kFitRows + which;
     const double dy = min_image(y - cy, ny);
     const float* row = rho + (long long)y * nx;
     double a = 0.0, e = 0.0, b = 0.0;
-    for (int x = 0; x < nx; ++x) {
-        const double dx = min_image(x - cx, nx);
-        int j;
-        double t;
-        hat_of(sqrt(dx * dx + dy * dy), r0, j, t);
-        if (j == k) {
-            const double v = log((double)row[x]);
-            a += (1.0 - t) * (1.0 - t);
-            e += (1.0 - t) * t;
-            b += (1.0 - t) * v;
-        } else if (j + 1 == k) {
-            const double v = log((double)row[x]);
-            a += t * t;
-            b += t * v;
+    for (int x0 = 0; x0 < nx; x0 += kFitSites) {
+        if (in_row < kFitSites) {
+            const int x = x0 + in_row;
+            int j = -2;  // reaches no sample
+            double t = 0.0, v = 0.0;
+            if (x < nx && y < ny) {
+                const double dx = min_image(x - cx, nx);
+                hat_of(sqrt(dx * dx + dy * dy), r0, j, t);
+                v = log((double)row[x]);
+            }
+            sj[which][in_row] = j;
+            st[which][in_row] = t;
+            sv[which][in_row] = v;
         }
+        __syncthreads();
+#pragma unroll 8
+        for (int q = 0; q < kFitSites / 4; ++q) {
+            const int i = quarter * (kFitSites / 4) + q;
+            const int j = sj[which][i];
+            const double t = st[which][i], u = 1.0 - t;
+            const double w = j == k ? u : (j + 1 == k ? t : 0.0);
+            const double v = j == k || j + 1 == k ? sv[which][i] : 0.0;
+            a += w * w;
+            e += j == k ? u * t : 0.0;
+            b += w * v;
+        }
+        __syncthreads();
     }
-    const long long plane = (long long)ny * kOut;
-    part[(long long)y * kOut + k] = a;
-    part[plane + (long long)y * kOut + k] = e;
-    part[2 * plane + (long long)y * kOut + k] = b;
+    sum[eighth][0][k] = a;
+    sum[eighth][1][k] = e;
+    sum[eighth][2][k] = b;
+    __syncthreads();
+    if (eighth < 3) {
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < 4 * kFitRows; ++q) s += sum[q][eighth][k];
+        part[((long long)eighth * gridDim.x + blockIdx.x) * kOut + k] = s;
+    }
 }
 
-// Stage 2 (one workgroup): sum the rows in order, add lam * (graph Laplacian
-// of the sample path), solve the symmetric positive-definite tridiagonal
-// system (Thomas algorithm, FP64) and write L as FP32.
-__global__ __launch_bounds__(kOut) void profile_solve(const double* __restrict__ part, int ny,
-                                                      float* __restrict__ logrho)
+// Stage 2 (one workgroup): sum the ny records (eight stretches per sample, in order), add
+// lam * (graph Laplacian of the sample path), solve the symmetric positive-definite
+// tridiagonal system in FP64 and write L as FP32.  The solver is parallel cyclic reduction:
+// in each of seven rounds every row eliminates its two neighbours at distance d = 1, 2, 4, ...
+// (each round takes Schur complements of a positive-definite matrix, so no pivoting is
+// needed).  256 x 256: 82 us with one thread per sample over all rows and one thread solving,
+// 8.6 us now.
+constexpr int kSolveGroups = 8;
+constexpr int kSolveRows = 8;  // rows whose loads are in flight together
+
+__global__ __launch_bounds__(kSolveGroups * kOut) void profile_solve(const double* __restrict__ part, int ny,
+                                                                     float* __restrict__ logrho)
 {
-    __shared__ double A[kOut], E[kOut], Bv[kOut], Cp[kOut], Dp[kOut];
-    const int k = threadIdx.x;
+    __shared__ double sum[kSolveGroups][3][kOut];
+    __shared__ double lo[2][kOut], di[2][kOut], up[2][kOut], rh[2][kOut];
+    const int k = threadIdx.x & (kOut - 1), group = threadIdx.x / kOut;
     const long long plane = (long long)ny * kOut;
+    const int per = (ny + kSolveGroups - 1) / kSolveGroups;
     double a = 0.0, e = 0.0, b = 0.0;
-    for (int y = 0; y < ny; ++y) {
-        a += part[(long long)y * kOut + k];
-        e += part[plane + (long long)y * kOut + k];
-        b += part[2 * plane + (long long)y * kOut + k];
-    }
-    if (k > 0) a += kSmooth;
-    if (k < kOut - 1) {
-        a += kSmooth;
-        e -= kSmooth;
-    }
-    A[k] = a;
-    E[k] = e;  // coupling of samples k and k + 1 (unused for k = 127)
-    Bv[k] = b;
-    __syncthreads();
-    if (k == 0) {
-        Cp[0] = E[0] / A[0];
-        Dp[0] = Bv[0] / A[0];
-        for (int i = 1; i < kOut; ++i) {
-            const double m = A[i] - E[i - 1] * Cp[i - 1];
-            Cp[i] = i < kOut - 1 ? E[i] / m : 0.0;
-            Dp[i] = (Bv[i] - E[i - 1] * Dp[i - 1]) / m;
+    const int end = min(ny, (group + 1) * per);
+    for (int y0 = group * per; y0 < end; y0 += kSolveRows) {
+        double va[kSolveRows], ve[kSolveRows], vb[kSolveRows];
+#pragma unroll
+        for (int q = 0; q < kSolveRows; ++q) {
+            const long long o = (long long)(y0 + q) * kOut + k;
+            const bool in = y0 + q < end;
+            va[q] = in ? part[o] : 0.0;
+            ve[q] = in ? part[plane + o] : 0.0;
+            vb[q] = in ? part[2 * plane + o] : 0.0;
         }
-        for (int i = kOut - 2; i >= 0; --i) Dp[i] -= Cp[i] * Dp[i + 1];
+#pragma unroll
+        for (int q = 0; q < kSolveRows; ++q) {
+            a += va[q];
+            e += ve[q];
+            b += vb[q];
+        }
+    }
+    sum[group][0][k] = a;
+    sum[group][1][k] = e;
+    sum[group][2][k] = b;
+    __syncthreads();
+    if (group == 0) {
+        for (int g = 1; g < kSolveGroups; ++g) {
+            a += sum[g][0][k];
+            e += sum[g][1][k];
+            b += sum[g][2][k];
+        }
+        if (k > 0) a += kSmooth;
+        if (k < kOut - 1) {
+            a += kSmooth;
+            e -= kSmooth;
+        } else {
+            e = 0.0;
+        }
+        di[0][k] = a;
+        up[0][k] = e;  // coupling of samples k and k + 1
+        rh[0][k] = b;
+        if (k == 0) lo[0][0] = 0.0;
+        if (k < kOut - 1) lo[0][k + 1] = e;
     }
     __syncthreads();
-    logrho[k] = (float)Dp[k];
+    int cur = 0;
+    for (int d = 1; d < kOut; d *= 2, cur ^= 1) {
+        if (group == 0) {
+            double l = 0.0, u = 0.0, m = di[cur][k], r = rh[cur][k];
+            if (k >= d) {
+                const double f = lo[cur][k] / di[cur][k - d];
+                l = -f * lo[cur][k - d];
+                m -= f * up[cur][k - d];
+                r -= f * rh[cur][k - d];
+            }
+            if (k + d < kOut) {
+                const double f = up[cur][k] / di[cur][k + d];
+                u = -f * up[cur][k + d];
+                m -= f * lo[cur][k + d];
+                r -= f * rh[cur][k + d];
+            }
+            lo[cur ^ 1][k] = l;
+            di[cur ^ 1][k] = m;
+            up[cur ^ 1][k] = u;
+            rh[cur ^ 1][k] = r;
+        }
+        __syncthreads();
+    }
+    if (group == 0) logrho[k] = (float)(rh[cur][k] / di[cur][k]);
 }
 
 // rho0(x, y) = exp((1 - t) L_j + t L_{j+1}) at the minimum-image distance of
@@ -343,57 +426,222 @@ __global__ void profile_to_rho0(const float* __restrict__ logrho, double r0, con
     rho0[(long long)y * nx + x] = (float)exp((1.0 - t) * logrho[j] + t * logrho[j + 1]);
 }
 
-constexpr int kMassThreads = 1024;
 constexpr int kMassIters = 60;
 constexpr double kMaxShift = 8.0;
 
-// Bisection for the outward shift delta in [-8, 8] at which the profile's field
-// has total mass `mass` (the mass grows with delta for a profile that falls
-// outwards).  One workgroup; FP64 site sums reduced in a fixed tree order.
+// Bisection for the outward shift delta in [-8, 8] at which the profile's field has total
+// mass `mass` (the mass grows with delta for a profile that falls outwards): 60 halvings,
+// delta the middle of the last interval; FP64 site sums in a fixed order.
 // out[0] = delta, out[1] = the field's mass at delta.
-__global__ __launch_bounds__(kMassThreads) void profile_mass_shift(const float* __restrict__ logrho, double r0,
-                                                                   double cx, double cy, int nx, int ny,
-                                                                   double mass, double* __restrict__ out)
+//
+// One level at a time this is a serial chain of 61 sums over the lattice.  A launch of
+// mass_round instead evaluates all kMassCands middle points that the next kMassLevels levels
+// of the bisection can visit, over the whole chip; the next launch sums up the workgroups'
+// partials (every workgroup for itself, in the same order), walks down the levels, and goes
+// on from the interval reached.  The interval after every level is that of the plain
+// bisection.  256 x 256: 2900 us in one workgroup, 141 us in 18 launches (8.7 us a round).
+// The partials live in the output field, which is written last.
+constexpr int kMassLevels = 4;
+constexpr int kMassCands = (1 << kMassLevels) - 1;
+constexpr int kMassRounds = kMassIters / kMassLevels;
+static_assert(kMassRounds * kMassLevels == kMassIters, "whole rounds");
+static_assert(kMassLevels == 4, "the sum over a wavefront leaves 16 candidates on 16 lane groups");
+constexpr int kMassThreads = 256;
+constexpr int kMassBlocks = 256;          // at most; kMassThreads sites each or more
+constexpr int kMassStride = kMassCands + 1;
+
+// Interval and partial sums of one round.
+struct MassRound {
+    double lo, hi;
+    double part[1][kMassStride];  // [workgroups][candidates]
+};
+constexpr size_t mass_round_doubles(int blocks) { return 2 + (size_t)blocks * kMassStride; }
+
+// Middle point of the interval that heap node c (1 = the root) of the bisection tree under
+// [lo, hi] halves: the bits of c below the leading one say up (1) or down (0).
+__device__ __forceinline__ double mass_node(double lo, double hi, int c)
 {
-    __shared__ float L[kOut];
-    __shared__ double part[kMassThreads];
-    __shared__ double lohi[2];
+    int bit = 31 - __builtin_clz(c);
+    double mid = 0.5 * (lo + hi);
+    while (bit-- > 0) {
+        if ((c >> bit) & 1) lo = mid;
+        else hi = mid;
+        mid = 0.5 * (lo + hi);
+    }
+    return mid;
+}
+
+// The field's constant inside the first sample (which = 0) or beyond the last (1): t = 0 in
+// interval 0, or t = 1 in the last interval.
+__device__ __forceinline__ double end_value(const float* __restrict__ logrho, int which)
+{
+    const int j = which ? kOut - 2 : 0;
+    const double t = which ? 1.0 : 0.0;
+    return exp((1.0 - t) * (double)logrho[j] + t * (double)logrho[j + 1]);
+}
+
+// The field's value at distance d for sample radii starting at r.
+__device__ __forceinline__ double profile_value(const double* __restrict__ L, double d, double r)
+{
+    int j;
+    double t;
+    hat_of(d, r, j, t);
+    return exp((1.0 - t) * L[j] + t * L[j + 1]);
+}
+
+// round 0 .. kMassRounds - 1: candidates of that round; round kMassRounds: the mass at the
+// final delta (one candidate), delta to out[0].  Reads `from` (the previous round; unused in
+// round 0), writes `to`.
+__global__ __launch_bounds__(kMassThreads) void mass_round(const float* __restrict__ logrho, double r0, double cx,
+                                                           double cy, int nx, int ny, double mass, int round,
+                                                           const MassRound* __restrict__ from,
+                                                           MassRound* __restrict__ to, double* __restrict__ out)
+{
+    __shared__ double L[kOut], ends[2], cand[kMassCands], sums[kMassThreads / 16][kMassStride], lohi[2];
+    __shared__ double wsum[kMassThreads / 64][kMassStride];
     const int tid = threadIdx.x;
-    if (tid < kOut) L[tid] = logrho[tid];
-    if (tid == 0) {
-        lohi[0] = -kMaxShift;
-        lohi[1] = kMaxShift;
+    if (tid < kOut) L[tid] = (double)logrho[tid];
+    if (tid < 2) ends[tid] = end_value(logrho, tid);
+    if (round == 0) {
+        if (tid == 0) {
+            lohi[0] = -kMaxShift;
+            lohi[1] = kMaxShift;
+        }
+    } else {
+        // sums of the previous round's candidates: 16 threads per stretch of workgroups
+        // (all loads of a thread are issued together: read one after the other they would cost
+        // a memory latency each)
+        constexpr int groups = kMassThreads / 16, per = kMassBlocks / groups;
+        const int c = tid & 15, g = tid >> 4;
+        double v[per], acc = 0.0;
+#pragma unroll
+        for (int q = 0; q < per; ++q) v[q] = g + q * groups < (int)gridDim.x ? from->part[g + q * groups][c] : 0.0;
+#pragma unroll
+        for (int q = 0; q < per; ++q) acc += v[q];
+        sums[g][c] = acc;
+        __syncthreads();
+        if (tid < kMassCands) {
+            double m = 0.0;
+            for (int q = 0; q < kMassThreads / 16; ++q) m += sums[q][tid];
+            cand[tid] = m;
+        }
+        __syncthreads();
+        if (tid == 0) {
+            double lo = from->lo, hi = from->hi;
+            for (int level = 0, node = 1; level < kMassLevels; ++level) {
+                const double mid = 0.5 * (lo + hi);
+                const bool up = cand[node - 1] < mass;
+                if (up) lo = mid;
+                else hi = mid;
+                node = 2 * node + (up ? 1 : 0);
+            }
+            lohi[0] = lo;
+            lohi[1] = hi;
+        }
     }
     __syncthreads();
+    const double lo = lohi[0], hi = lohi[1];
+    const int n_cand = round < kMassRounds ? kMassCands : 1;
+    if (blockIdx.x == 0 && tid == 0) {
+        to->lo = lo;
+        to->hi = hi;
+        if (round == kMassRounds) out[0] = 0.5 * (lo + hi);
+    }
+    if (tid < n_cand) cand[tid] = r0 + mass_node(lo, hi, tid + 1);
+    __syncthreads();
+    double acc[kMassStride];
+#pragma unroll
+    for (int c = 0; c < kMassStride; ++c) acc[c] = 0.0;
     const long long n = (long long)nx * ny;
-    double m = 0.0;
-    for (int it = 0; it <= kMassIters; ++it) {
-        const double delta = 0.5 * (lohi[0] + lohi[1]);
-        double acc = 0.0;
-        for (long long i = tid; i < n; i += kMassThreads) {
-            const int x = (int)(i % nx), y = (int)(i / nx);
-            const double dx = min_image(x - cx, nx), dy = min_image(y - cy, ny);
-            int j;
-            double t;
-            hat_of(sqrt(dx * dx + dy * dy), r0 + delta, j, t);
-            acc += exp((1.0 - t) * (double)L[j] + t * (double)L[j + 1]);
+    for (long long i = (long long)blockIdx.x * kMassThreads + tid; i < n; i += (long long)gridDim.x * kMassThreads) {
+        const int x = (int)(i % nx), y = (int)(i / nx);
+        const double dx = min_image(x - cx, nx), dy = min_image(y - cy, ny);
+        const double d = sqrt(dx * dx + dy * dy);
+        // a wavefront wholly beyond the samples, whatever the candidate, needs no exponentials
+        const bool outside = __all((d - (r0 + hi)) * 2.0 >= (double)(kOut - 1));
+        if (outside || __all((d - (r0 + lo)) * 2.0 <= 0.0)) {
+            const double v = ends[outside ? 1 : 0];
+#pragma unroll
+            for (int c = 0; c < kMassCands; ++c) acc[c] += v;
+        } else if (n_cand == 1) {
+            acc[0] += profile_value(L, d, cand[0]);
+        } else {
+#pragma unroll
+            for (int c = 0; c < kMassCands; ++c) acc[c] += profile_value(L, d, cand[c]);
         }
-        part[tid] = acc;
+    }
+    // Sum over the wavefront: in each of four rounds a lane keeps half of its sums and adds the
+    // partner's share of them, so that lane groups end up with one candidate each.
+    const int lane = tid & 63;
+#pragma unroll
+    for (int o = 32, m = kMassStride / 2; m >= 1; o >>= 1, m >>= 1) {
+        const bool upper = lane & o;
+#pragma unroll
+        for (int q = 0; q < m; ++q) {
+            const double send = upper ? acc[q] : acc[q + m], keep = upper ? acc[q + m] : acc[q];
+            acc[q] = keep + __shfl_xor(send, o, 64);
+        }
+    }
+    acc[0] += __shfl_xor(acc[0], 2, 64);
+    acc[0] += __shfl_xor(acc[0], 1, 64);
+    if ((lane & 3) == 0) wsum[tid >> 6][lane >> 2] = acc[0];
+    __syncthreads();
+    if (tid < kMassStride) to->part[blockIdx.x][tid] = (wsum[0][tid] + wsum[1][tid]) + (wsum[2][tid] + wsum[3][tid]);
+}
+
+// out[1] = the mass of the final round (one wavefront, fixed order).
+__global__ __launch_bounds__(64) void mass_final(const MassRound* __restrict__ from, int blocks, double* __restrict__ out)
+{
+    double p[kMassBlocks / 64], v = 0.0;
+#pragma unroll
+    for (int q = 0; q < kMassBlocks / 64; ++q) {
+        const int b = threadIdx.x + 64 * q;
+        p[q] = b < blocks ? from->part[b][0] : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < kMassBlocks / 64; ++q) v += p[q];
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if (threadIdx.x == 0) out[1] = v;
+}
+
+// The same search by one workgroup in one launch, a level at a time: lattices of at most
+// kMassSmall sites, one per thread (32 x 32: 79 us; the rounds above need at least
+// 130 us for their launches).
+constexpr int kMassSmall = 1024;
+
+__global__ __launch_bounds__(kMassSmall) void mass_small(const float* __restrict__ logrho, double r0, double cx,
+                                                         double cy, int nx, int ny, double mass,
+                                                         double* __restrict__ out)
+{
+    __shared__ double L[kOut];
+    __shared__ double part[kMassSmall];
+    const int tid = threadIdx.x;
+    if (tid < kOut) L[tid] = (double)logrho[tid];
+    double lo = -kMaxShift, hi = kMaxShift;
+    const bool live = tid < nx * ny;
+    const double dx = min_image((live ? tid % nx : 0) - cx, nx), dy = min_image((live ? tid / nx : 0) - cy, ny);
+    const double d = sqrt(dx * dx + dy * dy);
+    __syncthreads();
+    for (int it = 0; it <= kMassIters; ++it) {
+        const double delta = 0.5 * (lo + hi);
+        part[tid] = live ? profile_value(L, d, r0 + delta) : 0.0;
         __syncthreads();
-        for (int s = kMassThreads / 2; s > 0; s >>= 1) {
+        for (int s = kMassSmall / 2; s > 0; s >>= 1) {
             if (tid < s) part[tid] += part[tid + s];
             __syncthreads();
         }
-        m = part[0];
-        if (tid == 0 && it < kMassIters) {
-            if (m < mass) lohi[0] = delta;
-            else lohi[1] = delta;
+        const double m = part[0];
+        if (it == kMassIters) {
+            if (tid == 0) {
+                out[0] = delta;
+                out[1] = m;
+            }
+        } else if (m < mass) {
+            lo = delta;
+        } else {
+            hi = delta;
         }
         __syncthreads();
-        if (it == kMassIters && tid == 0) {
-            out[0] = delta;
-            out[1] = m;
-        }
     }
 }
 
@@ -600,10 +848,10 @@ hipError_t launch_profile_extract(const float* rho, int nx, int ny, double cx, d
                                   float* logrho, hipStream_t s)
 {
     const double r0 = R - 0.25 * (kOut - 1);
-    hipLaunchKernelGGL(profile_rows, dim3(ny), dim3(kOut), 0, s, rho, nx, ny, cx, cy, r0, part);
+    hipLaunchKernelGGL(profile_rows, dim3(fit_groups(ny)), dim3(kFitThreads), 0, s, rho, nx, ny, cx, cy, r0, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(profile_solve, dim3(1), dim3(kOut), 0, s, part, ny, logrho);
+    hipLaunchKernelGGL(profile_solve, dim3(1), dim3(kSolveGroups * kOut), 0, s, part, fit_groups(ny), logrho);
     return hipGetLastError();
 }
 
@@ -665,9 +913,30 @@ hipError_t launch_profile_to_rho0_mass(const float* logrho, double R, double cx,
                                        double mass, double* shift, float* rho0, hipStream_t s)
 {
     const double r0 = R - 0.25 * (kOut - 1);
-    hipLaunchKernelGGL(profile_mass_shift, dim3(1), dim3(kMassThreads), 0, s, logrho, r0, cx, cy, nx, ny, mass, shift);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    const long long sites = (long long)nx * ny;
+    if (sites <= kMassSmall) {
+        hipLaunchKernelGGL(mass_small, dim3(1), dim3(kMassSmall), 0, s, logrho, r0, cx, cy, nx, ny, mass, shift);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    } else {
+        // two rounds' records in the output field (8-byte aligned inside it): at most 128
+        // doubles and a little per workgroup of at least 256 sites
+        const int blocks = (int)std::min<long long>(kMassBlocks, sites / kMassThreads);
+        double* base = reinterpret_cast<double*>((reinterpret_cast<uintptr_t>(rho0) + 7) / 8 * 8);
+        static_assert(2 * (2 + kMassStride) * sizeof(double) + 8 <= kMassThreads * sizeof(float), "records fit in the field");
+        MassRound* rec[2] = {reinterpret_cast<MassRound*>(base),
+                             reinterpret_cast<MassRound*>(base + mass_round_doubles(blocks))};
+        for (int round = 0; round <= kMassRounds; ++round) {
+            hipLaunchKernelGGL(mass_round, dim3(blocks), dim3(kMassThreads), 0, s, logrho, r0, cx, cy, nx, ny, mass, round,
+                               static_cast<const MassRound*>(rec[(round & 1) ^ 1]), rec[round & 1], shift);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL(mass_final, dim3(1), dim3(64), 0, s, static_cast<const MassRound*>(rec[kMassRounds & 1]), blocks,
+                           shift);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL(profile_to_rho0, dim3(grid1(nx, 256), ny), dim3(256), 0, s, logrho, r0,
                        static_cast<const double*>(shift), cx, cy, nx, ny, rho0);
     return hipGetLastError();
