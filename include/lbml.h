@@ -83,12 +83,11 @@ lb_status lbml_train_step(lbml_net* net, const float* x, const float* base, cons
  * x_all (device [rows][4] raw features), base_all (device [rows][128], or NULL
  * for zero) and target_all (device [rows][128]), at learning rate lr[s] (device
  * [steps] FP32).  loss (device [steps] FP32, or NULL) receives each step's loss.
- * The kernels of one step (row gather, forward, backward, Adam, bf16 refresh)
- * are captured once into a HIP graph and replayed `steps` times; the step index,
- * learning rate and Adam's bias correction come from a schedule kept on the
- * device.  The result is bitwise that of `steps` calls of lbml_train_step on the
- * gathered rows.  B: multiple of 32, at most max_batch.  The net's stream must
- * not be the null stream (it is captured).  The indices are checked first
+ * A step is two launches (row gather, forward and backward; gradients,
+ * Adam and bf16 refresh); the step index, learning rate and Adam's bias
+ * correction come from a schedule kept on the device.  The result is bitwise
+ * that of `steps` calls of lbml_train_step on the gathered rows.  B: multiple of
+ * 32, at most max_batch.  The net's stream must not be the null stream.  The indices are checked first
  * (LB_EINVAL, nothing trained, if one is out of range).  steps = 0 returns LB_OK
  * at once (the array arguments may then be NULL).  Synchronises the stream. */
 lb_status lbml_train_steps(lbml_net* net, const float* x_all, const float* base_all, const float* target_all,

@@ -39,10 +39,14 @@ constexpr size_t b_off(int i) { return w_off(i) + (size_t)kOutN[i] * kIn[i]; }
 static_assert(w_off(kLayers) == LBML_PARAMS, "parameter count");
 
 struct Layout {
-    size_t theta, m, v, grad, norm, loss, wb[kLayers], x16, z[kLayers], h[kLayers - 1], c, dz[2];
-    size_t xg, bg, tg, sched;  // a graph-replayed training step: gathered rows and the device schedule
+    size_t theta, m, v, grad, norm, loss, wb[kLayers], wt[kLayers];
+    // a training pass leaves the layer inputs and pre-activation gradients, transposed
+    size_t xT, hT[kLayers - 1], dzT[kLayers], loss_part;
+    size_t sched;  // device schedule of a training loop
     size_t total;
 };
+
+constexpr int kXRows = 16;  // input columns in one matrix-core tile; the products of all but four are dropped
 
 Layout layout_of(int B)
 {
@@ -61,16 +65,11 @@ Layout layout_of(int B)
     L.norm = take(2 * lbml::kIn * sizeof(float));
     L.loss = take(sizeof(float));
     for (int i = 0; i < kLayers; ++i) L.wb[i] = take((size_t)kOutN[i] * kInPadded[i] * 2);
-    L.x16 = take((size_t)B * lbml::kInPad * 2);
-    for (int i = 0; i < kLayers; ++i) L.z[i] = take((size_t)B * kOutN[i] * 4);
-    for (int i = 0; i < kLayers - 1; ++i) L.h[i] = take((size_t)B * lbml::kHidden * 2);
-    // GEMM scratch: [B][256] activations or gradients, or the padded [256][32] first-layer weight gradient
-    L.c = take((size_t)B * lbml::kHidden * 4);
-    L.dz[0] = take((size_t)B * lbml::kHidden * 2);
-    L.dz[1] = take((size_t)B * lbml::kHidden * 2);
-    L.xg = take((size_t)B * lbml::kIn * 4);
-    L.bg = take((size_t)B * lbml::kOut * 4);
-    L.tg = take((size_t)B * lbml::kOut * 4);
+    for (int i = 1; i < kLayers; ++i) L.wt[i] = take((size_t)kOutN[i] * kInPadded[i] * 2);
+    L.xT = take((size_t)B * kXRows * 2);
+    for (int i = 0; i < kLayers - 1; ++i) L.hT[i] = take((size_t)B * lbml::kHidden * 2);
+    for (int i = 0; i < kLayers; ++i) L.dzT[i] = take((size_t)B * kOutN[i] * 2);
+    L.loss_part = take((size_t)B / 4 * sizeof(float));
     L.sched = take(sizeof(lbml::TrainSched));
     L.total = o;
     return L;
@@ -91,7 +90,7 @@ struct lbml_net {
     long long t = 0;          // Adam steps taken
     double p1 = 1.0, p2 = 1.0;  // b1^t and b2^t, one FP64 product per step (the device schedule repeats them)
     bool have_grad = false;
-    lbml::TrainSched sched_init{};  // host copy of the schedule uploaded before a graph-replayed loop
+    lbml::TrainSched sched_init{};  // host copy of the schedule uploaded before a training loop
 
     float* f(size_t off) { return reinterpret_cast<float*>(ws + off); }
     __bf16* h16(size_t off) { return reinterpret_cast<__bf16*>(ws + off); }
@@ -103,55 +102,57 @@ hipError_t refresh_bf16(lbml_net* n)
 {
     hipError_t e = hipSuccess;
     for (int i = 0; i < kLayers && e == hipSuccess; ++i)
-        e = lbml::launch_to_bf16(n->f(n->L.theta) + w_off(i), n->h16(n->L.wb[i]), kOutN[i], kIn[i], kInPadded[i],
-                                 n->stream);
+        e = lbml::launch_to_bf16(n->f(n->L.theta) + w_off(i), n->h16(n->L.wb[i]), i > 0 ? n->h16(n->L.wt[i]) : nullptr,
+                                 kOutN[i], kIn[i], kInPadded[i], n->stream);
     return e;
 }
 
-// Forward pass; the output layer writes y = network(x) + base (FP32 [B][128]).
-hipError_t forward(lbml_net* n, const float* x, const float* base, int B, float* y)
+// Arguments of a pass over B rows; a training loop adds its index table and schedule.
+lbml::MlpArgs pass_args(lbml_net* n, const float* x, const float* base, const float* target, int B, float* y)
 {
-    hipError_t e = lbml::launch_pack_input(x, n->f(n->L.norm), n->f(n->L.norm) + lbml::kIn, n->h16(n->L.x16), B,
-                                           n->stream);
-    const __bf16* hin = n->h16(n->L.x16);
-    for (int i = 0; i < kLayers && e == hipSuccess; ++i) {
-        const int K = kInPadded[i], N = kOutN[i];
-        e = lbml::gemm(hin, K, 1, n->h16(n->L.wb[i]), 1, K, n->f(n->L.c), N, B, N, K, n->stream);
-        if (e != hipSuccess) break;
-        const bool last = i == kLayers - 1;
-        float* z = last ? y : n->f(n->L.z[i]);
-        __bf16* hout = last ? nullptr : n->h16(n->L.h[i]);
-        e = lbml::launch_bias_act(n->f(n->L.c), n->f(n->L.theta) + b_off(i), last ? base : nullptr, z, hout, B, N,
-                                  n->stream);
-        hin = hout;
+    lbml::MlpArgs a{};
+    a.x = x;
+    a.base = base;
+    a.target = target;
+    a.y = y;
+    a.B = B;
+    a.norm = n->f(n->L.norm);
+    for (int i = 0; i < kLayers; ++i) {
+        a.w[i] = n->h16(n->L.wb[i]);
+        a.wt[i] = i > 0 ? n->h16(n->L.wt[i]) : nullptr;
+        a.bias[i] = n->f(n->L.theta) + b_off(i);
+        a.dzT[i] = n->h16(n->L.dzT[i]);
+        if (i < kLayers - 1) a.hT[i] = n->h16(n->L.hT[i]);
     }
-    return e;
+    a.xT = n->h16(n->L.xT);
+    a.loss_part = n->f(n->L.loss_part);
+    a.b1 = kBeta1;
+    a.b2 = kBeta2;
+    return a;
 }
 
-hipError_t backward(lbml_net* n, const float* target, int B, float* loss)
+lbml::GradArgs grad_args(lbml_net* n, int B, float* loss)
 {
-    float* grad = n->f(n->L.grad);
-    const float* y = n->f(n->L.z[kLayers - 1]);
-    int cur = 0;
-    hipError_t e = lbml::launch_mse_grad(y, target, n->h16(n->L.dz[cur]), loss, B, lbml::kOut, n->stream);
-    for (int i = kLayers - 1; i >= 0 && e == hipSuccess; --i) {
-        const int Kp = kInPadded[i], N = kOutN[i];
-        const __bf16* dz = n->h16(n->L.dz[cur]);
-        const __bf16* hin = i > 0 ? n->h16(n->L.h[i - 1]) : n->h16(n->L.x16);
-        // dW_i[N][Kp] = dZ^T H_in
-        float* dw = i > 0 ? grad + w_off(i) : n->f(n->L.c);
-        e = lbml::gemm(dz, 1, N, hin, Kp, 1, dw, Kp, N, Kp, B, n->stream);
-        if (e == hipSuccess && i == 0) e = lbml::launch_copy_cols(dw, Kp, grad + w_off(0), N, kIn[0], n->stream);
-        if (e == hipSuccess) e = lbml::launch_bias_grad(dz, grad + b_off(i), B, N, n->stream);
-        if (e != hipSuccess || i == 0) break;
-        // dH_{i-1}[B][Kp] = dZ W_i, then dZ_{i-1} = bf16(dH * GELU'(Z_{i-1}))
-        e = lbml::gemm(dz, N, 1, n->h16(n->L.wb[i]), Kp, 1, n->f(n->L.c), Kp, B, Kp, N, n->stream);
-        if (e == hipSuccess)
-            e = lbml::launch_gelu_back(n->f(n->L.c), n->f(n->L.z[i - 1]), n->h16(n->L.dz[cur ^ 1]), B * Kp,
-                                       n->stream);
-        cur ^= 1;
+    lbml::GradArgs g{};
+    for (int i = 0; i < kLayers; ++i) {
+        g.dzT[i] = n->h16(n->L.dzT[i]);
+        g.inT[i] = i > 0 ? n->h16(n->L.hT[i - 1]) : n->h16(n->L.xT);
+        g.w[i] = n->h16(n->L.wb[i]);
+        g.wt[i] = i > 0 ? n->h16(n->L.wt[i]) : nullptr;
+        g.w_off[i] = (int)w_off(i);
     }
-    return e;
+    g.loss_part = n->f(n->L.loss_part);
+    g.grad = n->f(n->L.grad);
+    g.loss = loss;
+    g.theta = n->f(n->L.theta);
+    g.m = n->f(n->L.m);
+    g.v = n->f(n->L.v);
+    g.b1 = (float)kBeta1;
+    g.b2 = (float)kBeta2;
+    g.eps = kEps;
+    g.B = B;
+    g.parts = B / lbml::mlp_rows(B);
+    return g;
 }
 
 lb_status check_net(lbml_net* n, int32_t B, bool train)
@@ -237,7 +238,7 @@ lb_status lbml_forward(lbml_net* n, const float* x, const float* base, int32_t B
     lb_status st = check_net(n, B, false);
     if (st != LB_OK) return st;
     if (!x || !y) return abi_fail(LB_EINVAL, "NULL argument");
-    hipError_t e = forward(n, x, base, B, y);
+    hipError_t e = lbml::launch_mlp_pass(pass_args(n, x, base, nullptr, B, y), false, n->stream);
     return e == hipSuccess ? LB_OK : abi_hip_fail(e, "lbml_forward");
 }
 
@@ -247,8 +248,8 @@ lb_status lbml_loss_grad(lbml_net* n, const float* x, const float* base, const f
     lb_status st = check_net(n, B, true);
     if (st != LB_OK) return st;
     if (!x || !target) return abi_fail(LB_EINVAL, "NULL argument");
-    hipError_t e = forward(n, x, base, B, n->f(n->L.z[kLayers - 1]));
-    if (e == hipSuccess) e = backward(n, target, B, loss ? loss : n->f(n->L.loss));
+    hipError_t e = lbml::launch_mlp_pass(pass_args(n, x, base, target, B, nullptr), true, n->stream);
+    if (e == hipSuccess) e = lbml::launch_mlp_grads(grad_args(n, B, loss ? loss : n->f(n->L.loss)), false, n->stream);
     if (e == hipSuccess && grad)
         e = hipMemcpyAsync(grad, n->f(n->L.grad), LBML_PARAMS * sizeof(float), hipMemcpyDeviceToDevice, n->stream);
     if (e != hipSuccess) return abi_hip_fail(e, "lbml_loss_grad");
@@ -289,7 +290,7 @@ lb_status lbml_train_steps(lbml_net* n, const float* x_all, const float* base_al
     if (steps == 0) return LB_OK;
     if (!x_all || !target_all || !idx || !lr) return abi_fail(LB_EINVAL, "NULL argument");
     if (rows < 1) return abi_fail(LB_EINVAL, "need rows >= 1");
-    if (!n->stream) return abi_fail(LB_EINVAL, "lbml_train_steps needs the net on a non-null stream (graph capture)");
+    if (!n->stream) return abi_fail(LB_EINVAL, "lbml_train_steps needs the net on a non-null stream");
     hipStream_t s = n->stream;
     auto* sc = reinterpret_cast<lbml::TrainSched*>(n->ws + n->L.sched);
     // the schedule starts at step 0 with the net's Adam state; indices are checked first
@@ -304,37 +305,20 @@ lb_status lbml_train_steps(lbml_net* n, const float* x_all, const float* base_al
     if (e != hipSuccess) return abi_hip_fail(e, "lbml_train_steps");
     if (bad) return abi_fail(LB_EINVAL, "lbml_train_steps: a row index lies outside [0, rows)");
 
-    // one step, captured: schedule, gather, forward, backward, loss record, Adam, bf16 refresh
-    hipGraph_t graph = nullptr;
-    e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
-    if (e != hipSuccess) return abi_hip_fail(e, "lbml_train_steps (begin capture)");
-    float* xg = n->f(n->L.xg);
-    float* bg = base_all ? n->f(n->L.bg) : nullptr;
-    float* tg = n->f(n->L.tg);
-    e = lbml::launch_sched_advance(sc, lr, kBeta1, kBeta2, s);
-    if (e == hipSuccess) e = lbml::launch_gather_rows(x_all, base_all, target_all, idx, sc, B, xg, bg, tg, s);
-    if (e == hipSuccess) e = forward(n, xg, bg, B, n->f(n->L.z[kLayers - 1]));
-    if (e == hipSuccess) e = backward(n, tg, B, n->f(n->L.loss));
-    if (e == hipSuccess && loss) e = lbml::launch_record_loss(n->f(n->L.loss), sc, loss, s);
-    if (e == hipSuccess)
-        e = lbml::launch_adam_sched(n->f(n->L.theta), n->f(n->L.m), n->f(n->L.v), n->f(n->L.grad), LBML_PARAMS, sc,
-                                    (float)kBeta1, (float)kBeta2, kEps, s);
-    if (e == hipSuccess) e = refresh_bf16(n);
-    const hipError_t ec = hipStreamEndCapture(s, &graph);
-    if (e == hipSuccess) e = ec;
-    hipGraphExec_t exec = nullptr;
-    if (e == hipSuccess) e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-    for (int32_t i = 0; i < steps && e == hipSuccess; ++i) e = hipGraphLaunch(exec, s);
+    // two launches per step; what changes from step to step is in the device schedule
+    lbml::MlpArgs a = pass_args(n, x_all, base_all, target_all, B, nullptr);
+    a.idx = idx;
+    a.lr = lr;
+    a.sc = sc;
+    lbml::GradArgs g = grad_args(n, B, n->f(n->L.loss));
+    g.sc = sc;
+    g.loss_out = loss;
+    for (int32_t i = 0; i < steps && e == hipSuccess; ++i) {
+        e = lbml::launch_mlp_pass(a, true, s);
+        if (e == hipSuccess) e = lbml::launch_mlp_grads(g, true, s);
+    }
     const hipError_t es = hipStreamSynchronize(s);
     if (e == hipSuccess) e = es;
-    if (exec) {
-        const hipError_t ed = hipGraphExecDestroy(exec);
-        if (e == hipSuccess) e = ed;
-    }
-    if (graph) {
-        const hipError_t ed = hipGraphDestroy(graph);
-        if (e == hipSuccess) e = ed;
-    }
     if (e != hipSuccess) return abi_hip_fail(e, "lbml_train_steps");
     for (int32_t i = 0; i < steps; ++i) {
         n->p1 *= kBeta1;

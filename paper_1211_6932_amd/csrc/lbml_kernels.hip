@@ -60,22 +60,12 @@ __global__ __launch_bounds__(256) void gemm_bf16(const __bf16* __restrict__ A, l
     for (int i = 0; i < 4; ++i) C[(long long)(m0 + (lane >> 4) * 4 + i) * ldc + n0 + r] = acc[i];
 }
 
-__device__ __forceinline__ float gelu(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
-
-__device__ __forceinline__ float gelu_prime(float z)
+// GELU and its derivative from z and e = erf(z / sqrt 2).
+__device__ __forceinline__ float gelu_erf(float z) { return erff(z * 0.70710678118654752f); }
+__device__ __forceinline__ float gelu(float z, float e) { return 0.5f * z * (1.0f + e); }
+__device__ __forceinline__ float gelu_prime(float z, float e)
 {
-    return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * expf(-0.5f * z * z) * 0.39894228040143268f;
-}
-
-// x [B][4] raw features -> bf16 [B][32]: standardised (x - mu) / sd, then
-// zero-padded to the matrix-core depth.
-__global__ void pack_input(const float* __restrict__ x, const float* __restrict__ mu,
-                           const float* __restrict__ inv_sd, __bf16* __restrict__ x16, int B)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= B * kInPad) return;
-    const int m = i / kInPad, k = i % kInPad;
-    x16[i] = static_cast<__bf16>(k < kIn ? (x[m * kIn + k] - mu[k]) * inv_sd[k] : 0.0f);
+    return 0.5f * (1.0f + e) + z * expf(-0.5f * z * z) * 0.39894228040143268f;
 }
 
 __global__ void fill_zero(unsigned int* __restrict__ p, size_t n)
@@ -84,87 +74,220 @@ __global__ void fill_zero(unsigned int* __restrict__ p, size_t n)
     if (i < n) p[i] = 0u;
 }
 
-// Z = C + b; H = bf16(GELU(Z)) (hidden layers), or Y = C + b + base (output
-// layer: H == nullptr; base [B][N] may be nullptr).
-__global__ void bias_act(const float* __restrict__ C, const float* __restrict__ bias,
-                         const float* __restrict__ base, float* __restrict__ Z, __bf16* __restrict__ H, int B, int N)
+// ---------------------------------------------------------------- the network
+// A pass over a batch is bound by latency, not by arithmetic (0.33 MFLOP a sample forward)
+// or bytes (0.33 MB of bf16 weights), so it is two launches: mlp_pass takes 16 rows of the
+// batch per workgroup through every layer, forward and, in training, back to the first
+// layer's pre-activation gradients; mlp_grads forms every weight and bias gradient from what
+// that left behind and, in a training loop, applies Adam to them on the spot.  512 rows:
+// 11.8 + 8.8 us, where one launch per operation (32 of them) took 115 us and the gaps (159 us a
+// training step, now 21.5 us).
+// Products use the matrix cores as gemm_bf16 does (same operand orientation, one accumulator
+// over k in steps of 32), whichever launch they are in.
+
+// Layers i = 0 .. 3: inputs (padded), outputs, offset of the weights in the parameter vector
+// (the biases follow them).
+__device__ constexpr int kLayerIn[4] = {kIn, kHidden, kHidden, kHidden};
+__device__ constexpr int kLayerPad[4] = {kInPad, kHidden, kHidden, kHidden};
+__device__ constexpr int kLayerOut[4] = {kHidden, kHidden, kHidden, kOut};
+constexpr int kMlpThreads = 1024;
+constexpr int kMlpLd = kHidden + 8;  // LDS row: 16 rows at 16 bytes fall on different banks
+
+// Every matrix operand is stored in fragment order: element (n, k) of an [..][K] matrix lies
+// where the lane that feeds it to a 16 x 16 x 32 product reads it, so that a wavefront's load
+// is one stretch of 1 KB (rows of the matrix would give it 64-byte pieces of 16 rows: 7000
+// cycles for the 128 KB of a layer; the pass over 512 rows takes 24 us that way, 11.8 us in
+// fragment order).
+__device__ __forceinline__ long long frag_at(int n, int k, int K)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= B * N) return;
-    float z = C[i] + bias[i % N];
-    if (base) z += base[i];
-    Z[i] = z;
-    if (H) H[i] = static_cast<__bf16>(gelu(z));
+    return ((long long)((n >> 4) * (K >> 5) + (k >> 5)) * 64 + (n & 15) + ((k & 31) >> 3) * 16) * 8 + (k & 7);
 }
 
-// dY = bf16(2 (Y - T) / (B N)); loss = mean (Y - T)^2, one workgroup, fixed order.
-__global__ __launch_bounds__(1024) void mse_grad(const float* __restrict__ Y, const float* __restrict__ T,
-                                                 __bf16* __restrict__ dY, float* __restrict__ loss, int B, int N)
+// Fragments of the right operand for the 16 output columns from n0 on.
+template <int K>
+__device__ __forceinline__ void load_frags(bf16x8 (&f)[8], const __bf16* __restrict__ W, int n0, int lane)
 {
-    __shared__ float part[1024];
-    const float scale = 2.0f / (float)(B * N);
-    float acc = 0.0f;
-    for (int i = threadIdx.x; i < B * N; i += 1024) {
-        const float d = Y[i] - T[i];
-        dY[i] = static_cast<__bf16>(scale * d);
-        acc += d * d;
+    const bf16x8* from = reinterpret_cast<const bf16x8*>(W) + (long long)(n0 >> 4) * (K / 32) * 64 + lane;
+#pragma unroll
+    for (int s = 0; s < K / 32; ++s) f[s] = from[64 * s];
+}
+
+// The wave's 16 x 16 tile of (LDS rows) x (fragments).
+template <int K>
+__device__ __forceinline__ floatx4 tile_product(const __bf16 (&A)[16][kMlpLd], const bf16x8 (&f)[8], int lane)
+{
+    floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int s = 0; s < K / 32; ++s) {
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(&A[lane & 15][32 * s + (lane >> 4) * 8]);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, f[s], acc, 0, 0, 0);
     }
-    part[threadIdx.x] = acc;
+    return acc;
+}
+
+// R values of one column into the LDS rows and into T (fragments along the batch).
+template <int R>
+__device__ __forceinline__ void put_column(__bf16 (&A)[16][kMlpLd], __bf16* __restrict__ T, int B, int m0, int col,
+                                           int lane, const __bf16 (&v)[R])
+{
+    const int q = lane >> 4;
+#pragma unroll
+    for (int j = 0; j < R; ++j) A[4 * q + j][col] = v[j];
+    if (T) {
+        typedef __bf16 bf16r __attribute__((ext_vector_type(R)));
+        bf16r w;
+#pragma unroll
+        for (int j = 0; j < R; ++j) w[j] = v[j];
+        *reinterpret_cast<bf16r*>(T + frag_at(col, m0 + R * q, B)) = w;
+    }
+}
+
+// One workgroup: 4 R rows of the batch.  A matrix-core tile has 16 rows, four per lane group;
+// R of the four are used, because the activation functions (an erf each, on the vector unit)
+// cost more than the products: with fewer rows per workgroup more compute units share them.
+// Wave w holds output columns 16 w .. 16 w + 15 of every layer, so the pre-activations that
+// the backward pass needs stay in its registers; layer inputs and gradients pass between
+// waves through LDS; a layer's weights are requested while the layer before is computed.
+// TRAIN: the layer inputs (x16, h) and pre-activation gradients dz are written in
+// fragments along the batch for mlp_grads, and the workgroup's loss sum.
+template <bool TRAIN, int R>
+__global__ __launch_bounds__(kMlpThreads) void mlp_pass(MlpArgs a)
+{
+    __shared__ __align__(16) __bf16 A[2][16][kMlpLd];
+    __shared__ float wave_loss[kOut / 16];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m0 = blockIdx.x * 4 * R, n0 = wave * 16, col = n0 + (lane & 15), q = lane >> 4;
+    const int B = a.B;
+    const bool last = wave < kOut / 16;  // has columns of the output layer
+    bf16x8 wf[8], wn[8];
+    load_frags<kInPad>(wf, a.w[0], n0, lane);
+    load_frags<kHidden>(wn, a.w[1], n0, lane);
+    // every load the epilogues need is requested here: a load issued after a later layer's
+    // weights would have to wait for them (loads return in order)
+    float bias[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bias[i] = i < 3 || last ? a.bias[i][col] : 0.0f;
+    const int* idx = a.idx ? a.idx + (long long)a.sc->next * B : nullptr;
+    auto source = [&](int m) __attribute__((always_inline)) { return (long long)(idx ? idx[m] : m); };
+    if (tid < 4 * R * kInPad) {
+        const int m = tid / kInPad, k = tid % kInPad;
+        const __bf16 v = static_cast<__bf16>(k < kIn ? (a.x[source(m0 + m) * kIn + k] - a.norm[k]) * a.norm[kIn + k] : 0.0f);
+        A[0][4 * (m / R) + m % R][k] = v;
+        if (TRAIN && k < kIn) a.xT[frag_at(k, m0 + m, B)] = v;
+    }
+    // the output layer's base and target, requested long before they are needed
+    float yb[R], yt[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) yb[j] = yt[j] = 0.0f;
+    if (last) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const long long at = source(m0 + R * q + j) * kOut + col;
+            if (a.base) yb[j] = a.base[at];
+            if (TRAIN) yt[j] = a.target[at];
+        }
+    }
     __syncthreads();
-    for (int s = 512; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) part[threadIdx.x] += part[threadIdx.x + s];
+
+    float z0[R], z1[R], z2[R], e0[R], e1[R], e2[R];
+    // a hidden layer's epilogue: z = c + b, h = bf16(GELU(z)) into the other LDS buffer
+    auto hidden = [&](const floatx4 acc, const float b, float (&z)[R], float (&e)[R], const int to, __bf16* hT)
+                      __attribute__((always_inline)) {
+        __bf16 h[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            z[j] = acc[j] + b;
+            e[j] = gelu_erf(z[j]);
+            h[j] = static_cast<__bf16>(gelu(z[j], e[j]));
+        }
+        put_column<R>(A[to], TRAIN ? hT : nullptr, B, m0, col, lane, h);
         __syncthreads();
-    }
-    if (threadIdx.x == 0 && loss) loss[0] = part[0] / (float)(B * N);
-}
+    };
+    hidden(tile_product<kInPad>(A[0], wf, lane), bias[0], z0, e0, 1, a.hT[0]);
+    load_frags<kHidden>(wf, a.w[2], n0, lane);
+    hidden(tile_product<kHidden>(A[1], wn, lane), bias[1], z1, e1, 0, a.hT[1]);
+    if (last) load_frags<kHidden>(wn, a.w[3], n0, lane);
+    hidden(tile_product<kHidden>(A[0], wf, lane), bias[2], z2, e2, 1, a.hT[2]);
+    if (TRAIN) load_frags<kOut>(wf, a.wt[3], n0, lane);
 
-// dZ = bf16(dH * GELU'(Z)).
-__global__ void gelu_back(const float* __restrict__ dH, const float* __restrict__ Z, __bf16* __restrict__ dZ,
-                          int n)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) dZ[i] = static_cast<__bf16>(dH[i] * gelu_prime(Z[i]));
-}
-
-// db[n] = sum_m dZ[m][n] (sequential in m: deterministic).
-__global__ void bias_grad(const __bf16* __restrict__ dZ, float* __restrict__ db, int B, int N)
-{
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= N) return;
-    float acc = 0.0f;
-    int m = 0;
-    // 16 rows loaded ahead, then added in row order: the loads overlap, the sum and
-    // its rounding stay those of the plain sequential loop
-    for (; m + 16 <= B; m += 16) {
-        float v[16];
+    float loss = 0.0f;
+    if (last) {
+        const floatx4 acc = tile_product<kHidden>(A[1], wn, lane);
+        const float b = bias[3];
+        const float scale = 2.0f / (float)(B * kOut);
+        __bf16 dy[R];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) v[j] = static_cast<float>(dZ[(long long)(m + j) * N + n]);
-#pragma unroll
-        for (int j = 0; j < 16; ++j) acc += v[j];
+        for (int j = 0; j < R; ++j) {
+            float z = acc[j] + b;
+            if (a.base) z += yb[j];
+            if (TRAIN) {
+                // dY = bf16(2 (Y - T) / (B N)); loss = mean (Y - T)^2
+                const float d = z - yt[j];
+                dy[j] = static_cast<__bf16>(scale * d);
+                loss += d * d;
+            } else {
+                a.y[(long long)(m0 + R * q + j) * kOut + col] = z;
+            }
+        }
+        if (TRAIN) {
+            put_column<R>(A[0], a.dzT[3], B, m0, col, lane, dy);
+            for (int o = 32; o > 0; o >>= 1) loss += __shfl_xor(loss, o, 64);
+            if (lane == 0) wave_loss[wave] = loss;
+        }
     }
-    for (; m < B; ++m) acc += static_cast<float>(dZ[(long long)m * N + n]);
-    db[n] = acc;
+    if (!TRAIN) return;
+    __syncthreads();
+    if (tid == 0) {
+        float sum = 0.0f;
+        for (int w = 0; w < kOut / 16; ++w) sum += wave_loss[w];
+        a.loss_part[blockIdx.x] = sum;
+    }
+
+    // dZ_{i-1} = bf16((dZ_i W_i) * GELU'(Z_{i-1}))
+    auto back = [&](const floatx4 acc, const float (&z)[R], const float (&e)[R], const int to, __bf16* dzT)
+                    __attribute__((always_inline)) {
+        __bf16 dz[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) dz[j] = static_cast<__bf16>(acc[j] * gelu_prime(z[j], e[j]));
+        put_column<R>(A[to], dzT, B, m0, col, lane, dz);
+        __syncthreads();
+    };
+    load_frags<kHidden>(wn, a.wt[2], n0, lane);
+    back(tile_product<kOut>(A[0], wf, lane), z2, e2, 1, a.dzT[2]);
+    load_frags<kHidden>(wf, a.wt[1], n0, lane);
+    back(tile_product<kHidden>(A[1], wn, lane), z1, e1, 0, a.dzT[1]);
+    back(tile_product<kHidden>(A[0], wf, lane), z0, e0, 1, a.dzT[0]);
+
+    // the schedule of a training loop: learning rate and bias corrections of this step (FP64
+    // running powers of b1, b2, as the host keeps them); mlp_grads counts the step
+    if (a.sc && blockIdx.x == 0 && tid == 0) {
+        TrainSched* sc = a.sc;
+        const int s = sc->next;
+        sc->cur = s;
+        sc->p1 *= a.b1;
+        sc->p2 *= a.b2;
+        sc->lr = a.lr[s];
+        sc->c1 = (float)(1.0 - sc->p1);
+        sc->c2 = (float)(1.0 - sc->p2);
+    }
 }
 
-// dst[n][k] = src[n][k] for k < cols (drops the zero padding of the first layer).
-__global__ void copy_cols(const float* __restrict__ src, int lds, float* __restrict__ dst, int rows, int cols)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < rows * cols) dst[i] = src[(i / cols) * lds + i % cols];
-}
+// Adam on one FP32 master parameter; returns its new value.  c1, c2: the bias corrections
+// 1 - b1^t, 1 - b2^t.
+struct AdamState { float p, m, v; };
 
-// Adam on the FP32 master parameters (the bf16 copies of the weights are
-// refreshed by to_bf16 afterwards).  c1, c2: the bias corrections 1 - b1^t, 1 - b2^t.
-__device__ __forceinline__ void adam_update(float* __restrict__ p, float* __restrict__ m, float* __restrict__ v,
-                                            const float* __restrict__ g, int i, float lr, float b1, float b2,
-                                            float eps, float c1, float c2)
+__device__ __forceinline__ float adam_update(float* __restrict__ p, float* __restrict__ m, float* __restrict__ v,
+                                             const AdamState old, float gi, int i, float lr, float b1, float b2,
+                                             float eps, float c1, float c2)
 {
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
+    const float mi = b1 * old.m + (1.0f - b1) * gi;
+    const float vi = b2 * old.v + (1.0f - b2) * gi * gi;
     m[i] = mi;
     v[i] = vi;
-    p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    const float pi = old.p - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    p[i] = pi;
+    return pi;
 }
 
 __global__ void adam(float* __restrict__ p, float* __restrict__ m, float* __restrict__ v,
@@ -172,54 +295,139 @@ __global__ void adam(float* __restrict__ p, float* __restrict__ m, float* __rest
                      float c2)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) adam_update(p, m, v, g, i, lr, b1, b2, eps, c1, c2);
+    if (i < n) adam_update(p, m, v, AdamState{p[i], m[i], v[i]}, g[i], i, lr, b1, b2, eps, c1, c2);
 }
 
-// The same update with the learning rate and bias corrections of the current
-// step read from the device schedule (training loops replayed from a graph).
-__global__ void adam_sched(float* __restrict__ p, float* __restrict__ m, float* __restrict__ v,
-                           const float* __restrict__ g, int n, const TrainSched* __restrict__ sc, float b1,
-                           float b2, float eps)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) adam_update(p, m, v, g, i, sc->lr, b1, b2, eps, sc->c1, sc->c2);
-}
+// Gradients of every parameter from the batch's layer inputs and pre-activation gradients
+// (fragments along the batch).  One wavefront per
+// 16 x 16 tile of a dW_i = dZ_i^T H_{i-1} (of the first layer's only the four columns of real
+// inputs are kept), then wavefronts of 64 bias gradients (sums over the batch in row order), then one
+// that sums up the loss.  ADAM: the update of the same parameters, the learning rate and
+// bias corrections from the schedule, and both bf16 copies of the weights.
+constexpr int kTiles3 = (kOut / 16) * (kHidden / 16), kTiles12 = (kHidden / 16) * (kHidden / 16), kTiles0 = kHidden / 16;
+constexpr int kTilesAll = kTiles3 + 2 * kTiles12 + kTiles0;
+constexpr int kBiases = 3 * kHidden + kOut;
+constexpr int kGradWaves = kTilesAll + kBiases / 64 + 1;
+constexpr int kGradAhead = 16;   // steps of 32 rows of the batch whose operands are in flight
+constexpr int kBiasAhead = 4;    // the same for the bias gradients
+constexpr int kBiasLd = 32 + 8;
 
-// One thread: advance the schedule to the next step: step index, learning rate
-// lr[step], running powers b1^t, b2^t (FP64 products, as the host keeps them) and
-// the bias corrections rounded to FP32.
-__global__ void sched_advance(TrainSched* __restrict__ sc, const float* __restrict__ lr, double b1, double b2)
+template <bool ADAM>
+__global__ __launch_bounds__(256) void mlp_grads(GradArgs g)
 {
-    const int s = sc->next;
-    sc->cur = s;
-    sc->next = s + 1;
-    sc->p1 *= b1;
-    sc->p2 *= b2;
-    sc->lr = lr[s];
-    sc->c1 = (float)(1.0 - sc->p1);
-    sc->c2 = (float)(1.0 - sc->p2);
-}
-
-// Rows idx[cur][i] of the training set into the step's buffers: features [B][4],
-// base [B][128] (if base_all is not NULL) and target [B][128].  One workgroup of
-// 128 threads per row.
-__global__ __launch_bounds__(kOut) void gather_rows(const float* __restrict__ x_all, const float* __restrict__ base_all,
-                                                    const float* __restrict__ t_all, const int* __restrict__ idx,
-                                                    const TrainSched* __restrict__ sc, int B, float* __restrict__ x,
-                                                    float* __restrict__ base, float* __restrict__ t)
-{
-    const int i = blockIdx.x, k = threadIdx.x;
-    const long long row = idx[(long long)sc->cur * B + i];
-    if (k < kIn) x[i * kIn + k] = x_all[row * kIn + k];
-    if (base_all) base[i * kOut + k] = base_all[row * kOut + k];
-    t[i * kOut + k] = t_all[row * kOut + k];
-}
-
-// loss_out[cur] = loss (one thread).
-__global__ void record_loss(const float* __restrict__ loss, const TrainSched* __restrict__ sc,
-                            float* __restrict__ loss_out)
-{
-    loss_out[sc->cur] = loss[0];
+    __shared__ __align__(16) __bf16 sh[4][64][kBiasLd];
+    const int lane = threadIdx.x & 63;
+    int t = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int B = g.B;
+    float lr = 0.0f, c1 = 1.0f, c2 = 1.0f;
+    if (ADAM) {
+        lr = g.sc->lr;
+        c1 = g.sc->c1;
+        c2 = g.sc->c2;
+    }
+    if (t < kTilesAll) {
+        const int i = t < kTiles3 ? 3 : t < kTiles3 + kTiles12 ? 2 : t < kTiles3 + 2 * kTiles12 ? 1 : 0;
+        t -= i == 3 ? 0 : i == 2 ? kTiles3 : i == 1 ? kTiles3 + kTiles12 : kTiles3 + 2 * kTiles12;
+        const int across = i == 0 ? 1 : kHidden / 16;
+        const int tm = (t / across) * 16, tn = (t % across) * 16;
+        const bf16x8* arow = reinterpret_cast<const bf16x8*>(g.dzT[i] + frag_at(tm, 0, B)) + lane;
+        const bf16x8* brow = reinterpret_cast<const bf16x8*>(g.inT[i] + frag_at(tn, 0, B)) + lane;
+        // the parameters and moments of this tile, requested with the first operands
+        const int c = tn + (lane & 15);
+        const bool kept = c < kLayerIn[i];
+        const int p0 = g.w_off[i] + (tm + (lane >> 4) * 4) * kLayerIn[i] + c;
+        AdamState old[4];
+        if (ADAM && kept) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int p = p0 + j * kLayerIn[i];
+                old[j] = AdamState{g.theta[p], g.m[p], g.v[p]};
+            }
+        }
+        floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+        int k0 = 0;
+        for (; k0 + 32 * kGradAhead <= B; k0 += 32 * kGradAhead) {
+            bf16x8 x[kGradAhead], y[kGradAhead];
+#pragma unroll
+            for (int s = 0; s < kGradAhead; ++s) {
+                x[s] = arow[2 * k0 + 64 * s];
+                y[s] = brow[2 * k0 + 64 * s];
+            }
+#pragma unroll
+            for (int s = 0; s < kGradAhead; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[s], y[s], acc, 0, 0, 0);
+        }
+        for (; k0 < B; k0 += 32)
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(arow[2 * k0], brow[2 * k0], acc, 0, 0, 0);
+        if (!kept) return;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int r = tm + (lane >> 4) * 4 + j;
+            const int p = p0 + j * kLayerIn[i];
+            g.grad[p] = acc[j];
+            if (ADAM) {
+                const __bf16 w =
+                    static_cast<__bf16>(adam_update(g.theta, g.m, g.v, old[j], acc[j], p, lr, g.b1, g.b2, g.eps, c1, c2));
+                g.w[i][frag_at(r, c, kLayerPad[i])] = w;
+                if (i > 0) g.wt[i][frag_at(c, r, kLayerOut[i])] = w;
+            }
+        }
+        return;
+    }
+    t -= kTilesAll;
+    if (t < kBiases / 64) {
+        const int n = t * 64 + lane;
+        const int i = n / kHidden, c = n % kHidden;  // 0 .. 3: three hidden layers, then the output
+        const int p = g.w_off[i] + kLayerOut[i] * kLayerIn[i] + c;
+        AdamState old{};
+        if (ADAM) old = AdamState{g.theta[p], g.m[p], g.v[p]};
+        // 32 rows of the batch at a time: the fragments of the 64 columns, turned around in LDS,
+        // then added by the column's lane in row order
+        const int i64 = (t * 64) / kHidden, c64 = (t * 64) % kHidden;
+        const bf16x8* from = reinterpret_cast<const bf16x8*>(g.dzT[i64] + frag_at(c64, 0, B)) + lane;
+        __bf16(*turn)[kBiasLd] = sh[threadIdx.x >> 6];
+        float acc = 0.0f;
+        for (int m = 0; m < B; m += 32 * kBiasAhead) {
+            bf16x8 x[kBiasAhead][4];
+#pragma unroll
+            for (int s = 0; s < kBiasAhead; ++s)
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (m + 32 * s < B) x[s][u] = from[(long long)u * (B >> 5) * 64 + 2 * m + 64 * s];
+#pragma unroll
+            for (int s = 0; s < kBiasAhead; ++s) {
+                if (m + 32 * s >= B) break;
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    *reinterpret_cast<bf16x8*>(&turn[16 * u + (lane & 15)][(lane >> 4) * 8]) = x[s][u];
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const bf16x8 w = *reinterpret_cast<const bf16x8*>(&turn[lane][8 * u]);
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) acc += static_cast<float>(w[j]);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+        g.grad[p] = acc;
+        if (ADAM) adam_update(g.theta, g.m, g.v, old, acc, p, lr, g.b1, g.b2, g.eps, c1, c2);
+        return;
+    }
+    if (t == kBiases / 64) {
+        float sum = 0.0f;
+        for (int q = lane; q < g.parts; q += 64) sum += g.loss_part[q];
+        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+        if (lane == 0) {
+            const float loss = sum / (float)(B * kOut);
+            g.loss[0] = loss;
+            if (ADAM) {
+                if (g.loss_out) g.loss_out[g.sc->cur] = loss;
+                g.sc->next += 1;
+            }
+        }
+    }
 }
 
 // flag[0] = 1 if some idx[j], j < n, lies outside [0, rows).
@@ -229,10 +437,17 @@ __global__ void check_rows(const int* __restrict__ idx, long long n, int rows, i
         if (idx[j] < 0 || idx[j] >= rows) flag[0] = 1;
 }
 
-__global__ void to_bf16(const float* __restrict__ src, __bf16* __restrict__ dst, int rows, int cols, int ldd)
+// bf16 copies of a layer's weights [rows][cols] in fragment order: dst for products over the
+// inputs (depth padded to pad) and, unless NULL, dst_t for products over the outputs.
+__global__ void to_bf16(const float* __restrict__ src, __bf16* __restrict__ dst, __bf16* __restrict__ dst_t, int rows,
+                        int cols, int pad)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < rows * cols) dst[(i / cols) * ldd + i % cols] = static_cast<__bf16>(src[i]);
+    if (i >= rows * cols) return;
+    const int r = i / cols, c = i % cols;
+    const __bf16 w = static_cast<__bf16>(src[i]);
+    dst[frag_at(r, c, pad)] = w;
+    if (dst_t) dst_t[frag_at(c, r, rows)] = w;
 }
 
 // ---------------------------------------------------------------- profiles
@@ -752,13 +967,6 @@ hipError_t gemm(const __bf16* A, long long sam, long long sak, const __bf16* B, 
     return hipGetLastError();
 }
 
-hipError_t launch_pack_input(const float* x, const float* mu, const float* inv_sd, __bf16* x16, int B,
-                             hipStream_t s)
-{
-    hipLaunchKernelGGL(pack_input, dim3(grid1((long long)B * kInPad, 256)), dim3(256), 0, s, x, mu, inv_sd, x16, B);
-    return hipGetLastError();
-}
-
 // bytes must be a multiple of 4
 hipError_t launch_fill(void* p, size_t bytes, hipStream_t s)
 {
@@ -768,34 +976,31 @@ hipError_t launch_fill(void* p, size_t bytes, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_bias_act(const float* C, const float* b, const float* base, float* Z, __bf16* H, int B, int N,
-                           hipStream_t s)
+// Rows per workgroup of the pass: four (one per lane group) up to 1024 rows, where that leaves
+// no more workgroups than compute units (512 rows: 11.8 us with 4 rows, 12.6 us with 8, 14.0 us
+// with 16); beyond, all 16 of the tile, since every workgroup reads all weights.
+int mlp_rows(int B) { return B <= 1024 ? 4 : 16; }
+
+hipError_t launch_mlp_pass(const MlpArgs& a, bool train, hipStream_t s)
 {
-    hipLaunchKernelGGL(bias_act, dim3(grid1((long long)B * N, 256)), dim3(256), 0, s, C, b, base, Z, H, B, N);
+    if (a.B <= 0 || a.B % (train ? 32 : 16)) return hipErrorInvalidValue;
+    const int rows = mlp_rows(a.B);
+    const dim3 grid(a.B / rows), block(kMlpThreads);
+    if (rows == 16) {
+        if (train) hipLaunchKernelGGL((mlp_pass<true, 4>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((mlp_pass<false, 4>), grid, block, 0, s, a);
+    } else {
+        if (train) hipLaunchKernelGGL((mlp_pass<true, 1>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((mlp_pass<false, 1>), grid, block, 0, s, a);
+    }
     return hipGetLastError();
 }
 
-hipError_t launch_mse_grad(const float* Y, const float* T, __bf16* dY, float* loss, int B, int N, hipStream_t s)
+hipError_t launch_mlp_grads(const GradArgs& g, bool update, hipStream_t s)
 {
-    hipLaunchKernelGGL(mse_grad, dim3(1), dim3(1024), 0, s, Y, T, dY, loss, B, N);
-    return hipGetLastError();
-}
-
-hipError_t launch_gelu_back(const float* dH, const float* Z, __bf16* dZ, int n, hipStream_t s)
-{
-    hipLaunchKernelGGL(gelu_back, dim3(grid1(n, 256)), dim3(256), 0, s, dH, Z, dZ, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_bias_grad(const __bf16* dZ, float* db, int B, int N, hipStream_t s)
-{
-    hipLaunchKernelGGL(bias_grad, dim3(grid1(N, 256)), dim3(256), 0, s, dZ, db, B, N);
-    return hipGetLastError();
-}
-
-hipError_t launch_copy_cols(const float* src, int lds, float* dst, int rows, int cols, hipStream_t s)
-{
-    hipLaunchKernelGGL(copy_cols, dim3(grid1((long long)rows * cols, 256)), dim3(256), 0, s, src, lds, dst, rows, cols);
+    if (g.B <= 0 || g.B % 32) return hipErrorInvalidValue;
+    if (update) hipLaunchKernelGGL(mlp_grads<true>, dim3((kGradWaves + 3) / 4), dim3(256), 0, s, g);
+    else hipLaunchKernelGGL(mlp_grads<false>, dim3((kGradWaves + 3) / 4), dim3(256), 0, s, g);
     return hipGetLastError();
 }
 
@@ -806,41 +1011,16 @@ hipError_t launch_adam(float* p, float* m, float* v, const float* g, int n, floa
     return hipGetLastError();
 }
 
-hipError_t launch_adam_sched(float* p, float* m, float* v, const float* g, int n, const TrainSched* sc, float b1,
-                             float b2, float eps, hipStream_t s)
-{
-    hipLaunchKernelGGL(adam_sched, dim3(grid1(n, 256)), dim3(256), 0, s, p, m, v, g, n, sc, b1, b2, eps);
-    return hipGetLastError();
-}
-
-hipError_t launch_sched_advance(TrainSched* sc, const float* lr, double b1, double b2, hipStream_t s)
-{
-    hipLaunchKernelGGL(sched_advance, dim3(1), dim3(1), 0, s, sc, lr, b1, b2);
-    return hipGetLastError();
-}
-
-hipError_t launch_gather_rows(const float* x_all, const float* base_all, const float* t_all, const int* idx,
-                              const TrainSched* sc, int B, float* x, float* base, float* t, hipStream_t s)
-{
-    hipLaunchKernelGGL(gather_rows, dim3(B), dim3(kOut), 0, s, x_all, base_all, t_all, idx, sc, B, x, base, t);
-    return hipGetLastError();
-}
-
-hipError_t launch_record_loss(const float* loss, const TrainSched* sc, float* loss_out, hipStream_t s)
-{
-    hipLaunchKernelGGL(record_loss, dim3(1), dim3(1), 0, s, loss, sc, loss_out);
-    return hipGetLastError();
-}
-
 hipError_t launch_check_rows(const int* idx, long long n, int rows, int* flag, hipStream_t s)
 {
     hipLaunchKernelGGL(check_rows, dim3(256), dim3(256), 0, s, idx, n, rows, flag);
     return hipGetLastError();
 }
 
-hipError_t launch_to_bf16(const float* src, __bf16* dst, int rows, int cols, int ldd, hipStream_t s)
+hipError_t launch_to_bf16(const float* src, __bf16* dst, __bf16* dst_t, int rows, int cols, int pad, hipStream_t s)
 {
-    hipLaunchKernelGGL(to_bf16, dim3(grid1((long long)rows * cols, 256)), dim3(256), 0, s, src, dst, rows, cols, ldd);
+    hipLaunchKernelGGL(to_bf16, dim3(grid1((long long)rows * cols, 256)), dim3(256), 0, s, src, dst, dst_t, rows, cols,
+                       pad);
     return hipGetLastError();
 }
 

@@ -10,8 +10,7 @@ constexpr int kHidden = 256;
 constexpr int kOut = 128;    // log-density samples across the interface
 constexpr double kSmooth = 1e-4;  // weight of the profile fit's smoothness term
 
-// Device state of a training loop replayed from a graph: the step being run
-// (cur), the next one, the running powers b1^t and b2^t of Adam's bias
+// Device state of a training loop: the step being run (cur), the next one, the running powers b1^t and b2^t of Adam's bias
 // correction (FP64, multiplied once per step as the host does), and the current
 // step's learning rate and FP32 bias corrections.
 struct TrainSched {
@@ -23,24 +22,50 @@ struct TrainSched {
 
 hipError_t gemm(const __bf16* A, long long sam, long long sak, const __bf16* B, long long sbk, long long sbn,
                 float* C, int ldc, int M, int N, int K, hipStream_t s);
-hipError_t launch_pack_input(const float* x, const float* mu, const float* inv_sd, __bf16* x16, int B,
-                             hipStream_t s);
-hipError_t launch_bias_act(const float* C, const float* b, const float* base, float* Z, __bf16* H, int B, int N,
-                           hipStream_t s);
-hipError_t launch_mse_grad(const float* Y, const float* T, __bf16* dY, float* loss, int B, int N, hipStream_t s);
-hipError_t launch_gelu_back(const float* dH, const float* Z, __bf16* dZ, int n, hipStream_t s);
-hipError_t launch_bias_grad(const __bf16* dZ, float* db, int B, int N, hipStream_t s);
-hipError_t launch_copy_cols(const float* src, int lds, float* dst, int rows, int cols, hipStream_t s);
+
+// One pass of a batch through the network.  Layers 0 .. 3: w[i] [out][in, padded] and wt[i]
+// [in][out] (i > 0) bf16 weights, bias[i].  These and the bf16 outputs below are in fragment
+// order (frag_at in lbml_kernels.hip).  Row m of the batch is row m of x, base (may be
+// NULL), target and y, or row idx[sc->next][m] of them.  Forward: y = network(x) + base.
+// Training: the first four rows of xT [16][B], hT[i] [256][B], dzT[i] [out][B] and the loss sums
+// loss_part [B / mlp_rows(B)]; with sc also the step's learning rate and bias corrections.
+struct MlpArgs {
+    const float *x, *base, *target;
+    const int* idx;
+    TrainSched* sc;
+    const float* lr;
+    double b1, b2;
+    const float* norm;  // feature means, then inverse standard deviations
+    const __bf16 *w[4], *wt[4];
+    const float* bias[4];
+    float* y;
+    __bf16 *xT, *hT[3], *dzT[4];
+    float* loss_part;
+    int B;
+};
+// B a multiple of 16 (forward) or 32 (training).  mlp_rows(B): rows per workgroup.
+int mlp_rows(int B);
+hipError_t launch_mlp_pass(const MlpArgs& a, bool train, hipStream_t s);
+
+// Gradients of all parameters from a training pass (inT[0] = xT, inT[i] = hT[i-1]) and the mean
+// loss; update: Adam on the parameters with the schedule's current values, their bf16 copies,
+// loss_out[sc->cur] (if not NULL) and the step count.
+struct GradArgs {
+    const __bf16 *dzT[4], *inT[4];
+    const float* loss_part;
+    float *grad, *loss, *loss_out;
+    float *theta, *m, *v;
+    __bf16 *w[4], *wt[4];
+    int w_off[4];
+    TrainSched* sc;
+    float b1, b2, eps;
+    int B, parts;  // parts = B / mlp_rows(B)
+};
+hipError_t launch_mlp_grads(const GradArgs& g, bool update, hipStream_t s);
 hipError_t launch_adam(float* p, float* m, float* v, const float* g, int n, float lr, float b1, float b2, float eps,
                        float c1, float c2, hipStream_t s);
-hipError_t launch_adam_sched(float* p, float* m, float* v, const float* g, int n, const TrainSched* sc, float b1,
-                             float b2, float eps, hipStream_t s);
-hipError_t launch_sched_advance(TrainSched* sc, const float* lr, double b1, double b2, hipStream_t s);
-hipError_t launch_gather_rows(const float* x_all, const float* base_all, const float* t_all, const int* idx,
-                              const TrainSched* sc, int B, float* x, float* base, float* t, hipStream_t s);
-hipError_t launch_record_loss(const float* loss, const TrainSched* sc, float* loss_out, hipStream_t s);
 hipError_t launch_check_rows(const int* idx, long long n, int rows, int* flag, hipStream_t s);
-hipError_t launch_to_bf16(const float* src, __bf16* dst, int rows, int cols, int ldd, hipStream_t s);
+hipError_t launch_to_bf16(const float* src, __bf16* dst, __bf16* dst_t, int rows, int cols, int pad, hipStream_t s);
 hipError_t launch_fill(void* p, size_t bytes, hipStream_t s);
 hipError_t launch_profile_extract(const float* rho, int nx, int ny, double cx, double cy, double R, double* part,
                                   float* logrho, hipStream_t s);

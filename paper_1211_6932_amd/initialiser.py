@@ -208,7 +208,7 @@ def schedule(n, steps, minibatch, lr, lr_min, seed):
 def train(X, base, T, steps=3000, lr=1e-3, lr_min=1e-5, minibatch=512, seed=1211, log=None, chunk=1000):
     """Adam on the mean squared error of (network + base) against T with a cosine
     learning-rate decay from lr to lr_min; minibatches drawn without replacement
-    within each pass over the data.  The steps run on the device in graph-replayed
+    within each pass over the data.  The steps run on the device in
     chunks (lbml_train_steps).  Then the FP64 level model of the interior is fitted.
     Returns (Initialiser, losses) with losses [(step, loss)] every 100 steps."""
     import torch

@@ -747,7 +747,7 @@ class Net:
         return None
 
     def train_steps(self, x_all, target_all, idx, lr, base_all=None, loss=None):
-        """len(lr) Adam steps replayed from a graph: step s on rows idx[s] of the device
+        """len(lr) Adam steps in one call: step s on rows idx[s] of the device
         tensors x_all [rows][4], target_all [rows][128] and base_all [rows][128] (or
         None), learning rate lr[s]; idx: device int32 [steps][B], lr: device float32
         [steps]; loss: device float32 [steps] receiving each step's loss, or None."""
