@@ -204,7 +204,9 @@ lb_status lb_set_state(lb_ctx* ctx, const void* src, int64_t t);
  * band = strips per tile band (the wavefronts of a workgroup cover `band`
  * strips in y times the rest in x); graph_chunk = steps per captured graph
  * (even, >= 2).  For each: a positive value sets it, 0 keeps the current
- * value, -1 (strip_rows, band only) restores the automatic choice.  Results do
+ * value, -1 (strip_rows, band only) restores the automatic choice, which is
+ * strips of some height or, on small lattices and with the 24-site stencil,
+ * regions of 32 x 32 sites (a positive strip_rows asks for strips).  Results do
  * not depend on any of them (bitwise). */
 lb_status lb_set_launch(lb_ctx* ctx, int32_t strip_rows, int32_t band, int32_t graph_chunk);
 

@@ -18,6 +18,7 @@
 //   copy_probe        plain streaming copy: attainable-bandwidth reference
 #include "d2q9_core.hpp"
 #include "d2q9_launch.hpp"
+#include "d2q9_region.hpp"
 #include "d2q9_two.hpp"
 
 namespace lbmp {
@@ -1203,6 +1204,56 @@ static hipError_t launch_mr(bool walls, const void* fin, void* fout, const StepC
     }
 #undef LBMP_MR
     return hipGetLastError();
+}
+
+template <int S, bool WALLS, int STENCIL>
+static hipError_t launch_region_psi(const void* fin, void* fout, const StepConst& k, int steps, int* flag,
+                                    hipStream_t s)
+{
+    using T = typename Codec<S>::T;
+    const dim3 grid((unsigned)(k.tiles_x * k.tiles_y)), block(kRegionThreads);
+    const T* in = static_cast<const T*>(fin);
+    T* out = static_cast<T*>(fout);
+    if (k.psi_form == kPsiSS)
+        hipLaunchKernelGGL((d2q9_region<S, WALLS, kPsiSS, STENCIL>), grid, block, 0, s, in, out, k, steps, flag);
+    else
+        hipLaunchKernelGGL((d2q9_region<S, WALLS, kPsiCS, STENCIL>), grid, block, 0, s, in, out, k, steps, flag);
+    return hipGetLastError();
+}
+
+int region_out(int stencil, int steps)
+{
+    const int halo = ((stencil == kStencilMultirange ? 2 : 1) + 1) * steps - 1;
+    return kRegion - 2 * halo;
+}
+
+hipError_t launch_region(int store, bool walls, const void* fin, void* fout, const StepConst& k, int steps, int* flag,
+                         hipStream_t s)
+{
+    const int out = region_out(k.stencil, steps);
+    if (steps < 1 || out < 1) return hipErrorInvalidValue;
+    if ((long long)k.row_stride * k.ny * 4 >= (1LL << 31)) return hipErrorInvalidValue;  // 32-bit offsets
+    StepConst kr = k;
+    kr.tiles_x = (k.nx + out - 1) / out;
+    kr.tiles_y = (k.ny + out - 1) / out;
+    if (k.stencil == kStencilMultirange) {
+        if (store != kStoreF32) return hipErrorInvalidValue;
+        return walls ? launch_region_psi<kStoreF32, true, kStencilMultirange>(fin, fout, kr, steps, flag, s)
+                     : launch_region_psi<kStoreF32, false, kStencilMultirange>(fin, fout, kr, steps, flag, s);
+    }
+#define LBMP_REGION(S_)                                                                                    \
+    return walls ? launch_region_psi<S_, true, kStencilNearest>(fin, fout, kr, steps, flag, s)             \
+                 : launch_region_psi<S_, false, kStencilNearest>(fin, fout, kr, steps, flag, s)
+    switch (store) {
+    case kStoreF32: LBMP_REGION(kStoreF32);
+    case kStoreF16: LBMP_REGION(kStoreF16);
+    case kStoreBF16: LBMP_REGION(kStoreBF16);
+    case kStoreF16Local: LBMP_REGION(kStoreF16Local);
+    case kStoreBF16Local: LBMP_REGION(kStoreBF16Local);
+    case kStoreF16Dest: LBMP_REGION(kStoreF16Dest);
+    default: return hipErrorInvalidValue;
+    }
+#undef LBMP_REGION
 }
 
 hipError_t launch_step(int store, bool walls, const void* fin, void* fout, const StepConst& k,

@@ -18,6 +18,12 @@ hipError_t launch_step(int store, bool walls, const void* fin, void* fout, const
 // waves: wavefronts per workgroup, kTwoWaves or kTwoWavesWide (results do not depend on it).
 hipError_t launch_two(bool walls, const void* fin, void* fout, const StepConst& k, int waves, int* flag, hipStream_t s);
 
+// `steps` time steps of a lattice (state below 2 GiB; any store and stencil) by regions
+// of 32 x 32 sites, of which each stores the inner region_out(stencil, steps) a side.
+int region_out(int stencil, int steps);
+hipError_t launch_region(int store, bool walls, const void* fin, void* fout, const StepConst& k, int steps, int* flag,
+                         hipStream_t s);
+
 // Whether launch_step runs the two-columns-per-lane kernel for this store type
 // and lattice width (destination-scaled FP16, even nx).
 bool pair_step(int store, int nx);

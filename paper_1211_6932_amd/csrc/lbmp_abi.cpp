@@ -238,6 +238,47 @@ int two_waves(const lb_params& p, int rows)
     return (long long)k.tiles_x * k.tiles_y >= 16LL * 4 * compute_units() ? lbmp::kTwoWavesWide : lbmp::kTwoWaves;
 }
 
+// Steps per launch by regions (d2q9_region), 0: the lattice is stepped by strips.
+//
+// Regions win as long as the overlap is computed by units that strips leave idle or waiting.
+// Measured, us per step, strips against regions (droplet, CS):
+//   FP32       128^2 4.07 / 2.03, 400 x 300 5.07 / 4.35, 512^2 6.45 / 5.79, 768 x 512 6.55 / 7.53
+//   FP16 dest  256^2 5.00 / 2.78, 600 x 250 5.91 / 5.05, 640 x 400 6.84 / 6.73, 641 x 640 7.57 / 8.79
+//   FP16       256^2 6.19 / 2.57, 1021 x 509 10.75 / 7.82, 2048 x 1024 25.7 / 21.8, 4096 x 1024 37.4 / 40.4
+//   FP16 local 200^2 7.37 / 2.59, 1021 x 509 14.27 / 8.65, 2048 x 1024 30.6 / 25.0, 2048 x 1400 31.4 / 31.9
+//   24 sites   200^2 7.66 / 3.14, 1021 x 509 14.82 / 11.05, 2048^2 79.3 / 64.0, 8192 x 4096 560 / 496
+// The 24-site stencil is bound by its strips' issue rate at every size: no limit but the
+// kernel's 32-bit offsets.
+//
+// A launch of n regions of `steps` steps takes about 4 + 1.1 steps + l (2.5 + 0.2 steps) us,
+// l = n / units - 0.6 where positive (fitted to the sizes above and 20 others for every
+// number of steps; the choice is within 9 % of the best one, on average 1 %).
+int region_steps(const lb_params& p)
+{
+    const long long sites = (long long)p.nx * p.ny;
+    if ((long long)row_slots(p.store) * pitch_of(p.nx, p.store) * p.ny * 4 >= (1LL << 31)) return 0;
+    const int ncu = compute_units();
+    long long most = 0;  // sites per compute unit
+    if (p.stencil == LB_STENCIL_MULTIRANGE) most = sites;
+    else if (p.store == LB_STORE_F32) most = 1200;
+    else if (p.store == LB_STORE_F16_DEST) most = 800;
+    else if (p.store == LB_STORE_F16_OFFSET || p.store == LB_STORE_BF16_OFFSET) most = 9000;
+    else most = 10000;
+    if (sites > most * ncu) return 0;
+    int best = 0;
+    double least = 1e300;
+    for (int steps = 1; lbmp::region_out(p.stencil, steps) > 0; ++steps) {
+        const long long out = lbmp::region_out(p.stencil, steps);
+        const double load = (double)(((p.nx + out - 1) / out) * ((p.ny + out - 1) / out)) / ncu;
+        const double cost = (4.0 + 1.1 * steps + std::max(0.0, load - 0.6) * (2.5 + 0.2 * steps)) / steps;
+        if (cost < least) {
+            least = cost;
+            best = steps;
+        }
+    }
+    return best;
+}
+
 // Strip height of the two-step launches.  A strip of h rows costs about h + 5 rows of work;
 // a SIMD that holds w of its strips (at most four at once) needs about 0.36 + 0.17 w per
 // row, in microseconds (fitted on 2048 x 1024 at heights 4-24: 16.0 us per step at 10 rows,
@@ -317,6 +358,7 @@ struct lb_ctx {
     lbmp::StepConst k2;  // launches of two steps (two == true)
     int waves2;          // wavefronts per workgroup of those launches
     bool two;
+    int region_steps;    // > 0: advanced by regions, up to that many steps per launch
     lbmp::StepConst kd;  // moments / diagnostics launches
     char* ws;
     void* f[2];
@@ -345,11 +387,17 @@ void drop_graphs(lb_ctx* c)
     }
 }
 
-// One launch from buffer `cur` into the other one: two steps where the lattice is stepped
-// that way and `left` allows it, else one.  *steps receives the number of steps taken.
+// One launch from buffer `cur` into the other one: by regions (the steps left spread evenly
+// over as few launches as they take), else two steps where the lattice is stepped that way
+// and `left` allows it, else one.  *steps receives the number of steps taken.
 hipError_t launch_some(lb_ctx* c, int cur, int64_t left, int* steps)
 {
     const bool walls = c->p.bc == LB_BC_WALLS_Y;
+    if (c->region_steps > 0) {
+        const int64_t launches = (left + c->region_steps - 1) / c->region_steps;
+        *steps = (int)((left + launches - 1) / launches);
+        return lbmp::launch_region(c->p.store, walls, c->f[cur], c->f[cur ^ 1], c->k, *steps, c->flag, c->stream);
+    }
     *steps = c->two && left >= 2 ? 2 : 1;
     if (*steps == 2) return lbmp::launch_two(walls, c->f[cur], c->f[cur ^ 1], c->k2, c->waves2, c->flag, c->stream);
     return lbmp::launch_step(c->p.store, walls, c->f[cur], c->f[cur ^ 1], c->k, c->flag, c->stream);
@@ -458,6 +506,7 @@ lb_status init_ctx(lb_ctx** out, const lb_params* p, void* workspace, size_t wor
     c->two = two_step(*p);
     c->k2 = derive_two(*p, auto_two_rows(*p), kDefaultBand);
     c->waves2 = two_waves(*p, c->k2.strip_rows);
+    c->region_steps = region_steps(*p);
     c->kd = derive(*p, pass_rows(*p));
     c->ws = static_cast<char*>(workspace);
     c->flag = reinterpret_cast<int*>(c->ws + L.flag_off);
@@ -674,6 +723,8 @@ lb_status lb_set_launch(lb_ctx* c, int32_t strip_rows, int32_t band, int32_t gra
     c->k2 = derive_two(c->p, rows2, bd);
     c->waves2 = two_waves(c->p, rows2);
     if (graph_chunk > 0) c->graph_chunk = graph_chunk;
+    if (strip_rows > 0) c->region_steps = 0;  // the caller asks for strips
+    if (strip_rows == -1) c->region_steps = region_steps(c->p);
     return LB_OK;
 }
 
