@@ -80,6 +80,8 @@ constexpr short kPrioPrefetch = 1;
 struct StepConst {
     int nx, ny, pitch;          // pitch in elements
     int tiles_x, tiles_y, strip_rows;
+    int paced;                  // single steps: the waves of a workgroup keep to one row (pace)
+    int back;                   // single steps: workgroups in descending order
     int band;                   // strips per tile band: consecutive tiles walk down `band` strips, then right
     long long row_stride;       // elements of the storage type per lattice row (9 or 11 pitches)
     float b4;                   // b / 4
@@ -386,6 +388,17 @@ __device__ __forceinline__ float density(const float f[9])
     return f[0] + ((f[1] + f[3]) + (f[2] + f[4])) + ((f[5] + f[7]) + (f[6] + f[8]));
 }
 
+// The partial sums of the density, and the differences of the same pairs: a walk that
+// computes a row's density before it collides the row keeps them.
+struct Sums { float ax, dg, xx, xy; };
+__device__ __forceinline__ float density(const float f[9], Sums& s)
+{
+    const float s13 = f[1] + f[3], s24 = f[2] + f[4];
+    const float s57 = f[5] + f[7], s68 = f[6] + f[8];
+    s = Sums{s13 + s24, s57 + s68, s13 - s24, s57 - s68};
+    return f[0] + s.ax + s.dg;
+}
+
 // Eq. (30) in FP64 for the diagnostics reductions (the liquid pressure is a
 // small difference of two large terms).
 __device__ __forceinline__ double p_eos_f64(double rho, double b4, double RT, double a)
@@ -437,6 +450,16 @@ __device__ __forceinline__ float root(float x)
     return fmaf(fmaf(-s, s, x), 0.5f * y, s);
 }
 
+// Shear rates of either phase as collide selects them.  in_vectors: held in vector registers
+// (a select takes one scalar operand at most: from scalars it costs a move each time).
+struct Shear { float a_l, a_g, b_l, b_g; };
+__device__ __forceinline__ Shear in_vectors(const StepConst& k)
+{
+    Shear s{k.a_nu_l, k.a_nu_g, k.b_nu_l, k.b_nu_g};
+    asm("" : "+v"(s.a_l), "+v"(s.a_g), "+v"(s.b_l), "+v"(s.b_g));
+    return s;
+}
+
 // Eq. (30) Carnahan-Starling pressure.
 __device__ __forceinline__ float p_eos(float rho, const StepConst& k)
 {
@@ -472,16 +495,18 @@ __device__ __forceinline__ float pseudopotential(float rho, const StepConst& k, 
     return ok ? root(psi2) : 0.0f;
 }
 
-// Eq. (7) with w(1) = 1/3, w(2) = 1/12, written out per neighbour:
-// psi rows m (y-1), c (y), p (y+1); columns L (x-1), C (x), R (x+1).
-__device__ __forceinline__ void force_stencil(float mL, float mC, float mR, float cL, float cC,
-                                              float cR, float pL, float pC, float pR,
-                                              const StepConst& k, float& Fx, float& Fy,
-                                              float& Fs2)
+// Eq. (7) with w(1) = 1/3, w(2) = 1/12, over the psi rows m (y-1), c (y), p (y+1) with
+// columns L (x-1), C (x), R (x+1).
+// A row enters as C and as D = R - L, S = R + L: a walk forms these once per row, not once
+// in each of the three force evaluations that use the row.
+struct PsiRow { float D, C, S; };
+__device__ __forceinline__ PsiRow psi_row(float L, float C, float R) { return PsiRow{R - L, C, R + L}; }
+__device__ __forceinline__ void force_stencil(const PsiRow& m, const PsiRow& c, const PsiRow& p,
+                                              const StepConst& k, float& Fx, float& Fy, float& Fs2)
 {
-    const float sx = (1.0f / 3.0f) * (cR - cL) + (1.0f / 12.0f) * ((pR - pL) + (mR - mL));
-    const float sy = (1.0f / 3.0f) * (pC - mC) + (1.0f / 12.0f) * ((pR + pL) - (mR + mL));
-    const float g = k.negG * cC;
+    const float sx = (1.0f / 3.0f) * c.D + (1.0f / 12.0f) * (p.D + m.D);
+    const float sy = (1.0f / 3.0f) * (p.C - m.C) + (1.0f / 12.0f) * (p.S - m.S);
+    const float g = k.negG * c.C;
     Fx = g * sx;
     Fy = g * sy;
     // |F|^2 / psi^2 = G^2 |sum w psi e|^2: the improved term of Eq. (25) needs no division
@@ -539,29 +564,27 @@ __device__ __forceinline__ void force_stencil_mr(const float (&P)[5][5], const S
 // With v from Eq. (6): m*_rho - m_rho = 0 and m*_j - m_j = F exactly.
 // (1 - s/2) times the extra Eq. (25) terms equals +12 sigma G^2 s_e |Fs|^2 for e
 // and -12 sigma G^2 s_zeta |Fs|^2 for eps.
+// s: the row's sums (density); nu: the shear rates of either phase.
 // Every expression is written so that mirroring the site in x or in y (which
 // negates vx, Fx, m_qx, m_xy or their y counterparts) negates or keeps each
 // intermediate exactly: a mirror-symmetric state stays mirror-symmetric.
-__device__ __forceinline__ void collide(float f[9], float rho, float vx, float vy, float Fx,
-                                        float Fy, float Fs2, const StepConst& k)
+__device__ __forceinline__ void collide(float f[9], float rho, const Sums& s, float vx, float vy,
+                                        float Fx, float Fy, float Fs2, const StepConst& k,
+                                        const Shear& nu)
 {
-    const float s13 = f[1] + f[3], s24 = f[2] + f[4];
-    const float s57 = f[5] + f[7], s68 = f[6] + f[8];
-    const float ax = s13 + s24;
-    const float dg = s57 + s68;
+    const float ax = s.ax, dg = s.dg;
     const float m_e = fmaf(-4.0f, f[0], fmaf(2.0f, dg, -ax));
     const float m_z = fmaf(4.0f, f[0], fmaf(-2.0f, ax, dg));
     const float d57 = f[5] - f[7], d68 = f[6] - f[8];
     const float m_qx = fmaf(-2.0f, f[1] - f[3], d57 - d68);
     const float m_qy = fmaf(-2.0f, f[2] - f[4], d57 + d68);
-    const float m_xx = s13 - s24;
-    const float m_xy = s57 - s68;
+    const float m_xx = s.xx, m_xy = s.xy;
 
     const float vF = vx * Fx + vy * Fy;
     const float v2 = vx * vx + vy * vy;
     const bool liq = rho >= k.rho_switch;
-    const float a_nu = liq ? k.a_nu_l : k.a_nu_g;
-    const float b_nu = liq ? k.b_nu_l : k.b_nu_g;
+    const float a_nu = liq ? nu.a_l : nu.a_g;
+    const float b_nu = liq ? nu.b_l : nu.b_g;
 
     // (m* - m) / norm for the non-conserved moments (Eq. 4, Eq. 3, Eq. 25)
     const float te = fmaf(-k.a_e, fmaf(-rho, fmaf(3.0f, v2, -2.0f), m_e), fmaf(k.b_e, vF, k.c_e * Fs2));
@@ -575,7 +598,7 @@ __device__ __forceinline__ void collide(float f[9], float rho, float vx, float v
     const float jx = Fx * (1.0f / 6.0f), jy = Fy * (1.0f / 6.0f);
     const float c_ax = fmaf(-2.0f, tz, -te);
     const float c_dg = fmaf(2.0f, te, tz);
-    f[0] += 4.0f * (tz - te);
+    f[0] = fmaf(4.0f, tz - te, f[0]);
     const float ux = fmaf(-2.0f, qx, jx), uy = fmaf(-2.0f, qy, jy);
     const float t13 = c_ax + pxx, t24 = c_ax - pxx;
     f[1] += t13 + ux;
@@ -590,6 +613,22 @@ __device__ __forceinline__ void collide(float f[9], float rho, float vx, float v
     f[8] += (d68p + xp) - yp;
 }
 
+__device__ __forceinline__ void collide(float f[9], float rho, float vx, float vy, float Fx,
+                                        float Fy, float Fs2, const StepConst& k)
+{
+    Sums s;
+    density(f, s);
+    collide(f, rho, s, vx, vy, Fx, Fy, Fs2, k, Shear{k.a_nu_l, k.a_nu_g, k.b_nu_l, k.b_nu_g});
+}
+
+// First moments of Eq. (6) before the force is added; the inner sums are collide's own.
+__device__ __forceinline__ void momentum(const float f[9], float& jx, float& jy)
+{
+    const float d57 = f[5] - f[7], d68 = f[6] - f[8];
+    jx = (f[1] - f[3]) + (d57 - d68);
+    jy = (f[2] - f[4]) + (d57 + d68);
+}
+
 // Workgroups are dispatched round-robin over the XCDs (block b runs on XCD
 // b mod 8).  Renumber them so that each XCD receives one contiguous run of
 // tiles: neighbouring strips (which share halo rows, halo columns and partly
@@ -600,6 +639,27 @@ __device__ __forceinline__ int logical_block(int b, int nb)
     const int per = nb / kNumXcd, rem = nb % kNumXcd;
     const int xcd = b % kNumXcd, idx = b / kNumXcd;
     return (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + idx;
+}
+
+// The same for a launch of single steps: every other launch goes through the lattice
+// backwards and so begins with what the one before wrote last, while the last-level cache
+// still holds it (8192 x 4096, one direction and alternating: FP16 276 and 263 us, FP16 dest
+// 267 and 262 us, FP16 local 379 and 374 us; two steps per launch: 249 and 249 us).
+__device__ __forceinline__ int launch_block(const StepConst& k)
+{
+    return k.back ? (int)gridDim.x - 1 - (int)blockIdx.x : (int)blockIdx.x;
+}
+
+// Keeps the waves of a workgroup, neighbours in x, on the same row, so that the workgroup
+// streams one wide stretch of each row at a time: pays where the state comes from memory
+// (two columns per lane, FP16 dest, 8192 x 4096: 274 us without, 267 us with; the kernels of
+// one column per lane lose: FP16 local 370 and 450 us; with two buffers that fit the
+// last-level cache the waits only cost, 2048 x 1024: 21.0 and 21.9 us).  No data is
+// exchanged; the hardware barrier counts only waves that have not ended, so waves of one
+// workgroup may walk strips of different heights.
+__device__ __forceinline__ void pace(const StepConst& k)
+{
+    if (k.paced) __builtin_amdgcn_s_barrier();
 }
 
 __device__ __forceinline__ float lane_from_left(float v) { return __shfl_up(v, 1, kWave); }

@@ -138,11 +138,13 @@ __global__ __launch_bounds__(kRegionThreads, region_waves_per_simd(S, STENCIL)) 
                 }
                 force_stencil_mr(W, k, Fx, Fy, Fs2);
             } else {
-                force_stencil(sp(yd, lx - 1), sp(yd, lx), sp(yd, lx + 1), sp(ly, lx - 1), sp(ly, lx), sp(ly, lx + 1),
-                              sp(yu, lx - 1), sp(yu, lx), sp(yu, lx + 1), k, Fx, Fy, Fs2);
+                auto row = [&](const int y9) __attribute__((always_inline)) {
+                    return psi_row(sp(y9, lx - 1), sp(y9, lx), sp(y9, lx + 1));
+                };
+                force_stencil(row(yd), row(ly), row(yu), k, Fx, Fy, Fs2);
             }
-            const float jx = (f[1] - f[3]) + ((f[5] - f[7]) + (f[8] - f[6]));
-            const float jy = (f[2] - f[4]) + ((f[5] - f[7]) + (f[6] - f[8]));
+            float jx, jy;
+            momentum(f, jx, jy);
             const float inv_rho = recip(r);
             collide(f, r, fmaf(0.5f, Fx, jx) * inv_rho, fmaf(0.5f, Fy, jy) * inv_rho, Fx, Fy, Fs2, k);
         }

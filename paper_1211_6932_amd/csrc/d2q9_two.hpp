@@ -41,20 +41,21 @@ __device__ __forceinline__ void two_walk(const float* __restrict__ fin, float* _
         if (WALLS) return y;
         return y < 0 ? y + k.ny : (y >= k.ny ? y - k.ny : y);
     };
-    struct Win { float L, C, R; };
+    const Shear nu = in_vectors(k);
+    using Win = PsiRow;
     auto window = [](const float v) __attribute__((always_inline)) {
-        return Win{lane_from_left(v), v, lane_from_right(v)};
+        return psi_row(lane_from_left(v), v, lane_from_right(v));
     };
-    auto collide_row = [&](float (&f)[9], const float r, const Win& before, const Win& c, const Win& after)
+    auto collide_row = [&](float (&f)[9], const float r, const Sums& sums, const Win& before, const Win& c, const Win& after)
                            __attribute__((always_inline)) {
         const Win& m = DIR > 0 ? before : after;
         const Win& p = DIR > 0 ? after : before;
         float Fx, Fy, Fs2;
-        force_stencil(m.L, m.C, m.R, c.L, c.C, c.R, p.L, p.C, p.R, k, Fx, Fy, Fs2);
-        const float jx = (f[1] - f[3]) + ((f[5] - f[7]) + (f[8] - f[6]));
-        const float jy = (f[2] - f[4]) + ((f[5] - f[7]) + (f[6] - f[8]));
+        force_stencil(m, c, p, k, Fx, Fy, Fs2);
+        float jx, jy;
+        momentum(f, jx, jy);
         const float inv_rho = recip(r);
-        collide(f, r, fmaf(0.5f, Fx, jx) * inv_rho, fmaf(0.5f, Fy, jy) * inv_rho, Fx, Fy, Fs2, k);
+        collide(f, r, sums, fmaf(0.5f, Fx, jx) * inv_rho, fmaf(0.5f, Fy, jy) * inv_rho, Fx, Fy, Fs2, k, nu);
     };
     // populations moving up (into the row above) / down, by column shift
     auto move_up = [](float (&to)[9], const float (&f)[9]) __attribute__((always_inline)) {
@@ -86,6 +87,7 @@ __device__ __forceinline__ void two_walk(const float* __restrict__ fin, float* _
     Win va{0.0f, 0.0f, 0.0f}, vb{0.0f, 0.0f, 0.0f}, vc{0.0f, 0.0f, 0.0f};
     float ra = 0.0f, rb = 0.0f, rc = 0.0f;
     float sa = 0.0f, sb = 0.0f, sc = 0.0f;
+    Sums f1{0.0f, 0.0f, 0.0f, 0.0f}, f2{0.0f, 0.0f, 0.0f, 0.0f};  // of rows r and r - 2 DIR
 #pragma unroll
     for (int a = 0; a < 9; ++a) ga[a] = gb[a] = gc[a] = 0.0f;
 
@@ -103,7 +105,7 @@ __device__ __forceinline__ void two_walk(const float* __restrict__ fin, float* _
     pull_row<kStoreF32, WALLS>(fin, k, wrap(rs), xm, xc, xp, fa);
     pull_row<kStoreF32, WALLS>(fin, k, wrap(rs + DIR), xm, xc, xp, fb);
     __builtin_amdgcn_s_setprio(0);
-    ra = density(fa);
+    ra = density(fa, f1);
     const float p0 = pseudopotential<PSI>(ra, k, bad);
     if (!has_h) pm = p0;
     wa = window(pm);
@@ -124,17 +126,18 @@ __device__ __forceinline__ void two_walk(const float* __restrict__ fin, float* _
         // the hardware barrier counts only waves that have not ended, so waves of one
         // workgroup may walk strips of different heights.
         __builtin_amdgcn_s_barrier();
+        Sums fn_sums{0.0f, 0.0f, 0.0f, 0.0f}, v_sums{0.0f, 0.0f, 0.0f, 0.0f};
         if (inside(r)) {
             __builtin_amdgcn_s_setprio(kPrioPrefetch);
             if (i <= n && inside(r + 2 * DIR)) pull_row<kStoreF32, WALLS>(fin, k, wrap(r + 2 * DIR), xm, xc, xp, fq);
             __builtin_amdgcn_s_setprio(0);
             if (inside(r + DIR)) {
-                rn = density(fn);
+                rn = density(fn, fn_sums);
                 a = window(pseudopotential<PSI>(rn, k, bad));
             } else {
                 a = c;  // mirror beyond a wall
             }
-            collide_row(f, rho, b, c, a);
+            collide_row(f, rho, f1, b, c, a);
             if (DIR > 0) move_down(v, f); else move_up(v, f);
             w[0] = f[0];
             w[1] = lane_from_left(f[1]);
@@ -145,7 +148,7 @@ __device__ __forceinline__ void two_walk(const float* __restrict__ fin, float* _
         const int q = r - DIR;
         if (i >= 0 && inside(q)) {
             bool bad2 = false;
-            q1 = density(v);
+            q1 = density(v, v_sums);
             h = window(pseudopotential<PSI>(q1, k, bad2));
             bad = bad || (bad2 && check);
             if (WALLS && q == e0) d = h;
@@ -153,7 +156,7 @@ __device__ __forceinline__ void two_walk(const float* __restrict__ fin, float* _
             h = d;  // mirror beyond a wall
         }
         if (i >= 2) {
-            collide_row(u, q2, e, d, h);
+            collide_row(u, q2, f2, e, d, h);
             if (live) {
                 float* out = fout + (long long)(q - DIR) * k.row_stride;
 #pragma unroll
@@ -164,6 +167,8 @@ __device__ __forceinline__ void two_walk(const float* __restrict__ fin, float* _
         // registers that row r - 2 DIR has left
         if (DIR > 0) move_up(u, f); else move_down(u, f);
         if (WALLS && r == e1) { if (DIR > 0) reflect_down(w, f); else reflect_up(w, f); }
+        f1 = fn_sums;
+        f2 = v_sums;
     };
     for (int i = is; i < n + 2; i += 3) {
         row(i, fa, fb, fc, ra, rb, wa, wb, wc, ga, gb, gc, sa, sb, va, vb, vc);

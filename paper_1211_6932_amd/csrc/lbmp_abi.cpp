@@ -36,6 +36,7 @@ constexpr size_t kAlign = 256;
 constexpr int kMinStripRows = 3;
 constexpr int kBatchPersistentRows = 24;  // measured best (one workgroup walks a whole lattice)
 constexpr int kDefaultBand = 1;
+constexpr size_t kLastLevelCache = (size_t)256 << 20;
 constexpr int kDefaultGraphChunk = 32;
 constexpr int kMaxSide = 1 << 20;
 
@@ -208,6 +209,16 @@ lbmp::StepConst derive(const lb_params& p, int strip_rows, int band = 1)
                                 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36};
     const bool global16 = p.store == LB_STORE_F16_OFFSET || p.store == LB_STORE_BF16_OFFSET;
     for (int a = 0; a < 9; ++a) k.off[a] = global16 ? (float)(w[a] * p.rho_ref) : 0.0f;
+    return k;
+}
+
+// Constants of the single-step launches of one lattice.  The waves of their workgroups are
+// paced (pace) where the two buffers exceed the last-level cache.  Batches are not: their
+// persistent launch gives the waves of a workgroup different numbers of strips.
+lbmp::StepConst derive_single(const lb_params& p, int strip_rows, int band)
+{
+    lbmp::StepConst k = derive(p, strip_rows, band);
+    k.paced = 2 * layout_of(p).buf_bytes > kLastLevelCache;
     return k;
 }
 
@@ -400,7 +411,9 @@ hipError_t launch_some(lb_ctx* c, int cur, int64_t left, int* steps)
     }
     *steps = c->two && left >= 2 ? 2 : 1;
     if (*steps == 2) return lbmp::launch_two(walls, c->f[cur], c->f[cur ^ 1], c->k2, c->waves2, c->flag, c->stream);
-    return lbmp::launch_step(c->p.store, walls, c->f[cur], c->f[cur ^ 1], c->k, c->flag, c->stream);
+    lbmp::StepConst k = c->k;
+    k.back = cur;
+    return lbmp::launch_step(c->p.store, walls, c->f[cur], c->f[cur ^ 1], k, c->flag, c->stream);
 }
 
 lb_status step_direct(lb_ctx* c, int64_t n)
@@ -502,7 +515,7 @@ lb_status init_ctx(lb_ctx** out, const lb_params* p, void* workspace, size_t wor
     if (!c) return fail(LB_ENOMEM, "host allocation failed");
     c->p = *p;
     c->L = L;
-    c->k = derive(*p, auto_strip_rows(*p), kDefaultBand);
+    c->k = derive_single(*p, auto_strip_rows(*p), kDefaultBand);
     c->two = two_step(*p);
     c->k2 = derive_two(*p, auto_two_rows(*p), kDefaultBand);
     c->waves2 = two_waves(*p, c->k2.strip_rows);
@@ -719,7 +732,7 @@ lb_status lb_set_launch(lb_ctx* c, int32_t strip_rows, int32_t band, int32_t gra
     }
     if (band > 0) bd = band;
     if (band == -1) bd = kDefaultBand;
-    c->k = derive(c->p, rows, bd);
+    c->k = derive_single(c->p, rows, bd);
     c->k2 = derive_two(c->p, rows2, bd);
     c->waves2 = two_waves(c->p, rows2);
     if (graph_chunk > 0) c->graph_chunk = graph_chunk;
