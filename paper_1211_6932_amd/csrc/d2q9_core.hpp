@@ -31,7 +31,6 @@ constexpr int kMrTileW = kWave - 4;   // output columns per wavefront, 24-site s
 constexpr int kTwoTileW = kWave - 6;  // output columns per wavefront, two time steps per launch
 constexpr int kTwoWaves = 4;          // wavefronts per workgroup, two time steps per launch
 constexpr int kTwoWavesWide = 8;      // the same on lattices with many strips per compute unit
-constexpr int kTwoWavesBatch = 4;     // the same, many lattices in one launch
 constexpr int kPairWaves = 4;         // wavefronts per workgroup, two columns per lane
 constexpr int kWavesPerBlock = 16;    // wavefronts (strips) per workgroup: FP32 step, FP32 batch
 constexpr int kBatchWaves = 16;       // wavefronts per workgroup (= per lattice) of the persistent batch

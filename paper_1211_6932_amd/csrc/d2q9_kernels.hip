@@ -856,14 +856,14 @@ __global__ __launch_bounds__(kWave * kPairWaves) void d2q9_batch_pair(
 // Two steps of every lattice of a list in one launch (FP32; descriptors with 58-column
 // tiles).  The 512-lattice sweep (51.8 M sites, bound as two_walk): 745 us per step with
 // single steps, 428 us with this.
-template <bool WALLS, int PSI>
-__global__ __launch_bounds__(kWave * kTwoWavesBatch)
+template <bool WALLS, int PSI, int WPB>
+__global__ __launch_bounds__(kWave * WPB)
 __attribute__((amdgpu_waves_per_eu(4))) void d2q9_batch_two(
     const BatchInstance* __restrict__ inst, const int* __restrict__ tile_start,
     const int* __restrict__ wg_first, int ntotal, int parity)
 {
     int g;
-    const BatchInstance* I = flat_lattice<kTwoWavesBatch>(inst, tile_start, wg_first, ntotal, g);
+    const BatchInstance* I = flat_lattice<WPB>(inst, tile_start, wg_first, ntotal, g);
     if (!I) return;
     const StepConst k = I->k;
     two_tile<WALLS, PSI>(reinterpret_cast<const float*>(I->f[parity]), reinterpret_cast<float*>(I->f[parity ^ 1]), k, g,
@@ -1360,12 +1360,20 @@ hipError_t launch_batch_flat(int store, bool walls, int psi, bool pair, const Ba
 }
 
 hipError_t launch_batch_two(bool walls, int psi, const BatchInstance* inst, const int* tile_start, const int* wg_first,
-                            int ntotal, int parity, hipStream_t s)
+                            int ntotal, int waves, int parity, hipStream_t s)
 {
     if (ntotal <= 0) return hipSuccess;
-    const dim3 grid((ntotal + kTwoWavesBatch - 1) / kTwoWavesBatch), block(kWave * kTwoWavesBatch);
-#define LBMP_TWOB(W_, P_) \
-    hipLaunchKernelGGL((d2q9_batch_two<W_, P_>), grid, block, 0, s, inst, tile_start, wg_first, ntotal, parity)
+    if (waves != kTwoWaves && waves != kTwoWavesWide) return hipErrorInvalidValue;
+    const dim3 grid((ntotal + waves - 1) / waves), block(kWave * waves);
+#define LBMP_TWOB(W_, P_)                                                                                              \
+    do {                                                                                                               \
+        if (waves == kTwoWavesWide)                                                                                    \
+            hipLaunchKernelGGL((d2q9_batch_two<W_, P_, kTwoWavesWide>), grid, block, 0, s, inst, tile_start, wg_first, \
+                               ntotal, parity);                                                                        \
+        else                                                                                                           \
+            hipLaunchKernelGGL((d2q9_batch_two<W_, P_, kTwoWaves>), grid, block, 0, s, inst, tile_start, wg_first,     \
+                               ntotal, parity);                                                                        \
+    } while (0)
     if (walls) {
         if (psi == kPsiSS) LBMP_TWOB(true, kPsiSS); else LBMP_TWOB(true, kPsiCS);
     } else {

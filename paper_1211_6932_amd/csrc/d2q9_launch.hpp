@@ -48,9 +48,9 @@ hipError_t launch_batch_flat(int store, bool walls, int psi, bool pair, const Ba
                              const int* tile_start, const int* wg_first, int ntotal, int parity, hipStream_t s);
 
 // Two steps of every lattice of a list (FP32, each at least 8 x 8; descriptors with
-// kTwoTileW-column tiles, kTwoWavesBatch tiles per workgroup).
+// kTwoTileW-column tiles, `waves` tiles per workgroup: kTwoWaves or kTwoWavesWide).
 hipError_t launch_batch_two(bool walls, int psi, const BatchInstance* inst, const int* tile_start, const int* wg_first,
-                            int ntotal, int parity, hipStream_t s);
+                            int ntotal, int waves, int parity, hipStream_t s);
 
 // Wavefronts (tiles) per workgroup of launch_batch_flat.
 int batch_waves_per_block(int store, bool pair);

@@ -290,14 +290,24 @@ int region_steps(const lb_params& p)
     return best;
 }
 
-// Strip height of the two-step launches.  A strip of h rows costs about h + 5 rows of work;
-// a SIMD that holds w of its strips (at most four at once) needs about 0.36 + 0.17 w per
-// row, in microseconds (fitted on 2048 x 1024 at heights 4-24: 16.0 us per step at 10 rows,
-// where every strip is resident at once, 18.2 us at 8 rows, 19.9 us at 4 rows, 20.5 us at
-// 24 rows).  On large lattices the cost falls slowly with h and the stride of the resident
-// strips decides: 8192 x 4096 at 8 / 12 / 16 / 22 / 36 rows 255 / 248 / 247 / 248 / 268 us.
-// On small ones the walk itself is the time: 128 x 128 at 2 / 3 / 4 / 8 rows 4.1 / 4.9 /
-// 5.2 / 7.8 us.
+// Time of a two-step launch of `strips` strips of h rows in workgroups of `waves`, in us per
+// step: a strip costs about h + 5 rows of work, and a SIMD that holds w of them (at most four
+// at once) needs about 0.36 + 0.17 w per row.  Fitted on 2048 x 1024 at heights 4-24: 16.0 us
+// per step at 10 rows, where every strip is resident at once, 18.2 us at 8 rows, 19.9 us at
+// 4 rows, 20.5 us at 24 rows.  It holds for batches, whose strips are one list: 40 lattices of
+// 200 x 200 at 6 / 8 / 12 / 16 rows 18.1 / 14.2 / 17.7 / 21.3 us (19.1 / 13.5 / 17.7 / 21.8 by
+// this).
+double two_cost(int h, long long strips, int waves, int ncu)
+{
+    const long long groups = (strips + waves - 1) / waves;
+    const double load = (double)((groups + ncu - 1) / ncu) * (waves / 4.0);
+    return (h + 5) * (0.36 * std::ceil(load / 4.0) + 0.17 * load);
+}
+
+// Strip height of the two-step launches: the cheapest.  On large lattices the cost falls
+// slowly with h and the stride of the resident strips decides: 8192 x 4096 at 8 / 12 / 16 /
+// 22 / 36 rows 255 / 248 / 247 / 248 / 268 us.  On small ones the walk itself is the time:
+// 128 x 128 at 2 / 3 / 4 / 8 rows 4.1 / 4.9 / 5.2 / 7.8 us.
 int auto_two_rows(const lb_params& p)
 {
     const int ncu = compute_units();
@@ -305,9 +315,7 @@ int auto_two_rows(const lb_params& p)
     double least = 1e300;
     for (int h = 2; h <= 18 && h <= p.ny; ++h) {
         const lbmp::StepConst k = derive_two(p, h);
-        const long long groups = ((long long)k.tiles_x * k.tiles_y + lbmp::kTwoWaves - 1) / lbmp::kTwoWaves;
-        const double load = (double)((groups + ncu - 1) / ncu);  // waves per SIMD
-        const double cost = (h + 5) * (0.36 * std::ceil(load / 4.0) + 0.17 * load);
+        const double cost = two_cost(h, (long long)k.tiles_x * k.tiles_y, lbmp::kTwoWaves, ncu);
         if (cost < least) {
             least = cost;
             best = h;
@@ -768,12 +776,15 @@ namespace {
 constexpr int kMaxStripRows = 64;
 constexpr int kTuneMaxRows = 8;
 
-// Two-step launches (FP32), the same sweep, by strip rows: 4: 101k  6: 114k  8: 119k
-// 10: 121k  12: 122k  16: 120k  24: 119k  48: 111k (73.5k with the best single-step height);
-// 96 lattices of 256 x 256: 8: 108k  12: 108k  16: 109k  48: 104k (57k).  One height serves
-// every width.
-constexpr int kBatchTwoRows = 12;
+// Heights that lb_batch_tune tries for the two-step launches.
 constexpr int kTuneTwoRows[] = {4, 6, 8, 10, 12, 14, 16, 20};
+
+// Height of equal strips of about `rows` rows.
+int even_rows(int ny, int rows)
+{
+    const int strips = std::max(1, (ny + rows / 2) / rows);
+    return (ny + strips - 1) / strips;
+}
 
 int default_batch_rows(int store)
 {
@@ -799,7 +810,7 @@ struct lb_batch {
     // FP32 lattices (all of them group 0) of at least 8 x 8 are stepped two at a time in the
     // stepwise mode, with descriptors and tables of their own (same dispatch order).
     bool two;
-    int two_rows, two_ntotal;
+    int two_rows, two_waves, two_ntotal;  // two_rows: tuned height, 0: batch_two_rows
     lbmp::BatchInstance* two_desc;
     int *two_start, *two_first;
     size_t two_capacity;
@@ -854,7 +865,7 @@ size_t batch_two_capacity(const lb_params* p, int n)
 {
     size_t tiles = 0;
     for (int i = 0; i < n; ++i) tiles += (size_t)((p[i].nx + lbmp::kTwoTileW - 1) / lbmp::kTwoTileW) * p[i].ny;
-    return tiles / lbmp::kTwoWavesBatch + 1;
+    return tiles / lbmp::kTwoWaves + 1;
 }
 
 size_t batch_two_bytes(const lb_params* p, int n)
@@ -930,6 +941,33 @@ int lattice_rows(const lb_batch* b, int i)
     return b->group_rows[batch_pair(b->inst[i]->p) ? 1 : 0];
 }
 
+// Wavefronts per workgroup of the two-step launches of a batch: with a full chip 8 pace a
+// wider stretch of a row (512 lattices of sides 64-512 at 16 rows 424 us per step, 435 us with
+// 4); as long as every strip can be resident 4 spread more evenly.
+int batch_two_waves(long long strips) { return strips > 16LL * compute_units() ? lbmp::kTwoWavesWide : lbmp::kTwoWaves; }
+
+// Strip height of the two-step launches of a batch: the cheapest for all its strips (two_cost).
+int batch_two_rows(const lb_batch* b)
+{
+    const int ncu = compute_units();
+    int best = 2;
+    double least = 1e300;
+    for (int h = 2; h <= 20; ++h) {
+        long long strips = 0;
+        for (int i = 0; i < b->n; ++i) {
+            const lb_params& p = b->inst[i]->p;
+            const int rows = even_rows(p.ny, h);
+            strips += (long long)((p.nx + lbmp::kTwoTileW - 1) / lbmp::kTwoTileW) * ((p.ny + rows - 1) / rows);
+        }
+        const double cost = two_cost(h, strips, batch_two_waves(strips), ncu);
+        if (cost < least) {
+            least = cost;
+            best = h;
+        }
+    }
+    return best;
+}
+
 // Copy the per-lattice launch descriptors (dispatch order) and the tile tables of
 // both groups to the device.
 hipError_t write_batch_descriptors(lb_batch* b)
@@ -975,13 +1013,15 @@ hipError_t write_batch_descriptors(lb_batch* b)
     if (b->two && b->mode == LB_BATCH_STEPWISE) {
         host2 = host;
         start2.assign(n + 1, 0);
+        const int target = b->two_rows > 0 ? b->two_rows : batch_two_rows(b);
         for (int j = 0; j < n; ++j) {
-            const int rows = b->fixed_rows > 0 ? b->fixed_rows : b->two_rows;
-            host2[j].k = derive_two(b->inst[b->order[j]]->p, rows);
+            const lb_params& p = b->inst[b->order[j]]->p;
+            host2[j].k = derive_two(p, b->fixed_rows > 0 ? b->fixed_rows : even_rows(p.ny, target));
             start2[j + 1] = start2[j] + host2[j].k.tiles_x * host2[j].k.tiles_y;
         }
         b->two_ntotal = start2[n];
-        for (int t = 0, i = 0; t < b->two_ntotal; t += lbmp::kTwoWavesBatch) {
+        b->two_waves = batch_two_waves(b->two_ntotal);
+        for (int t = 0, i = 0; t < b->two_ntotal; t += b->two_waves) {
             while (t >= start2[i + 1]) ++i;
             first2.push_back(i);
         }
@@ -1060,7 +1100,7 @@ hipError_t batch_launch_some(lb_batch* b, int parity, int64_t left, int* steps)
     *steps = b->two && left >= 2 ? 2 : 1;
     if (*steps == 1) return batch_flat_launch(b, parity);
     return lbmp::launch_batch_two(b->bc == LB_BC_WALLS_Y, b->psi, b->two_desc, b->two_start, b->two_first, b->two_ntotal,
-                                  parity, b->stream);
+                                  b->two_waves, parity, b->stream);
 }
 
 lb_status build_batch_graph(lb_batch* b, int from)
@@ -1152,7 +1192,7 @@ lb_status lb_batch_init(lb_batch** out, const lb_params* p, int32_t n, void* wor
     hoff += align_up(b->wg_capacity * sizeof(int), kAlign);
     b->two = batch_two(p, n);
     if (b->two) {
-        b->two_rows = kBatchTwoRows;
+        b->two_rows = 0;
         b->two_desc = reinterpret_cast<lbmp::BatchInstance*>(ws + hoff);
         hoff += align_up((size_t)n * sizeof(lbmp::BatchInstance), kAlign);
         b->two_start = reinterpret_cast<int*>(ws + hoff);
