@@ -290,6 +290,21 @@ int region_steps(const lb_params& p)
     return best;
 }
 
+// Whether regions also take a single step (left over, or all that was asked for): their launch
+// is then no longer shared by several.  Strips against regions, us: FP32 128^2 6.1 / 4.3,
+// 600 x 250 7.5 / 8.2; FP16 dest 256^2 5.0 / 5.4; FP16 256^2 6.2 / 5.1, 500 x 400 6.6 / 8.6;
+// FP16 local 1448 x 724 21.5 / 20.3, 2048 x 1024 30.6 / 39.3; 24 sites 1021 x 509 14.8 / 14.5,
+// 1448 x 724 22.3 / 25.1.
+bool region_single(const lb_params& p)
+{
+    long long most = 4300;  // sites per compute unit
+    if (p.stencil == LB_STENCIL_MULTIRANGE) most = 2000;
+    else if (p.store == LB_STORE_F32) most = 400;
+    else if (p.store == LB_STORE_F16_DEST) most = 100;
+    else if (p.store == LB_STORE_F16_OFFSET || p.store == LB_STORE_BF16_OFFSET) most = 300;
+    return (long long)p.nx * p.ny <= most * compute_units();
+}
+
 // Time of a two-step launch of `strips` strips of h rows in workgroups of `waves`, in us per
 // step: a strip costs about h + 5 rows of work, and a SIMD that holds w of them (at most four
 // at once) needs about 0.36 + 0.17 w per row.  Fitted on 2048 x 1024 at heights 4-24: 16.0 us
@@ -378,6 +393,7 @@ struct lb_ctx {
     int waves2;          // wavefronts per workgroup of those launches
     bool two;
     int region_steps;    // > 0: advanced by regions, up to that many steps per launch
+    bool region_single;  // by regions also where a launch takes one step
     lbmp::StepConst kd;  // moments / diagnostics launches
     char* ws;
     void* f[2];
@@ -415,9 +431,11 @@ hipError_t launch_some(lb_ctx* c, int cur, int64_t left, int* steps)
     if (c->region_steps > 0) {
         const int64_t launches = (left + c->region_steps - 1) / c->region_steps;
         *steps = (int)((left + launches - 1) / launches);
-        return lbmp::launch_region(c->p.store, walls, c->f[cur], c->f[cur ^ 1], c->k, *steps, c->flag, c->stream);
+        if (*steps > 1 || c->region_single)
+            return lbmp::launch_region(c->p.store, walls, c->f[cur], c->f[cur ^ 1], c->k, *steps, c->flag, c->stream);
+    } else {
+        *steps = c->two && left >= 2 ? 2 : 1;
     }
-    *steps = c->two && left >= 2 ? 2 : 1;
     if (*steps == 2) return lbmp::launch_two(walls, c->f[cur], c->f[cur ^ 1], c->k2, c->waves2, c->flag, c->stream);
     lbmp::StepConst k = c->k;
     k.back = cur;
@@ -528,6 +546,7 @@ lb_status init_ctx(lb_ctx** out, const lb_params* p, void* workspace, size_t wor
     c->k2 = derive_two(*p, auto_two_rows(*p), kDefaultBand);
     c->waves2 = two_waves(*p, c->k2.strip_rows);
     c->region_steps = region_steps(*p);
+    c->region_single = region_single(*p);
     c->kd = derive(*p, pass_rows(*p));
     c->ws = static_cast<char*>(workspace);
     c->flag = reinterpret_cast<int*>(c->ws + L.flag_off);

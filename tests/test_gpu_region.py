@@ -95,3 +95,15 @@ def test_an_unstable_site_is_reported(bc):
         with pytest.raises(B.LbError):
             s.check()
         s.close()
+
+
+@pytest.mark.parametrize("store,stencil,nx,ny", [("f16dest", 0, 200, 161), ("f16", 0, 300, 271), ("f32", 0, 400, 301),
+                                                 ("f32", 1, 800, 700), ("f16local", 0, 1200, 1001)])
+def test_a_left_over_single_step_by_strips(store, stencil, nx, ny):
+    """Sizes where regions take several steps per launch but leave one step to the strips."""
+    case = lattice(nx, ny, 1, 0, stencil)
+    one, reg = make(case, store), make(case, store)
+    one.set_launch(strip_rows=4)
+    for n in (1, 2, 3, 1, 7):
+        assert np.array_equal(state(one.step(n)), state(reg.step(n))), n
+    one.close(), reg.close()
