@@ -135,10 +135,22 @@ lb_status lbml_profile_to_rho0(const float* logrho, double R, double cx, double 
  * which its total mass sum rho0 equals `mass`, for instance the mass of the
  * tanh start of the same droplet, so that both starts relax to the same
  * equilibrium.  shift: device, 2 doubles, receives (delta, achieved mass);
- * delta is clamped to [-8, 8] if the mass is not reachable.  One workgroup
- * does the search: cost ~60 passes over the lattice.  Asynchronous. */
+ * delta is clamped to [-8, 8] if the mass is not reachable.  Asynchronous. */
 lb_status lbml_profile_to_rho0_mass(const float* logrho, double R, double cx, double cy, int32_t nx, int32_t ny,
                                     double mass, double* shift, float* rho0, void* stream);
+
+/* lbml_profiles_to_rho0_mass: n of these (n >= 1; p: host array, copied by the call) in
+ * launches that serve up to 32 profiles each.  The fields and shifts of different entries
+ * must not overlap; every entry is checked before the first launch.  Results are bitwise
+ * those of n calls of lbml_profile_to_rho0_mass.  Asynchronous. */
+typedef struct lbml_placement {
+    const float* logrho;
+    double R, cx, cy, mass;
+    int32_t nx, ny;
+    double* shift;
+    float* rho0;
+} lbml_placement;
+lb_status lbml_profiles_to_rho0_mass(const lbml_placement* p, int32_t n, void* stream);
 
 /* Liquid level.  Inside a relaxed droplet the density is uniform, the coexisting
  * liquid density (Sec. IV.A) shifted by the droplet's Laplace pressure

@@ -383,19 +383,28 @@ lb_status lbml_profile_to_rho0(const float* logrho, double R, double cx, double 
     return e == hipSuccess ? LB_OK : abi_hip_fail(e, "lbml_profile_to_rho0");
 }
 
+lb_status lbml_profiles_to_rho0_mass(const lbml_placement* p, int32_t n, void* stream)
+{
+    if (!p || n < 1) return abi_fail(LB_EINVAL, "need p and n >= 1");
+    for (int i = 0; i < n; ++i) {
+        const lbml_placement& q = p[i];
+        if (!q.rho0 || !q.logrho || !q.shift) return abi_fail(LB_EINVAL, "NULL argument");
+        if (q.nx < 1 || q.ny < 1 || q.ny > 65535 || (long long)q.nx * q.ny > (1LL << 31))
+            return abi_fail(LB_EINVAL, "bad lattice size");
+        if (!std::isfinite(q.cx) || !std::isfinite(q.cy) || !std::isfinite(q.R) || q.R < 0.0 || q.R > 1e6)
+            return abi_fail(LB_EINVAL, "centre and radius must be finite, 0 <= R <= 1e6");
+        if (!std::isfinite(q.mass) || !(q.mass > 0.0)) return abi_fail(LB_EINVAL, "mass must be positive and finite");
+        if (reinterpret_cast<uintptr_t>(q.shift) % 8) return abi_fail(LB_EINVAL, "shift must be 8-byte aligned");
+    }
+    hipError_t e = lbml::launch_profiles_to_rho0_mass(p, n, static_cast<hipStream_t>(stream));
+    return e == hipSuccess ? LB_OK : abi_hip_fail(e, "lbml_profile_to_rho0_mass");
+}
+
 lb_status lbml_profile_to_rho0_mass(const float* logrho, double R, double cx, double cy, int32_t nx, int32_t ny,
                                     double mass, double* shift, float* rho0, void* stream)
 {
-    if (!rho0 || !logrho || !shift) return abi_fail(LB_EINVAL, "NULL argument");
-    if (nx < 1 || ny < 1 || ny > 65535 || (long long)nx * ny > (1LL << 31))
-        return abi_fail(LB_EINVAL, "bad lattice size");
-    if (!std::isfinite(cx) || !std::isfinite(cy) || !std::isfinite(R) || R < 0.0 || R > 1e6)
-        return abi_fail(LB_EINVAL, "centre and radius must be finite, 0 <= R <= 1e6");
-    if (!std::isfinite(mass) || !(mass > 0.0)) return abi_fail(LB_EINVAL, "mass must be positive and finite");
-    if (reinterpret_cast<uintptr_t>(shift) % 8) return abi_fail(LB_EINVAL, "shift must be 8-byte aligned");
-    hipError_t e = lbml::launch_profile_to_rho0_mass(logrho, R, cx, cy, nx, ny, mass, shift, rho0,
-                                                     static_cast<hipStream_t>(stream));
-    return e == hipSuccess ? LB_OK : abi_hip_fail(e, "lbml_profile_to_rho0_mass");
+    const lbml_placement p{logrho, R, cx, cy, mass, nx, ny, shift, rho0};
+    return lbml_profiles_to_rho0_mass(&p, 1, stream);
 }
 
 lb_status lbml_profile_levels(const float* L, const float* x, int32_t B, double* levels, void* stream)

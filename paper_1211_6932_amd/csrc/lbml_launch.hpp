@@ -2,6 +2,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include "lbml.h"
+
 namespace lbml {
 
 constexpr int kIn = 4;       // inputs: a, T/T_c, R, nu_g/nu_l (standardised)
@@ -76,8 +78,7 @@ hipError_t launch_profile_extract_static(const float* rho, int nx, int ny, doubl
 int static_profile_rows();
 hipError_t launch_profile_to_rho0(const float* logrho, double R, double cx, double cy, int nx, int ny, float* rho0,
                                   hipStream_t s);
-hipError_t launch_profile_to_rho0_mass(const float* logrho, double R, double cx, double cy, int nx, int ny,
-                                       double mass, double* shift, float* rho0, hipStream_t s);
+hipError_t launch_profiles_to_rho0_mass(const lbml_placement* p, int n, hipStream_t s);
 hipError_t launch_profile_levels(const float* L, const float* x, int B, double* lev, hipStream_t s);
 hipError_t launch_profile_anchor(float* L, const float* x, const double* target, int B, hipStream_t s);
 

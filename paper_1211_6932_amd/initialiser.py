@@ -294,15 +294,11 @@ def learned_rho0(model, ws, anchored=True):
     starts then relax towards the same equilibrium).  Returns (fields, shifts)."""
     import torch
     prof = predict(model, ws, anchored)
-    fields, shifts = [], []
-    for i, w in enumerate(ws):
-        mass = float(w.rho0.astype(np.float32).sum(dtype=np.float64))
-        f, sh = lbmp.profile_to_rho0_mass(prof[i], w.info["R0"], w.info["cx"], w.info["cy"], w.params["nx"],
-                                          w.params["ny"], mass)
-        fields.append(f)
-        shifts.append(sh)
+    fields, shifts = lbmp.profiles_to_rho0_mass(
+        prof, [(w.info["R0"], w.info["cx"], w.info["cy"], w.params["nx"], w.params["ny"],
+                float(w.rho0.astype(np.float32).sum(dtype=np.float64))) for w in ws])
     torch.cuda.synchronize()
-    return fields, [float(s[0]) for s in torch.stack(shifts).cpu()]
+    return fields, shifts[:, 0].tolist()
 
 
 def evaluate(model, ws, steps=30000, every=50, log=None, ablation=False):

@@ -70,10 +70,17 @@ EXPORTS = [
     "lbml_loss_grad", "lbml_adam", "lbml_train_step", "lbml_destroy", "lbml_profile_extract",
     "lbml_profile_to_rho0", "lbml_gemm_bf16", "lbml_profile_scratch_bytes", "lbml_profile_to_rho0_mass",
     "lbml_profile_extract_noalloc", "lbml_profile_levels", "lbml_profile_anchor", "lbml_level_fit",
-    "lbml_level_eval", "lbml_train_steps",
+    "lbml_level_eval", "lbml_train_steps", "lbml_profiles_to_rho0_mass",
 ]
 LBML_IN, LBML_HIDDEN, LBML_OUT, LBML_PARAMS = 4, 256, 128, 165760
 LBML_LEVEL_TERMS = 168
+
+
+class lbml_placement(ctypes.Structure):
+    """One profile's placement of include/lbml.h."""
+    _fields_ = [("logrho", ctypes.c_void_p), ("R", ctypes.c_double), ("cx", ctypes.c_double), ("cy", ctypes.c_double),
+                ("mass", ctypes.c_double), ("nx", ctypes.c_int32), ("ny", ctypes.c_int32), ("shift", ctypes.c_void_p),
+                ("rho0", ctypes.c_void_p)]
 
 
 class lbml_level_model(ctypes.Structure):
@@ -169,6 +176,7 @@ def load():
         "lbml_profile_extract": ([vp, i32, i32, f64, f64, f64, vp, ctypes.c_size_t, vp, vp], ctypes.c_int),
         "lbml_profile_extract_noalloc": ([vp, i32, i32, f64, f64, f64, vp, vp], ctypes.c_int),
         "lbml_profile_to_rho0": ([vp, f64, f64, f64, i32, i32, vp, vp], ctypes.c_int),
+        "lbml_profiles_to_rho0_mass": ([ctypes.POINTER(lbml_placement), i32, vp], ctypes.c_int),
         "lbml_profile_to_rho0_mass": ([vp, f64, f64, f64, i32, i32, f64, vp, vp, vp], ctypes.c_int),
         "lbml_gemm_bf16": ([vp, i64, i64, vp, i64, i64, vp, i32, i32, i32, i32, vp], ctypes.c_int),
         "lbml_profile_levels": ([vp, vp, i32, vp, vp], ctypes.c_int),
@@ -434,6 +442,12 @@ def lbml_profile_to_rho0_mass(logrho_ptr, R, cx, cy, nx, ny, mass, shift_ptr, rh
     return _check(load().lbml_profile_to_rho0_mass(_vp(logrho_ptr), float(R), float(cx), float(cy), int(nx), int(ny),
                                                    float(mass), _vp(shift_ptr), _vp(rho0_ptr), _vp(stream)),
                   "lbml_profile_to_rho0_mass")
+
+
+def lbml_profiles_to_rho0_mass(placements, stream):
+    """placements: lbml_placement objects."""
+    p = (lbml_placement * len(placements))(*placements)
+    return _check(load().lbml_profiles_to_rho0_mass(p, len(p), _vp(stream)), "lbml_profiles_to_rho0_mass")
 
 
 def lbml_profile_levels(L_ptr, x_ptr, B, levels_ptr, stream):
@@ -813,6 +827,24 @@ def profile_to_rho0_mass(logrho, R, cx, cy, nx, ny, mass, out=None, shift=None, 
         shift = torch.empty(2, dtype=torch.float64, device=logrho.device)
     lbml_profile_to_rho0_mass(logrho.data_ptr(), R, cx, cy, nx, ny, mass, shift.data_ptr(), out.data_ptr(), stream)
     return out, shift
+
+
+def profiles_to_rho0_mass(logrho, placements, stream=0):
+    """profile_to_rho0_mass of each row of a device tensor logrho [n][128], placements: n of
+    (R, cx, cy, nx, ny, mass).  Returns (fields, shifts [n][2]); empty for n = 0."""
+    import torch
+    if logrho.stride(-1) != 1 or len(placements) != len(logrho):
+        raise ValueError("need n profiles contiguous in the last dimension and n placements")
+    fields = [torch.empty((int(ny), int(nx)), dtype=torch.float32, device=logrho.device)
+              for _, _, _, nx, ny, _ in placements]
+    shifts = torch.empty((len(fields), 2), dtype=torch.float64, device=logrho.device)
+    if fields:
+        step = logrho.stride(0) * logrho.element_size()
+        lbml_profiles_to_rho0_mass(
+            [lbml_placement(logrho.data_ptr() + i * step, float(R), float(cx), float(cy), float(mass), int(nx), int(ny),
+                            shifts.data_ptr() + 16 * i, fields[i].data_ptr())
+             for i, (R, cx, cy, nx, ny, mass) in enumerate(placements)], stream)
+    return fields, shifts
 
 
 def profile_levels(L, x, out=None, stream=0):

@@ -65,3 +65,19 @@ def test_mass(nx, ny, kind):
         assert abs(m - ref.sum()) <= 1e-9 * ref.sum()
         assert np.abs(field.cpu().numpy() / want - 1).max() < 1e-6
         assert store[0] == -1.0 and store[-1] == -1.0
+
+
+def test_mass_of_many_profiles():
+    """More profiles than one launch serves, of different sizes (among them lattices searched
+    by one workgroup): bitwise the fields and shifts of single calls."""
+    rng = np.random.default_rng(5)
+    sizes = [(int(a), int(b)) for a, b in rng.integers(20, 200, (33, 2))] + [(16, 16), (32, 32), (256, 257)]
+    L = torch.from_numpy(np.stack([profile("droplet") + 0.01 * i for i in range(len(sizes))]).astype(np.float32)).cuda()
+    places = [(0.25 * min(nx, ny), 0.45 * nx, 0.55 * ny, nx, ny, 0.05 * nx * ny) for nx, ny in sizes]
+    print("[gpu-case] mass placement of many profiles", flush=True)
+    fields, shifts = B.profiles_to_rho0_mass(L, places)
+    torch.cuda.synchronize()
+    for i, (R, cx, cy, nx, ny, mass) in enumerate(places):
+        field, shift = B.profile_to_rho0_mass(L[i], R, cx, cy, nx, ny, mass)
+        torch.cuda.synchronize()
+        assert torch.equal(field, fields[i]) and torch.equal(shift, shifts[i]), i
