@@ -39,6 +39,9 @@ __global__ __launch_bounds__(kRegionThreads, region_waves_per_simd(S, STENCIL)) 
     using T = typename C::T;
     constexpr bool local = S == kStoreF16Local || S == kStoreBF16Local;
     constexpr int reach = STENCIL == kStencilMultirange ? 2 : 1;
+    // the density's partial sums kept over the exchange of psi (600 x 250 with walls 3.95 us per
+    // step, 4.15 us recomputed); the 24-site stencil needs the registers (400 x 300 4.73 / 4.55 us)
+    constexpr bool keep = STENCIL == kStencilNearest;
     // a border around the region's sites keeps every neighbour at a fixed distance (what is
     // read from it is not used)
     constexpr int P = kRegion + 2 * reach, F = kRegion + 2;
@@ -117,8 +120,10 @@ __global__ __launch_bounds__(kRegionThreads, region_waves_per_simd(S, STENCIL)) 
         const int m = (reach + 1) * s;
         const bool busy = row0 + kWave / kRegion > m && row0 < kRegion - m;
         float r = 0.0f;
+        Sums sums{0.0f, 0.0f, 0.0f, 0.0f};
         if (busy) {
-            r = density(f);
+            if constexpr (keep) r = density(f, sums);
+            else r = density(f);
             bool b = false;
             sp(ly, lx) = pseudopotential<PSI>(r, k, b);
             bad = bad || (b && in && min(lx, ly) >= m && max(lx, ly) < kRegion - m);
@@ -146,7 +151,9 @@ __global__ __launch_bounds__(kRegionThreads, region_waves_per_simd(S, STENCIL)) 
             float jx, jy;
             momentum(f, jx, jy);
             const float inv_rho = recip(r);
-            collide(f, r, fmaf(0.5f, Fx, jx) * inv_rho, fmaf(0.5f, Fy, jy) * inv_rho, Fx, Fy, Fs2, k);
+            const float vx = fmaf(0.5f, Fx, jx) * inv_rho, vy = fmaf(0.5f, Fy, jy) * inv_rho;
+            if constexpr (!keep) density(f, sums);
+            collide(f, r, sums, vx, vy, Fx, Fy, Fs2, k, Shear{k.a_nu_l, k.a_nu_g, k.b_nu_l, k.b_nu_g});
         }
         // what the encoding stores, still as T
         T g[9];
