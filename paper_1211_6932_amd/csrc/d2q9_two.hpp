@@ -19,11 +19,11 @@ namespace lbmp {
 // arithmetic is that of strip_walk: the result is bitwise that of two single steps.
 //
 // What bounds it (8192 x 4096 splash): the single step moves 72 B per site and step and is
-// bound by HBM (428 us, 78.4k MLUPS).  Here 36 B and the halo rows remain, and the vector
-// ALU limits: 315 instructions per wavefront row and pair of steps, issued at about 90 % of
-// the rate at the clock the card holds under this load (2.05 GHz).  248 us per step, 135k
-// MLUPS.  One column per lane: the walk needs 118 VGPRs, so four waves per SIMD hide the
-// latency of its loads.
+// bound by HBM (428 us, 78.4k MLUPS).  Here 36 B and the halo rows remain, 5.5 TB/s or 88 % of
+// what a copy reaches, and the vector ALUs are busy for 76 % of the time: 276 instructions
+// per wavefront row and pair of steps (with 315 of them, at 90 %, a step took the same 248 us,
+// 135k MLUPS; 2048 x 1024 took 2 % longer).  One column per lane: the walk needs 121 VGPRs, so
+// four waves per SIMD hide the latency of its loads.
 template <bool WALLS, int PSI, int DIR>
 __device__ __forceinline__ void two_walk(const float* __restrict__ fin, float* __restrict__ fout,
                                          const StepConst& k, const int ty, const bool live, const bool check,

@@ -22,8 +22,8 @@ import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 # the kernel sources and the build script that fixes their compiler flags
-KERNEL_SOURCES = ["paper_1211_6932_amd/csrc/d2q9_core.hpp", "paper_1211_6932_amd/csrc/d2q9_kernels.hip",
-                  "paper_1211_6932_amd/build.py"]
+KERNEL_SOURCES = ["paper_1211_6932_amd/csrc/d2q9_core.hpp", "paper_1211_6932_amd/csrc/d2q9_two.hpp",
+                  "paper_1211_6932_amd/csrc/d2q9_kernels.hip", "paper_1211_6932_amd/build.py"]
 COPY_BYTES = 1 << 30
 
 
@@ -67,9 +67,9 @@ def _counter_by_kernel(d, counter):
 
 
 def _is_step_kernel(name):
-    """A time-step kernel: d2q9_strip<store, walls, MODE = 0, psi form>, or the
-    two-columns-per-lane d2q9_pair<walls, psi form>."""
-    if re.search(r"d2q9_pair(<|I)", name):  # the profiler may leave this name mangled
+    """A time-step kernel: d2q9_two (two steps), d2q9_strip<store, walls, MODE = 0, psi form>,
+    or the two-columns-per-lane d2q9_pair<walls, psi form>."""
+    if re.search(r"d2q9_(pair|two)(<|I)", name):  # the profiler may leave this name mangled
         return True
     m = re.search(r"d2q9_strip<(\d+), (true|false), (\d+), (\d+)>", name)
     return bool(m) and m.group(3) == "0"
