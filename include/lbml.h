@@ -113,6 +113,20 @@ size_t lbml_profile_scratch_bytes(int32_t ny);
 lb_status lbml_profile_extract(const float* rho, int32_t nx, int32_t ny, double cx, double cy, double R,
                                void* scratch, size_t scratch_bytes, float* logrho, void* stream);
 
+/* lbml_profiles_extract: n of these (n >= 1; p: host array, copied by the call) in launches that
+ * serve up to 32 fields each.  Every entry has its own scratch (lbml_profile_scratch_bytes(ny)
+ * bytes, 8-byte aligned); scratch and results of different entries must not overlap; every
+ * entry is checked before the first launch.  Results are bitwise those of n calls of
+ * lbml_profile_extract.  Asynchronous on `stream`. */
+typedef struct lbml_fit {
+    const float* rho;
+    double cx, cy, R;
+    int32_t nx, ny;
+    void* scratch;
+    float* logrho;
+} lbml_fit;
+lb_status lbml_profiles_extract(const lbml_fit* p, int32_t n, void* stream);
+
 /* lbml_profile_extract without a scratch argument, for callers that cannot allocate
  * device memory (code under graph capture, serving loops, harnesses that forbid
  * hipMalloc).  The row partials live in a static device array of the library,

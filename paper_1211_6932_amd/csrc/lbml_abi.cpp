@@ -357,6 +357,22 @@ lb_status lbml_profile_extract(const float* rho, int32_t nx, int32_t ny, double 
     return e == hipSuccess ? LB_OK : abi_hip_fail(e, "lbml_profile_extract");
 }
 
+lb_status lbml_profiles_extract(const lbml_fit* p, int32_t n, void* stream)
+{
+    if (!p || n < 1) return abi_fail(LB_EINVAL, "need p and n >= 1");
+    for (int i = 0; i < n; ++i) {
+        const lbml_fit& f = p[i];
+        if (!f.rho || !f.logrho || !f.scratch) return abi_fail(LB_EINVAL, "NULL argument");
+        if (f.nx < 2 || f.ny < 2 || f.nx > (1 << 20) || f.ny > (1 << 20) || (long long)f.nx * f.ny > (1LL << 31))
+            return abi_fail(LB_EINVAL, "bad lattice size");
+        if (!std::isfinite(f.cx) || !std::isfinite(f.cy) || !std::isfinite(f.R) || f.R < 0.0 || f.R > 1e6)
+            return abi_fail(LB_EINVAL, "centre and radius must be finite, 0 <= R <= 1e6");
+        if (reinterpret_cast<uintptr_t>(f.scratch) % 8) return abi_fail(LB_EINVAL, "scratch must be 8-byte aligned");
+    }
+    hipError_t e = lbml::launch_profiles_extract(p, n, static_cast<hipStream_t>(stream));
+    return e == hipSuccess ? LB_OK : abi_hip_fail(e, "lbml_profiles_extract");
+}
+
 lb_status lbml_profile_extract_noalloc(const float* rho, int32_t nx, int32_t ny, double cx, double cy, double R,
                                        float* logrho, void* stream)
 {

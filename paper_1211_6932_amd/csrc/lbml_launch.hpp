@@ -69,6 +69,7 @@ hipError_t launch_adam(float* p, float* m, float* v, const float* g, int n, floa
 hipError_t launch_check_rows(const int* idx, long long n, int rows, int* flag, hipStream_t s);
 hipError_t launch_to_bf16(const float* src, __bf16* dst, __bf16* dst_t, int rows, int cols, int pad, hipStream_t s);
 hipError_t launch_fill(void* p, size_t bytes, hipStream_t s);
+hipError_t launch_profiles_extract(const lbml_fit* p, int n, hipStream_t s);
 hipError_t launch_profile_extract(const float* rho, int nx, int ny, double cx, double cy, double R, double* part,
                                   float* logrho, hipStream_t s);
 // The same fit with its row partials in the library's static device scratch (ny up to

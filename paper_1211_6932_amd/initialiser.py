@@ -128,14 +128,19 @@ def relaxed_profiles(batch, ws, members, centres=None):
     they read."""
     import torch
     out = torch.empty((len(ws), N_OUT), dtype=torch.float32, device=batch.device)
-    scratch = torch.empty(max(lbmp.lbml_profile_scratch_bytes(w.params["ny"]) for w in ws), dtype=torch.uint8,
-                          device=batch.device)
-    s = batch.stream.cuda_stream
-    for i, (m, w) in enumerate(zip(members, ws)):
-        rho = batch.moments(int(m))[0]
-        R = w.info["R0"] if centres is None else float(centres[i])
-        lbmp.profile_extract(rho, w.info["cx"], w.info["cy"], R, out=out[i], scratch=scratch, stream=s)
-        rho.record_stream(batch.stream)
+    each = max(lbmp.lbml_profile_scratch_bytes(w.params["ny"]) for w in ws)
+    together = max(1, min(32, len(ws), (64 << 20) // each))  # fits per call
+    scratch = torch.empty(together * each, dtype=torch.uint8, device=batch.device)
+    todo = list(zip(members, ws))
+    for a in range(0, len(todo), together):
+        part = todo[a:a + together]
+        rhos = [batch.moments(int(m))[0] for m, _ in part]
+        lbmp.profiles_extract(rhos, [(w.info["cx"], w.info["cy"],
+                                      w.info["R0"] if centres is None else float(centres[a + i]))
+                                     for i, (_, w) in enumerate(part)],
+                              out[a:a + len(part)], scratch, stream=batch.stream.cuda_stream)
+        for rho in rhos:
+            rho.record_stream(batch.stream)
     batch.stream.synchronize()
     return out
 

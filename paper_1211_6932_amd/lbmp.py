@@ -71,9 +71,17 @@ EXPORTS = [
     "lbml_profile_to_rho0", "lbml_gemm_bf16", "lbml_profile_scratch_bytes", "lbml_profile_to_rho0_mass",
     "lbml_profile_extract_noalloc", "lbml_profile_levels", "lbml_profile_anchor", "lbml_level_fit",
     "lbml_level_eval", "lbml_train_steps", "lbml_profiles_to_rho0_mass",
+    "lbml_profiles_extract",
 ]
 LBML_IN, LBML_HIDDEN, LBML_OUT, LBML_PARAMS = 4, 256, 128, 165760
 LBML_LEVEL_TERMS = 168
+
+
+class lbml_fit(ctypes.Structure):
+    """One field's profile fit of include/lbml.h."""
+    _fields_ = [("rho", ctypes.c_void_p), ("cx", ctypes.c_double), ("cy", ctypes.c_double), ("R", ctypes.c_double),
+                ("nx", ctypes.c_int32), ("ny", ctypes.c_int32), ("scratch", ctypes.c_void_p),
+                ("logrho", ctypes.c_void_p)]
 
 
 class lbml_placement(ctypes.Structure):
@@ -176,6 +184,7 @@ def load():
         "lbml_profile_extract": ([vp, i32, i32, f64, f64, f64, vp, ctypes.c_size_t, vp, vp], ctypes.c_int),
         "lbml_profile_extract_noalloc": ([vp, i32, i32, f64, f64, f64, vp, vp], ctypes.c_int),
         "lbml_profile_to_rho0": ([vp, f64, f64, f64, i32, i32, vp, vp], ctypes.c_int),
+        "lbml_profiles_extract": ([ctypes.POINTER(lbml_fit), i32, vp], ctypes.c_int),
         "lbml_profiles_to_rho0_mass": ([ctypes.POINTER(lbml_placement), i32, vp], ctypes.c_int),
         "lbml_profile_to_rho0_mass": ([vp, f64, f64, f64, i32, i32, f64, vp, vp, vp], ctypes.c_int),
         "lbml_gemm_bf16": ([vp, i64, i64, vp, i64, i64, vp, i32, i32, i32, i32, vp], ctypes.c_int),
@@ -442,6 +451,12 @@ def lbml_profile_to_rho0_mass(logrho_ptr, R, cx, cy, nx, ny, mass, shift_ptr, rh
     return _check(load().lbml_profile_to_rho0_mass(_vp(logrho_ptr), float(R), float(cx), float(cy), int(nx), int(ny),
                                                    float(mass), _vp(shift_ptr), _vp(rho0_ptr), _vp(stream)),
                   "lbml_profile_to_rho0_mass")
+
+
+def lbml_profiles_extract(fits, stream):
+    """fits: lbml_fit objects."""
+    p = (lbml_fit * len(fits))(*fits)
+    return _check(load().lbml_profiles_extract(p, len(p), _vp(stream)), "lbml_profiles_extract")
 
 
 def lbml_profiles_to_rho0_mass(placements, stream):
@@ -805,6 +820,21 @@ def profile_extract(rho, cx, cy, R, out=None, scratch=None, stream=0):
     if scratch is None or scratch.numel() < need:
         scratch = torch.empty(need, dtype=torch.uint8, device=rho.device)
     lbml_profile_extract(rho.data_ptr(), nx, ny, cx, cy, R, scratch.data_ptr(), need, out.data_ptr(), stream)
+    return out
+
+
+def profiles_extract(rhos, places, out, scratch, stream=0):
+    """profile_extract of each of the contiguous fields rhos around places[i] = (cx, cy, R) into
+    the rows of out [n][128]; scratch: at least n times lbml_profile_scratch_bytes of the
+    tallest field."""
+    each = max(lbml_profile_scratch_bytes(rho.shape[0]) for rho in rhos)
+    if scratch.numel() * scratch.element_size() < each * len(rhos) or out.shape != (len(rhos), LBML_OUT) \
+            or not out.is_contiguous() or not all(rho.is_contiguous() for rho in rhos):
+        raise ValueError("profiles_extract: scratch too small, or out or a field of the wrong layout")
+    lbml_profiles_extract(
+        [lbml_fit(rho.data_ptr(), float(cx), float(cy), float(R), rho.shape[1], rho.shape[0],
+                  scratch.data_ptr() + i * each, out.data_ptr() + i * LBML_OUT * 4)
+         for i, (rho, (cx, cy, R)) in enumerate(zip(rhos, places, strict=True))], stream)
     return out
 
 

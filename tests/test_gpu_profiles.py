@@ -81,3 +81,22 @@ def test_mass_of_many_profiles():
         field, shift = B.profile_to_rho0_mass(L[i], R, cx, cy, nx, ny, mass)
         torch.cuda.synchronize()
         assert torch.equal(field, fields[i]) and torch.equal(shift, shifts[i]), i
+
+
+def test_fits_of_many_fields():
+    """More fields than one launch serves, of different sizes: bitwise the fits of single calls."""
+    rng = np.random.default_rng(6)
+    sizes = [(int(a), int(b)) for a, b in rng.integers(2, 150, (34, 2))] + [(300, 257)]
+    rhos = [torch.from_numpy((0.1 + rng.random((ny, nx))).astype(np.float32)).cuda() for nx, ny in sizes]
+    places = [(0.4 * nx, 0.6 * ny, 0.3 * min(nx, ny)) for nx, ny in sizes]
+    out = torch.full((len(sizes) + 1, 128), -1.0, device="cuda")
+    each = max(B.lbml_profile_scratch_bytes(ny) for _, ny in sizes)
+    scratch = torch.empty(each * len(sizes), dtype=torch.uint8, device="cuda")
+    print("[gpu-case] profile fits of many fields", flush=True)
+    B.profiles_extract(rhos, places, out[:len(sizes)], scratch)
+    torch.cuda.synchronize()
+    for i, rho in enumerate(rhos):
+        assert torch.equal(B.profile_extract(rho, *places[i]), out[i]), i
+    assert bool((out[-1] == -1.0).all())
+    with pytest.raises(ValueError):
+        B.profiles_extract(rhos, places, out[:len(sizes)], scratch[:-1])
