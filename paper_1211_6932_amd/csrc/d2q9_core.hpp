@@ -633,20 +633,25 @@ __device__ __forceinline__ void momentum(const float f[9], float& jx, float& jy)
 // tiles: neighbouring strips (which share halo rows, halo columns and partly
 // written cache lines at tile edges) then mostly meet in the same L2.  The map
 // is a permutation of block ids, so results do not depend on it.
-__device__ __forceinline__ int logical_block(int b, int nb)
+// back: each XCD goes through its run from the end (see launch_block).
+__device__ __forceinline__ int logical_block(int b, int nb, bool back = false)
 {
     const int per = nb / kNumXcd, rem = nb % kNumXcd;
     const int xcd = b % kNumXcd, idx = b / kNumXcd;
-    return (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + idx;
+    const int start = xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per;
+    const int last = per - (xcd < rem ? 0 : 1);
+    return start + (back ? last - idx : idx);
 }
 
-// The same for a launch of single steps: every other launch goes through the lattice
-// backwards and so begins with what the one before wrote last, while the last-level cache
-// still holds it (8192 x 4096, one direction and alternating: FP16 276 and 263 us, FP16 dest
-// 267 and 262 us, FP16 local 379 and 374 us; two steps per launch: 249 and 249 us).
+// The same for a launch of single steps: where the state exceeds the last-level cache, every
+// other launch takes each XCD's run from its end and so begins with what the one before wrote
+// last, while that cache still holds it (8192 x 4096, one direction and alternating: FP16 275
+// and 263 us, FP16 dest 268 and 262 us, FP16 local 381 and 374 us; two steps per launch: 249
+// and 249 us).  The runs stay on their XCDs: swapping them loses what is in the L2s (FP16 dest
+// 700 x 500 7.2 and 8.9 us).
 __device__ __forceinline__ int launch_block(const StepConst& k)
 {
-    return k.back ? (int)gridDim.x - 1 - (int)blockIdx.x : (int)blockIdx.x;
+    return logical_block(blockIdx.x, gridDim.x, k.back != 0);
 }
 
 // Keeps the waves of a workgroup, neighbours in x, on the same row, so that the workgroup

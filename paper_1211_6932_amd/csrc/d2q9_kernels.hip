@@ -290,7 +290,7 @@ __attribute__((amdgpu_waves_per_eu(1))) void d2q9_strip(
     // the wave index is uniform across the wave: keep it (and every row address
     // derived from it) in scalar registers
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int tile = logical_block(launch_block(k), gridDim.x) * waves_per_block(S, MODE) + wave;
+    const int tile = launch_block(k) * waves_per_block(S, MODE) + wave;
     if (tile >= k.tiles_x * k.tiles_y) return;  // whole wavefront leaves together
     strip_tile<S, WALLS, MODE, PSI>(fin, fout, k, tile, lane, flag, rho_out, ux_out, uy_out, dg, partial);
 }
@@ -623,7 +623,7 @@ __attribute__((amdgpu_waves_per_eu(1))) void d2q9_pair(
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int tile = logical_block(launch_block(k), gridDim.x) * kPairWaves + wave;
+    const int tile = launch_block(k) * kPairWaves + wave;
     if (tile >= k.tiles_x * k.tiles_y) return;  // whole wavefront leaves together
     pair_tile<WALLS, PSI>(fin, fout, k, tile, lane, flag);
 }

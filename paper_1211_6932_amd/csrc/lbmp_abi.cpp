@@ -438,7 +438,7 @@ hipError_t launch_some(lb_ctx* c, int cur, int64_t left, int* steps)
     }
     if (*steps == 2) return lbmp::launch_two(walls, c->f[cur], c->f[cur ^ 1], c->k2, c->waves2, c->flag, c->stream);
     lbmp::StepConst k = c->k;
-    k.back = cur;
+    k.back = k.paced ? cur : 0;
     return lbmp::launch_step(c->p.store, walls, c->f[cur], c->f[cur ^ 1], k, c->flag, c->stream);
 }
 
