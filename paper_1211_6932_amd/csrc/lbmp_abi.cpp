@@ -249,62 +249,6 @@ int two_waves(const lb_params& p, int rows)
     return (long long)k.tiles_x * k.tiles_y >= 16LL * 4 * compute_units() ? lbmp::kTwoWavesWide : lbmp::kTwoWaves;
 }
 
-// Steps per launch by regions (d2q9_region), 0: the lattice is stepped by strips.
-//
-// Regions win as long as the overlap is computed by units that strips leave idle or waiting.
-// Measured, us per step, strips against regions (droplet, CS):
-//   FP32       128^2 4.07 / 2.03, 400 x 300 5.07 / 4.35, 512^2 6.45 / 5.79, 768 x 512 6.55 / 7.53
-//   FP16 dest  256^2 5.00 / 2.78, 600 x 250 5.91 / 5.05, 640 x 400 6.84 / 6.73, 641 x 640 7.57 / 8.79
-//   FP16       256^2 6.19 / 2.57, 1021 x 509 10.75 / 7.82, 2048 x 1024 25.7 / 21.8, 4096 x 1024 37.4 / 40.4
-//   FP16 local 200^2 7.37 / 2.59, 1021 x 509 14.27 / 8.65, 2048 x 1024 30.6 / 25.0, 2048 x 1400 31.4 / 31.9
-//   24 sites   200^2 7.66 / 3.14, 1021 x 509 14.82 / 11.05, 2048^2 79.3 / 64.0, 8192 x 4096 560 / 496
-// The 24-site stencil is bound by its strips' issue rate at every size: no limit but the
-// kernel's 32-bit offsets.
-//
-// A launch of n regions of `steps` steps takes about 4 + 1.1 steps + l (2.5 + 0.2 steps) us,
-// l = n / units - 0.6 where positive (fitted to the sizes above and 20 others for every
-// number of steps; the choice is within 9 % of the best one, on average 1 %).
-int region_steps(const lb_params& p)
-{
-    const long long sites = (long long)p.nx * p.ny;
-    if ((long long)row_slots(p.store) * pitch_of(p.nx, p.store) * p.ny * 4 >= (1LL << 31)) return 0;
-    const int ncu = compute_units();
-    long long most = 0;  // sites per compute unit
-    if (p.stencil == LB_STENCIL_MULTIRANGE) most = sites;
-    else if (p.store == LB_STORE_F32) most = 1200;
-    else if (p.store == LB_STORE_F16_DEST) most = 800;
-    else if (p.store == LB_STORE_F16_OFFSET || p.store == LB_STORE_BF16_OFFSET) most = 9000;
-    else most = 10000;
-    if (sites > most * ncu) return 0;
-    int best = 0;
-    double least = 1e300;
-    for (int steps = 1; lbmp::region_out(p.stencil, steps) > 0; ++steps) {
-        const long long out = lbmp::region_out(p.stencil, steps);
-        const double load = (double)(((p.nx + out - 1) / out) * ((p.ny + out - 1) / out)) / ncu;
-        const double cost = (4.0 + 1.1 * steps + std::max(0.0, load - 0.6) * (2.5 + 0.2 * steps)) / steps;
-        if (cost < least) {
-            least = cost;
-            best = steps;
-        }
-    }
-    return best;
-}
-
-// Whether regions also take a single step (left over, or all that was asked for): their launch
-// is then no longer shared by several.  Strips against regions, us: FP32 128^2 6.1 / 4.3,
-// 600 x 250 7.5 / 8.2; FP16 dest 256^2 5.0 / 5.4; FP16 256^2 6.2 / 5.1, 500 x 400 6.6 / 8.6;
-// FP16 local 1448 x 724 21.5 / 20.3, 2048 x 1024 30.6 / 39.3; 24 sites 1021 x 509 14.8 / 14.5,
-// 1448 x 724 22.3 / 25.1.
-bool region_single(const lb_params& p)
-{
-    long long most = 4300;  // sites per compute unit
-    if (p.stencil == LB_STENCIL_MULTIRANGE) most = 2000;
-    else if (p.store == LB_STORE_F32) most = 400;
-    else if (p.store == LB_STORE_F16_DEST) most = 100;
-    else if (p.store == LB_STORE_F16_OFFSET || p.store == LB_STORE_BF16_OFFSET) most = 300;
-    return (long long)p.nx * p.ny <= most * compute_units();
-}
-
 // Time of a two-step launch of `strips` strips of h rows in workgroups of `waves`, in us per
 // step: a strip costs about h + 5 rows of work, and a SIMD that holds w of them (at most four
 // at once) needs about 0.36 + 0.17 w per row.  Fitted on 2048 x 1024 at heights 4-24: 16.0 us
@@ -339,6 +283,20 @@ int auto_two_rows(const lb_params& p)
     return best;
 }
 
+// Wavefronts per workgroup of the step kernel of this lattice, and its workgroups resident at
+// once.
+int strip_waves(const lb_params& p)
+{
+    return lbmp::pair_step(p.store, p.nx) ? lbmp::kPairWaves : lbmp::step_waves_per_block(p.store);
+}
+
+long long resident_groups(const lb_params& p)
+{
+    const bool walls = p.bc == LB_BC_WALLS_Y;
+    const int nb = lbmp::pair_step(p.store, p.nx) ? lbmp::pair_blocks_per_cu(walls) : lbmp::step_blocks_per_cu(p.store, walls);
+    return (long long)std::max(1, nb) * compute_units();
+}
+
 // Strip height for the step kernel.  Short strips are fastest on large grids
 // even though they re-read two halo rows per strip: the tiles are numbered
 // row-band by row-band, so the resident wavefronts work on a narrow band of
@@ -362,18 +320,122 @@ int auto_strip_rows(const lb_params& p)
         preferred = 8;
     else if (p.store == LB_STORE_F16_LOCAL || p.store == LB_STORE_BF16_LOCAL)
         preferred = 4;
-    int dev = 0, ncu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu <= 0)
-        return preferred;
-    const bool walls = p.bc == LB_BC_WALLS_Y;
-    const int nb = std::max(1, pair ? lbmp::pair_blocks_per_cu(walls) : lbmp::step_blocks_per_cu(p.store, walls));
-    const long long resident = (long long)nb * (pair ? lbmp::kPairWaves : lbmp::step_waves_per_block(p.store)) * ncu;
+    const long long resident = resident_groups(p) * strip_waves(p);
     const int tile_w = pair ? lbmp::kPairTileW : lbmp::kTileW;
     const long long tiles_x = (p.nx + tile_w - 1) / tile_w;
     const long long strips_wanted = (resident + tiles_x - 1) / tiles_x;
     const long long h = std::max<long long>(2, p.ny / strips_wanted);
     return (int)std::min<long long>(h, preferred);
+}
+
+// Regions of `steps` steps per compute unit.
+double region_load(const lb_params& p, int steps, int ncu)
+{
+    const long long out = lbmp::region_out(p.stencil, steps);
+    return (double)(((p.nx + out - 1) / out) * ((p.ny + out - 1) / out)) / ncu;
+}
+
+// Steps per launch by regions (d2q9_region), 0: the lattice is stepped by strips.
+//
+// Regions win as long as the overlap is computed by units that strips leave idle or waiting.
+// Measured, us per step, strips against regions (droplet, CS):
+//   FP32       128^2 4.07 / 2.03, 400 x 300 5.07 / 4.35, 512^2 6.45 / 5.79, 768 x 512 6.55 / 7.53
+//   FP16 dest  256^2 5.00 / 2.78, 600 x 250 5.91 / 5.05, 640 x 400 6.84 / 6.73, 641 x 640 7.57 / 8.79
+//   FP16       256^2 6.19 / 2.57, 1021 x 509 10.75 / 7.82, 2048 x 1024 25.7 / 21.8, 4096 x 1024 37.4 / 40.4
+//   FP16 local 200^2 7.37 / 2.59, 1021 x 509 14.27 / 8.65, 2048 x 1024 30.6 / 25.0, 2048 x 1400 31.4 / 31.9
+//   24 sites   200^2 7.66 / 3.14, 1021 x 509 14.82 / 11.05, 2048^2 79.3 / 64.0, 8192 x 4096 560 / 496
+// (768 x 512 and the like against FP32 strips of two steps per launch).  These are limits only:
+// at a given number of sites the strips' time depends on how their workgroups divide among
+// the units and the regions' on how many rows and columns of them lie outside the lattice, so
+// below the limits region_pays compares the two.
+//
+// A launch of n regions of `steps` steps takes about 4 + 1.1 steps + l (2.5 + 0.2 steps) us,
+// l = n / units - 0.6 where positive (fitted to the sizes above and 20 others for every
+// number of steps; the choice is within 9 % of the best one, on average 1 %).
+int region_steps(const lb_params& p)
+{
+    const long long sites = (long long)p.nx * p.ny;
+    if ((long long)row_slots(p.store) * pitch_of(p.nx, p.store) * p.ny * 4 >= (1LL << 31)) return 0;
+    const int ncu = compute_units();
+    long long most = 0;  // sites per compute unit
+    if (p.stencil == LB_STENCIL_MULTIRANGE) most = sites;
+    else if (p.store == LB_STORE_F32) most = 1200;
+    else if (p.store == LB_STORE_F16_DEST) most = 800;
+    else if (p.store == LB_STORE_F16_OFFSET || p.store == LB_STORE_BF16_OFFSET) most = 9000;
+    else most = 10000;
+    if (sites > most * ncu) return 0;
+    int best = 0;
+    double least = 1e300;
+    for (int steps = 1; lbmp::region_out(p.stencil, steps) > 0; ++steps) {
+        const double load = region_load(p, steps, ncu);
+        const double cost = (4.0 + 1.1 * steps + std::max(0.0, load - 0.6) * (2.5 + 0.2 * steps)) / steps;
+        if (cost < least) {
+            least = cost;
+            best = steps;
+        }
+    }
+    return best;
+}
+
+// Times in us of a step by strips and of a launch of `steps` steps by regions:
+//   strips   s0 + fill min(1, workgroups / resident) + rounds (s1 + s2 rows), the workgroups
+//            taking turns in `rounds` of as many as are resident at once;
+//   regions  r0 + r1 steps + load (r2 + r3 steps), + r4 where some unit has two regions.
+// Fitted on 250 lattices of each kind (3e3 to 4e6 sites, sides 8 to 125000, walls and
+// periodic): strips within 8 % and rather too low, regions within 9 %, so that a launch by
+// regions is a gain where these say so (of 3500 choices 20 lost more than 2 %, none more than
+// 8 %; by the numbers of sites alone 360 did, up to 2.5 times).  Strips against regions, us per
+// step: FP16 1984 x 1024 17.5 / 22.1, 992 x 2048 16.0 / 24.1 (one full round of strips), 2048 x
+// 1024 25.7 / 21.8 (two, the second nearly empty); FP32 37500 x 8 6.6 / 9.9, FP16 125000 x 8
+// 14 / 31 (regions mostly off the lattice); 24 sites 1876 x 1823 48.8 / 53.9.  Single steps: FP16
+// local 525 x 505 8.3 / 11.1, 724^2 15.0 / 12.2; 24 sites 641 x 640 9.2 / 12.3, 724^2 16.1 / 13.8.
+struct LaunchCost { double s0, fill, s1, s2, r0, r1, r2, r3, r4; };
+LaunchCost launch_cost(const lb_params& p, bool pair)
+{
+    if (p.stencil == LB_STENCIL_MULTIRANGE) return {1.2, 1.2, 2.35, 2.2, 3.5, 1.1, 3.85, 0.0, 0.4};
+    if (p.store == LB_STORE_F32) return {0.7, 1.0, 0.8, 2.25, 2.95, 1.07, 6.24, -0.31, 0.64};
+    if (p.store == LB_STORE_F16_DEST)
+        return pair ? LaunchCost{1.1, 0.0, 3.15, 0.37, 2.7, 1.3, 6.85, -0.92, 5.2}
+                    : LaunchCost{-0.8, 0.0, 4.8, 0.2, 2.7, 1.3, 6.85, -0.92, 5.2};
+    if (p.store == LB_STORE_F16_OFFSET || p.store == LB_STORE_BF16_OFFSET)
+        return {1.6, 1.2, 2.2, 1.3, 4.4, 0.67, 2.2, 0.55, 1.5};
+    return {1.0, 1.2, 3.2, 1.7, 4.75, 0.8, 2.75, 0.45, 0.9};
+}
+
+// Whether a launch of `steps` steps by regions takes no longer than the same steps by strips
+// (height `rows`, `resident` workgroups of `waves` strips at once).
+bool region_pays(const lb_params& p, int steps, int rows, long long resident, int waves)
+{
+    const int ncu = compute_units();
+    const bool pair = lbmp::pair_step(p.store, p.nx);
+    // FP32 has strips of two steps per launch: regions win on every lattice below the limit
+    // but the flattest (600 x 250 5.1 / 3.7, 4687 x 64 6.4 / 5.6, 9375 x 32 6.5 / 7.2)
+    if (p.store == LB_STORE_F32 && p.stencil == LB_STENCIL_NEAREST && steps > 1)
+        return p.ny >= 64 || (long long)p.nx * p.ny <= 600LL * ncu;
+    // 24 sites, well beyond the last-level cache: the strips slow down, the regions do not
+    // (1160 x 3206, 268 MB, 53.2 / 60.1; 2048 x 2048, 302 MB, 82 / 64)
+    if (p.stencil == LB_STENCIL_MULTIRANGE && steps > 1 && 2 * layout_of(p).buf_bytes > (size_t)272 << 20) return true;
+    const LaunchCost c = launch_cost(p, pair);
+    const int tile = pair ? lbmp::kPairTileW : tile_width(p);
+    const long long strips = (long long)((p.nx + tile - 1) / tile) * ((p.ny + rows - 1) / rows);
+    const long long groups = (strips + waves - 1) / waves;
+    const double strip = c.s0 + c.fill * std::min(1.0, (double)groups / resident) +
+                         (double)((groups + resident - 1) / resident) * (c.s1 + c.s2 * rows);
+    const double load = region_load(p, steps, ncu);
+    const double region = c.r0 + c.r1 * steps + load * (c.r2 + c.r3 * steps) + (load > 1.0 ? c.r4 : 0.0);
+    return region * (steps == 1 ? 1.06 : 1.0) <= steps * strip;  // single steps are the closest
+}
+
+// The numbers of steps (bits 1 and up) that the lattice takes by regions in one launch.
+unsigned region_mask(const lb_params& p, int most)
+{
+    if (most <= 0) return 0;
+    const int rows = auto_strip_rows(p);
+    const long long resident = resident_groups(p);
+    unsigned mask = 0;
+    for (int steps = 1; steps <= most; ++steps)
+        if (region_pays(p, steps, rows, resident, strip_waves(p))) mask |= 1u << steps;
+    return mask;
 }
 
 }  // namespace
@@ -392,8 +454,8 @@ struct lb_ctx {
     lbmp::StepConst k2;  // launches of two steps (two == true)
     int waves2;          // wavefronts per workgroup of those launches
     bool two;
-    int region_steps;    // > 0: advanced by regions, up to that many steps per launch
-    bool region_single;  // by regions also where a launch takes one step
+    int region_steps;      // > 0: advanced by regions, up to that many steps per launch
+    unsigned region_mask;  // bit n: a launch that takes n steps is by regions, else these are by strips
     lbmp::StepConst kd;  // moments / diagnostics launches
     char* ws;
     void* f[2];
@@ -412,6 +474,15 @@ struct lb_ctx {
 
 namespace {
 
+// Regions as the rules say; none where no launch would be by regions at the full number of
+// steps.
+void set_regions(lb_ctx* c)
+{
+    c->region_steps = region_steps(c->p);
+    c->region_mask = region_mask(c->p, c->region_steps);
+    if (!(c->region_mask >> c->region_steps & 1)) c->region_steps = 0;
+}
+
 void drop_graphs(lb_ctx* c)
 {
     for (int i = 0; i < 2; ++i) {
@@ -423,19 +494,20 @@ void drop_graphs(lb_ctx* c)
 }
 
 // One launch from buffer `cur` into the other one: by regions (the steps left spread evenly
-// over as few launches as they take), else two steps where the lattice is stepped that way
-// and `left` allows it, else one.  *steps receives the number of steps taken.
+// over as few launches as they take) where that number of steps pays, else two steps where
+// the lattice is stepped that way and `left` allows it, else one.  *steps receives the number
+// of steps taken.
 hipError_t launch_some(lb_ctx* c, int cur, int64_t left, int* steps)
 {
     const bool walls = c->p.bc == LB_BC_WALLS_Y;
     if (c->region_steps > 0) {
         const int64_t launches = (left + c->region_steps - 1) / c->region_steps;
         *steps = (int)((left + launches - 1) / launches);
-        if (*steps > 1 || c->region_single)
+        if (c->region_mask >> *steps & 1)
             return lbmp::launch_region(c->p.store, walls, c->f[cur], c->f[cur ^ 1], c->k, *steps, c->flag, c->stream);
-    } else {
-        *steps = c->two && left >= 2 ? 2 : 1;
+        left = *steps;
     }
+    *steps = c->two && left >= 2 ? 2 : 1;
     if (*steps == 2) return lbmp::launch_two(walls, c->f[cur], c->f[cur ^ 1], c->k2, c->waves2, c->flag, c->stream);
     lbmp::StepConst k = c->k;
     k.back = k.paced ? cur : 0;
@@ -545,8 +617,7 @@ lb_status init_ctx(lb_ctx** out, const lb_params* p, void* workspace, size_t wor
     c->two = two_step(*p);
     c->k2 = derive_two(*p, auto_two_rows(*p), kDefaultBand);
     c->waves2 = two_waves(*p, c->k2.strip_rows);
-    c->region_steps = region_steps(*p);
-    c->region_single = region_single(*p);
+    set_regions(c);
     c->kd = derive(*p, pass_rows(*p));
     c->ws = static_cast<char*>(workspace);
     c->flag = reinterpret_cast<int*>(c->ws + L.flag_off);
@@ -764,7 +835,7 @@ lb_status lb_set_launch(lb_ctx* c, int32_t strip_rows, int32_t band, int32_t gra
     c->waves2 = two_waves(c->p, rows2);
     if (graph_chunk > 0) c->graph_chunk = graph_chunk;
     if (strip_rows > 0) c->region_steps = 0;  // the caller asks for strips
-    if (strip_rows == -1) c->region_steps = region_steps(c->p);
+    if (strip_rows == -1) set_regions(c);
     return LB_OK;
 }
 
