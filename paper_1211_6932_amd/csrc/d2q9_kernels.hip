@@ -1050,7 +1050,8 @@ __global__ __launch_bounds__(256) void copy_probe(const float4* __restrict__ src
 // Dynamic LDS that caps the resident workgroups of a strip kernel at `cap` per CU
 // (0: no cap).  The one-column destination-scaled FP16 step runs fastest with five 4-wave
 // workgroups per CU (measured on the 8192 x 4096 splash: 107.9k MLUPS, against
-// 102.8k with the six its registers allow and 105.5k with four); the LDS is
+// 102.8k with the six its registers allow and 105.5k with four; 128 lattices of odd widths
+// 101-355 x 350 in a batch: 113 us per step with five, 117 us with six); the LDS is
 // reserved only to limit occupancy and is never accessed.
 static size_t occupancy_cap_lds(int cap)
 {
@@ -1327,6 +1328,7 @@ hipError_t launch_batch_flat(int store, bool walls, int psi, bool pair, const Ba
     if (ntotal <= 0) return hipSuccess;
     const int wpb = batch_waves_per_block(store, pair);
     const int blocks = (ntotal + wpb - 1) / wpb;
+    const size_t lds = occupancy_cap_lds(!pair && store == kStoreF16Dest ? kDestBlocksPerCu : 0);
     if (pair) {
         if (store != kStoreF16Dest) return hipErrorInvalidValue;
 #define LBMP_PAIRB(W_, P_)                                                                         \
@@ -1344,10 +1346,10 @@ hipError_t launch_batch_flat(int store, bool walls, int psi, bool pair, const Ba
     do {                                                                                           \
         if (psi == kPsiSS)                                                                         \
             hipLaunchKernelGGL((d2q9_batch_flat<S_, W_, kPsiSS, N_>), dim3(blocks), dim3(kWave * N_), \
-                               0, s, inst, tile_start, wg_first, ntotal, parity);                  \
+                               lds, s, inst, tile_start, wg_first, ntotal, parity);                \
         else                                                                                       \
             hipLaunchKernelGGL((d2q9_batch_flat<S_, W_, kPsiCS, N_>), dim3(blocks), dim3(kWave * N_), \
-                               0, s, inst, tile_start, wg_first, ntotal, parity);                  \
+                               lds, s, inst, tile_start, wg_first, ntotal, parity);                  \
     } while (0)
     switch (store) {
     case kStoreF32: if (walls) LBMP_FLAT(kStoreF32, true, kWavesPerBlock); else LBMP_FLAT(kStoreF32, false, kWavesPerBlock); break;
