@@ -878,37 +878,49 @@ __global__ void mass_fields(const MassJobs jobs)
         rho0_site(job.logrho, job.r0 + job.out[0], job.cx, job.cy, job.nx, job.ny, x, y, job.rho0);
 }
 
-// The same search by one workgroup in one launch, a level at a time: lattices of at most
-// kMassSmall sites, one per thread (32 x 32: 79 us; the rounds above need at least
-// 130 us for their launches).
-constexpr int kMassSmall = 1024;
+// The same search by one workgroup per profile in one launch, a level at a time: lattices of
+// at most kMassSmall sites, two per thread (32 x 32: 78 us, 33 x 32: 82 us, 45 x 45: 99 us; the rounds above need
+// 135 us and more for their launches, 152 us on 33 x 32 and 45 x 45).
+constexpr int kMassSmallThreads = 1024;
+constexpr int kMassSmallSites = 2;
+constexpr int kMassSmall = kMassSmallSites * kMassSmallThreads;
 
-__global__ __launch_bounds__(kMassSmall) void mass_small(const float* __restrict__ logrho, double r0, double cx,
-                                                         double cy, int nx, int ny, double mass,
-                                                         double* __restrict__ out)
+__global__ __launch_bounds__(kMassSmallThreads) void mass_small(const MassJobs jobs)
 {
+    const MassJob& job = jobs.job[blockIdx.x];
+    if (job.blocks > 0) return;  // by mass_round
+    const int nx = job.nx, n = job.nx * job.ny;
+    const double r0 = job.r0, mass = job.mass;
     __shared__ double L[kOut];
-    __shared__ double part[kMassSmall];
+    __shared__ double part[kMassSmallThreads];
     const int tid = threadIdx.x;
-    if (tid < kOut) L[tid] = (double)logrho[tid];
+    if (tid < kOut) L[tid] = (double)job.logrho[tid];
     double lo = -kMaxShift, hi = kMaxShift;
-    const bool live = tid < nx * ny;
-    const double dx = min_image((live ? tid % nx : 0) - cx, nx), dy = min_image((live ? tid / nx : 0) - cy, ny);
-    const double d = sqrt(dx * dx + dy * dy);
+    double d[kMassSmallSites];
+#pragma unroll
+    for (int q = 0; q < kMassSmallSites; ++q) {
+        const int i = tid + q * kMassSmallThreads;
+        const double dx = min_image((i < n ? i % nx : 0) - job.cx, nx), dy = min_image((i < n ? i / nx : 0) - job.cy, job.ny);
+        d[q] = sqrt(dx * dx + dy * dy);
+    }
     __syncthreads();
     for (int it = 0; it <= kMassIters; ++it) {
         const double delta = 0.5 * (lo + hi);
-        part[tid] = live ? profile_value(L, d, r0 + delta) : 0.0;
+        double v = 0.0;
+#pragma unroll
+        for (int q = 0; q < kMassSmallSites; ++q)
+            if (tid + q * kMassSmallThreads < n) v += profile_value(L, d[q], r0 + delta);
+        part[tid] = v;
         __syncthreads();
-        for (int s = kMassSmall / 2; s > 0; s >>= 1) {
+        for (int s = kMassSmallThreads / 2; s > 0; s >>= 1) {
             if (tid < s) part[tid] += part[tid + s];
             __syncthreads();
         }
         const double m = part[0];
         if (it == kMassIters) {
             if (tid == 0) {
-                out[0] = delta;
-                out[1] = m;
+                job.out[0] = delta;
+                job.out[1] = m;
             }
         } else if (m < mass) {
             lo = delta;
@@ -1177,13 +1189,7 @@ static hipError_t launch_mass_jobs(const lbml_placement* p, int n, hipStream_t s
                       {nullptr, nullptr}, p[i].shift, p[i].rho0};
         gx = std::max(gx, (int)grid1(p[i].nx, 256));
         gy = std::max(gy, p[i].ny);
-        if (sites <= kMassSmall) {
-            hipLaunchKernelGGL(mass_small, dim3(1), dim3(kMassSmall), 0, s, job.logrho, job.r0, job.cx, job.cy, job.nx,
-                               job.ny, job.mass, job.out);
-            const hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-            continue;
-        }
+        if (sites <= kMassSmall) continue;  // blocks 0: by mass_small
         // two rounds' records in the output field (8-byte aligned inside it): at most 128
         // doubles and a little per workgroup of at least 256 sites
         job.blocks = (int)std::min<long long>(kMassBlocks, sites / kMassThreads);
@@ -1193,6 +1199,11 @@ static hipError_t launch_mass_jobs(const lbml_placement* p, int n, hipStream_t s
         job.rec[1] = reinterpret_cast<MassRound*>(base + mass_round_doubles(job.blocks));
         blocks = std::max(blocks, job.blocks);
         ++large;
+    }
+    if (large < n) {
+        hipLaunchKernelGGL(mass_small, dim3(n), dim3(kMassSmallThreads), 0, s, jobs);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
     if (large > 0) {
         for (int round = 0; round <= kMassRounds; ++round) {
