@@ -622,7 +622,7 @@ lb_status init_ctx(lb_ctx** out, const lb_params* p, void* workspace, size_t wor
     c->two = two_step(*p);
     c->k2 = derive_two(*p, auto_two_rows(*p), kDefaultBand);
     c->waves2 = two_waves(*p, c->k2.strip_rows);
-    set_regions(c);
+    if (sync) set_regions(c);  // a batch steps its lattices itself, by strips
     c->kd = derive(*p, pass_rows(*p));
     c->ws = static_cast<char*>(workspace);
     c->flag = reinterpret_cast<int*>(c->ws + L.flag_off);
@@ -888,52 +888,6 @@ int default_batch_rows(int store)
     return 2;
 }
 
-}  // namespace
-
-struct lb_batch {
-    int n;
-    int mode;                        // LB_BATCH_STEPWISE or LB_BATCH_PERSISTENT
-    int fixed_rows;                  // > 0: every lattice walks strips of this height
-    int group_rows[2];               // stepwise heights per kernel group (default or tuned)
-    // Stepwise lattices form two groups, each stepped by its own launch: group 0 one
-    // column per lane, group 1 two columns per lane (destination-scaled FP16, even
-    // nx).  Group g holds dispatch positions [gfirst[g], gfirst[g] + gcount[g]) of
-    // `desc` and `order`; its tile prefix sums start at tile_start + gfirst[g] + g and
-    // its workgroup table at wg_first + wg_off[g].
-    int gfirst[2], gcount[2], ntotal[2];
-    size_t wg_off[2];
-    // FP32 lattices (all of them group 0) of at least 8 x 8 are stepped two at a time in the
-    // stepwise mode, with descriptors and tables of their own (same dispatch order).
-    bool two;
-    int two_rows, two_waves, two_ntotal;  // two_rows: tuned height, 0: batch_two_rows
-    lbmp::BatchInstance* two_desc;
-    int *two_start, *two_first;
-    size_t two_capacity;
-    int* tile_start;                 // device, n + 2 entries
-    int* wg_first;                   // device, lattice of each workgroup's first tile
-    size_t wg_capacity;              // entries available in wg_first
-    hipGraph_t graph[2];
-    hipGraphExec_t exec[2];
-    hipEvent_t ev[2];                // bracket the last lb_batch_step (stepwise mode)
-    std::vector<lb_ctx*> inst;       // per-lattice contexts on slices of the workspace
-    std::vector<int> order;          // dispatch position -> lattice index
-    std::vector<int> rows;           // strip height per lattice (current launch mode)
-    lbmp::BatchInstance* desc;       // device descriptors in dispatch order
-    unsigned long long* clocks;      // device, 2 per workgroup
-    // diagnostics of all lattices together (in lattice order)
-    lbmp::DiagInstance* diag;        // device, n
-    lbmp::DiagConst* regions;        // device, n
-    double* diag_out;                // device, n records of kDiagOut
-    int *diag_start, *diag_first;    // device, tile prefix sums (n + 1) and workgroup table
-    int* flags;                      // device, n
-    int diag_ntotal;
-    hipStream_t stream;
-    int store, bc, psi;
-    bool poisoned;
-};
-
-namespace {
-
 // Whether lattice p is stepped two columns per lane in the stepwise batch.
 bool batch_pair(const lb_params& p) { return lbmp::pair_step(p.store, p.nx); }
 
@@ -963,13 +917,6 @@ size_t batch_two_capacity(const lb_params* p, int n)
     return tiles / lbmp::kTwoWaves + 1;
 }
 
-size_t batch_two_bytes(const lb_params* p, int n)
-{
-    if (!batch_two(p, n)) return 0;
-    return align_up((size_t)n * sizeof(lbmp::BatchInstance), kAlign) + align_up((size_t)(n + 1) * sizeof(int), kAlign) +
-           align_up(batch_two_capacity(p, n) * sizeof(int), kAlign);
-}
-
 int batch_diag_tiles(const lb_params* p, int n)
 {
     long long tiles = 0;
@@ -977,25 +924,87 @@ int batch_diag_tiles(const lb_params* p, int n)
     return (int)std::min<long long>(tiles, 0x7fffffff);
 }
 
-// Sections of the diagnostics part of the header, in order: instances, regions, results,
-// tile prefix sums, workgroup table, flags.
-size_t batch_diag_sections(const lb_params* p, int n, size_t off[7])
+// Offsets of the batch's own part of the workspace, in front of the lattices'.  What the host
+// writes comes first, in one piece: the descriptors and tile prefix sums of the launches and
+// of the diagnostics, then `tables`, room for the workgroup tables of all of them.
+struct BatchLayout {
+    size_t desc, two_desc, tile_start, two_start, diag, diag_start, tables;
+    size_t table_entries;
+    size_t clocks, regions, diag_out, flags, total;
+};
+
+BatchLayout batch_layout(const lb_params* p, int n)
 {
-    const size_t bytes[6] = {(size_t)n * sizeof(lbmp::DiagInstance), (size_t)n * sizeof(lbmp::DiagConst),
-                             (size_t)n * lbmp::kDiagOut * sizeof(double), (size_t)(n + 1) * sizeof(int),
-                             ((size_t)batch_diag_tiles(p, n) / lbmp::kPassWaves + 1) * sizeof(int),
-                             (size_t)n * sizeof(int)};
-    off[0] = 0;
-    for (int i = 0; i < 6; ++i) off[i + 1] = off[i] + align_up(bytes[i], kAlign);
-    return off[6];
+    BatchLayout L{};
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        const size_t at = off;
+        off += align_up(bytes, kAlign);
+        return at;
+    };
+    const bool two = batch_two(p, n);
+    L.desc = take((size_t)n * sizeof(lbmp::BatchInstance));
+    L.two_desc = take(two ? (size_t)n * sizeof(lbmp::BatchInstance) : 0);
+    L.tile_start = take((size_t)(n + 2) * sizeof(int));
+    L.two_start = take(two ? (size_t)(n + 1) * sizeof(int) : 0);
+    L.diag = take((size_t)n * sizeof(lbmp::DiagInstance));
+    L.diag_start = take((size_t)(n + 1) * sizeof(int));
+    L.table_entries = batch_wg_capacity(p, n) + (two ? batch_two_capacity(p, n) : 0) +
+                      (size_t)batch_diag_tiles(p, n) / lbmp::kPassWaves + 1;
+    L.tables = take(L.table_entries * sizeof(int));
+    L.clocks = take((size_t)n * 16);
+    L.regions = take((size_t)n * sizeof(lbmp::DiagConst));
+    L.diag_out = take((size_t)n * lbmp::kDiagOut * sizeof(double));
+    L.flags = take((size_t)n * sizeof(int));
+    L.total = off;
+    return L;
 }
 
-size_t batch_header_bytes(const lb_params* p, int n)
-{
-    size_t off[7];
-    return batch_diag_sections(p, n, off) + batch_two_bytes(p, n) + align_up((size_t)n * sizeof(lbmp::BatchInstance), kAlign) + align_up((size_t)n * 16, kAlign) +
-           align_up((size_t)(n + 2) * sizeof(int), kAlign) + align_up(batch_wg_capacity(p, n) * sizeof(int), kAlign);
-}
+}  // namespace
+
+struct lb_batch {
+    int n;
+    int mode;                        // LB_BATCH_STEPWISE or LB_BATCH_PERSISTENT
+    int fixed_rows;                  // > 0: every lattice walks strips of this height
+    int group_rows[2];               // stepwise heights per kernel group (default or tuned)
+    // Stepwise lattices form two groups, each stepped by its own launch: group 0 one
+    // column per lane, group 1 two columns per lane (destination-scaled FP16, even
+    // nx).  Group g holds dispatch positions [gfirst[g], gfirst[g] + gcount[g]) of
+    // `desc` and `order`; its tile prefix sums start at tile_start + gfirst[g] + g and
+    // its workgroup table at wg_first + wg_off[g].
+    int gfirst[2], gcount[2], ntotal[2];
+    size_t wg_off[2];
+    // FP32 lattices (all of them group 0) of at least 8 x 8 are stepped two at a time in the
+    // stepwise mode, with descriptors and tables of their own (same dispatch order).
+    bool two;
+    int two_rows, two_waves, two_ntotal;  // two_rows: tuned height, 0: batch_two_rows
+    lbmp::BatchInstance* two_desc;
+    int *two_start, *two_first;
+    int* tile_start;                 // device, n + 2 entries
+    int* wg_first;                   // device, lattice of each workgroup's first tile
+    char* ws;                        // workspace
+    BatchLayout L;
+    hipGraph_t graph[2];
+    hipGraphExec_t exec[2];
+    hipEvent_t ev[2];                // bracket the last lb_batch_step (stepwise mode)
+    std::vector<lb_ctx*> inst;       // per-lattice contexts on slices of the workspace
+    std::vector<int> order;          // dispatch position -> lattice index
+    std::vector<int> rows;           // strip height per lattice (current launch mode)
+    lbmp::BatchInstance* desc;       // device descriptors in dispatch order
+    unsigned long long* clocks;      // device, 2 per workgroup
+    // diagnostics of all lattices together (in lattice order)
+    lbmp::DiagInstance* diag;        // device, n
+    lbmp::DiagConst* regions;        // device, n
+    double* diag_out;                // device, n records of kDiagOut
+    int *diag_start, *diag_first;    // device, tile prefix sums (n + 1) and workgroup table
+    int* flags;                      // device, n
+    int diag_ntotal;
+    hipStream_t stream;
+    int store, bc, psi;
+    bool poisoned;
+};
+
+namespace {
 
 void drop_batch_graphs(lb_batch* b)
 {
@@ -1063,20 +1072,41 @@ int batch_two_rows(const lb_batch* b)
     return best;
 }
 
-// Copy the per-lattice launch descriptors (dispatch order) and the tile tables of
-// both groups to the device.
+// Copy the launch descriptors (dispatch order), those of the diagnostics (lattice order) and
+// their tile tables to the device, in one copy (creating a batch of one lattice took 154 us with
+// a copy for each, 104 us so).
 hipError_t write_batch_descriptors(lb_batch* b)
 {
     drop_batch_graphs(b);
     const int n = b->n;
-    std::vector<lbmp::BatchInstance> host(n);
-    std::vector<int> start(n + 2, 0);
-    std::vector<int> first;
+    const BatchLayout& L = b->L;
+    std::vector<char> image(L.tables, 0);
+    std::vector<int> tables;
+    auto* host = reinterpret_cast<lbmp::BatchInstance*>(image.data() + L.desc);
+    int* const start = reinterpret_cast<int*>(image.data() + L.tile_start);
+    // diagnostics
+    {
+        auto* diag = reinterpret_cast<lbmp::DiagInstance*>(image.data() + L.diag);
+        int* st = reinterpret_cast<int*>(image.data() + L.diag_start);
+        for (int i = 0; i < n; ++i) {
+            const lb_ctx* c = b->inst[i];
+            diag[i] = lbmp::DiagInstance{c->kd, {c->f[0], c->f[1]}, c->flag, c->partial};
+            st[i + 1] = st[i] + c->kd.tiles_x * c->kd.tiles_y;
+        }
+        b->diag_ntotal = st[n];
+        b->diag_first = reinterpret_cast<int*>(b->ws + L.tables);
+        for (int t = 0, i = 0; t < b->diag_ntotal; t += lbmp::kPassWaves) {
+            while (t >= st[i + 1]) ++i;
+            tables.push_back(i);
+        }
+    }
+    // single steps, both groups
     b->rows.assign(n, 0);
-    size_t woff = 0;
+    b->wg_first = reinterpret_cast<int*>(b->ws + L.tables) + tables.size();
+    const size_t wg0 = tables.size();
     for (int g = 0; g < 2; ++g) {
         const int j0 = b->gfirst[g], cnt = b->gcount[g];
-        int* st = start.data() + j0 + g;
+        int* st = start + j0 + g;
         st[0] = 0;
         for (int j = 0; j < cnt; ++j) {
             const int i = b->order[j0 + j];
@@ -1094,72 +1124,36 @@ hipError_t write_batch_descriptors(lb_batch* b)
         b->ntotal[g] = st[cnt];
         const int wpb = lbmp::batch_waves_per_block(b->store, g == 1);
         const int blocks = (b->ntotal[g] + wpb - 1) / wpb;
-        b->wg_off[g] = woff;
+        b->wg_off[g] = tables.size() - wg0;
         for (int blk = 0, i = 0; blk < blocks; ++blk) {
             const int t = blk * wpb;
             while (t >= st[i + 1]) ++i;
-            first.push_back(i);
+            tables.push_back(i);
         }
-        woff += (size_t)blocks;
     }
-    if (woff > b->wg_capacity) return hipErrorInvalidValue;
-    std::vector<lbmp::BatchInstance> host2;
-    std::vector<int> start2, first2;
+    // two steps per launch
     if (b->two && b->mode == LB_BATCH_STEPWISE) {
-        host2 = host;
-        start2.assign(n + 1, 0);
+        auto* host2 = reinterpret_cast<lbmp::BatchInstance*>(image.data() + L.two_desc);
+        int* st = reinterpret_cast<int*>(image.data() + L.two_start);
         const int target = b->two_rows > 0 ? b->two_rows : batch_two_rows(b);
         for (int j = 0; j < n; ++j) {
             const lb_params& p = b->inst[b->order[j]]->p;
+            host2[j] = host[j];
             host2[j].k = derive_two(p, b->fixed_rows > 0 ? b->fixed_rows : even_rows(p.ny, target));
-            start2[j + 1] = start2[j] + host2[j].k.tiles_x * host2[j].k.tiles_y;
+            st[j + 1] = st[j] + host2[j].k.tiles_x * host2[j].k.tiles_y;
         }
-        b->two_ntotal = start2[n];
+        b->two_ntotal = st[n];
         b->two_waves = batch_two_waves(b->two_ntotal);
+        b->two_first = reinterpret_cast<int*>(b->ws + L.tables) + tables.size();
         for (int t = 0, i = 0; t < b->two_ntotal; t += b->two_waves) {
-            while (t >= start2[i + 1]) ++i;
-            first2.push_back(i);
+            while (t >= st[i + 1]) ++i;
+            tables.push_back(i);
         }
-        if (first2.size() > b->two_capacity) return hipErrorInvalidValue;
     }
-    hipError_t e = hipMemcpyAsync(b->desc, host.data(), n * sizeof(lbmp::BatchInstance), hipMemcpyHostToDevice,
-                                  b->stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(b->tile_start, start.data(), start.size() * sizeof(int), hipMemcpyHostToDevice, b->stream);
-    if (e == hipSuccess && !first.empty())
-        e = hipMemcpyAsync(b->wg_first, first.data(), first.size() * sizeof(int), hipMemcpyHostToDevice, b->stream);
-    if (e == hipSuccess && !host2.empty()) {
-        e = hipMemcpyAsync(b->two_desc, host2.data(), n * sizeof(lbmp::BatchInstance), hipMemcpyHostToDevice, b->stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(b->two_start, start2.data(), start2.size() * sizeof(int), hipMemcpyHostToDevice, b->stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(b->two_first, first2.data(), first2.size() * sizeof(int), hipMemcpyHostToDevice, b->stream);
-    }
-    if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
-    return e;
-}
-
-// Copy the descriptors of the diagnostics passes to the device.
-hipError_t write_diag_descriptors(lb_batch* b)
-{
-    const int n = b->n;
-    std::vector<lbmp::DiagInstance> host(n);
-    std::vector<int> start(n + 1, 0), first;
-    for (int i = 0; i < n; ++i) {
-        const lb_ctx* c = b->inst[i];
-        host[i] = lbmp::DiagInstance{c->kd, {c->f[0], c->f[1]}, c->flag, c->partial};
-        start[i + 1] = start[i] + c->kd.tiles_x * c->kd.tiles_y;
-    }
-    b->diag_ntotal = start[n];
-    for (int t = 0, i = 0; t < b->diag_ntotal; t += lbmp::kPassWaves) {
-        while (t >= start[i + 1]) ++i;
-        first.push_back(i);
-    }
-    hipError_t e = hipMemcpyAsync(b->diag, host.data(), host.size() * sizeof(host[0]), hipMemcpyHostToDevice, b->stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(b->diag_start, start.data(), start.size() * sizeof(int), hipMemcpyHostToDevice, b->stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(b->diag_first, first.data(), first.size() * sizeof(int), hipMemcpyHostToDevice, b->stream);
+    if (tables.size() > L.table_entries) return hipErrorInvalidValue;
+    const char* const extra = reinterpret_cast<const char*>(tables.data());
+    image.insert(image.end(), extra, extra + tables.size() * sizeof(int));
+    hipError_t e = hipMemcpyAsync(b->ws, image.data(), image.size(), hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     return e;
 }
@@ -1168,9 +1162,14 @@ hipError_t write_diag_descriptors(lb_batch* b)
 hipError_t read_batch_flags(lb_batch* b, std::vector<int>& flags)
 {
     flags.assign(b->n, 0);
-    hipError_t e = lbmp::launch_batch_flags(b->diag, b->n, b->flags, b->stream);
+    const int* from = b->inst[0]->flag;  // one lattice: its word, without a launch to gather (20 us, 23 us with it)
+    hipError_t e = hipSuccess;
+    if (b->n > 1) {
+        from = b->flags;
+        e = lbmp::launch_batch_flags(b->diag, b->n, b->flags, b->stream);
+    }
     if (e == hipSuccess)
-        e = hipMemcpyAsync(flags.data(), b->flags, flags.size() * sizeof(int), hipMemcpyDeviceToHost, b->stream);
+        e = hipMemcpyAsync(flags.data(), from, flags.size() * sizeof(int), hipMemcpyDeviceToHost, b->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     return e;
 }
@@ -1249,7 +1248,7 @@ lb_status validate_batch(const lb_params* p, int32_t n)
 size_t lb_batch_workspace_bytes(const lb_params* p, int32_t n)
 {
     if (validate_batch(p, n) != LB_OK) return 0;
-    size_t total = batch_header_bytes(p, n);
+    size_t total = batch_layout(p, n).total;
     for (int i = 0; i < n; ++i) total += layout_of(p[i]).total;
     return total;
 }
@@ -1275,35 +1274,21 @@ lb_status lb_batch_init(lb_batch** out, const lb_params* p, int32_t n, void* wor
     b->bc = p[0].bc;
     b->psi = p[0].psi_form;
     char* ws = static_cast<char*>(workspace);
-    size_t hoff = 0;
-    b->desc = reinterpret_cast<lbmp::BatchInstance*>(ws + hoff);
-    hoff += align_up((size_t)n * sizeof(lbmp::BatchInstance), kAlign);
-    b->clocks = reinterpret_cast<unsigned long long*>(ws + hoff);
-    hoff += align_up((size_t)n * 16, kAlign);
-    b->tile_start = reinterpret_cast<int*>(ws + hoff);
-    hoff += align_up((size_t)(n + 2) * sizeof(int), kAlign);
-    b->wg_first = reinterpret_cast<int*>(ws + hoff);
-    b->wg_capacity = batch_wg_capacity(p, n);
-    hoff += align_up(b->wg_capacity * sizeof(int), kAlign);
+    const BatchLayout L = batch_layout(p, n);
+    b->ws = ws;
+    b->L = L;
     b->two = batch_two(p, n);
-    if (b->two) {
-        b->two_rows = 0;
-        b->two_desc = reinterpret_cast<lbmp::BatchInstance*>(ws + hoff);
-        hoff += align_up((size_t)n * sizeof(lbmp::BatchInstance), kAlign);
-        b->two_start = reinterpret_cast<int*>(ws + hoff);
-        hoff += align_up((size_t)(n + 1) * sizeof(int), kAlign);
-        b->two_first = reinterpret_cast<int*>(ws + hoff);
-        b->two_capacity = batch_two_capacity(p, n);
-        hoff += align_up(b->two_capacity * sizeof(int), kAlign);
-    }
-    size_t sec[7];
-    batch_diag_sections(p, n, sec);
-    b->diag = reinterpret_cast<lbmp::DiagInstance*>(ws + hoff + sec[0]);
-    b->regions = reinterpret_cast<lbmp::DiagConst*>(ws + hoff + sec[1]);
-    b->diag_out = reinterpret_cast<double*>(ws + hoff + sec[2]);
-    b->diag_start = reinterpret_cast<int*>(ws + hoff + sec[3]);
-    b->diag_first = reinterpret_cast<int*>(ws + hoff + sec[4]);
-    b->flags = reinterpret_cast<int*>(ws + hoff + sec[5]);
+    b->two_rows = 0;
+    b->desc = reinterpret_cast<lbmp::BatchInstance*>(ws + L.desc);
+    b->two_desc = reinterpret_cast<lbmp::BatchInstance*>(ws + L.two_desc);
+    b->tile_start = reinterpret_cast<int*>(ws + L.tile_start);
+    b->two_start = reinterpret_cast<int*>(ws + L.two_start);
+    b->diag = reinterpret_cast<lbmp::DiagInstance*>(ws + L.diag);
+    b->diag_start = reinterpret_cast<int*>(ws + L.diag_start);
+    b->clocks = reinterpret_cast<unsigned long long*>(ws + L.clocks);
+    b->regions = reinterpret_cast<lbmp::DiagConst*>(ws + L.regions);
+    b->diag_out = reinterpret_cast<double*>(ws + L.diag_out);
+    b->flags = reinterpret_cast<int*>(ws + L.flags);
     b->mode = LB_BATCH_STEPWISE;
     hipError_t ee = hipEventCreate(&b->ev[0]);
     if (ee == hipSuccess) ee = hipEventCreate(&b->ev[1]);
@@ -1311,7 +1296,7 @@ lb_status lb_batch_init(lb_batch** out, const lb_params* p, int32_t n, void* wor
         lb_batch_destroy(b);
         return hip_fail(ee, "hipEventCreate");
     }
-    size_t off = batch_header_bytes(p, n);
+    size_t off = L.total;
     b->inst.assign(n, nullptr);
     for (int i = 0; i < n; ++i) {
         const size_t bytes = layout_of(p[i]).total;
@@ -1327,7 +1312,6 @@ lb_status lb_batch_init(lb_batch** out, const lb_params* p, int32_t n, void* wor
     b->group_rows[0] = b->group_rows[1] = default_batch_rows(b->store);
     order_batch(b);
     hipError_t e = write_batch_descriptors(b);
-    if (e == hipSuccess) e = write_diag_descriptors(b);
     std::vector<int> flags;
     if (e == hipSuccess) e = read_batch_flags(b, flags);
     if (e != hipSuccess) {
