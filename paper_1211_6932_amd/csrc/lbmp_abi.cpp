@@ -1074,8 +1074,9 @@ int batch_two_rows(const lb_batch* b)
 
 // Copy the launch descriptors (dispatch order), those of the diagnostics (lattice order) and
 // their tile tables to the device, in one copy (creating a batch of one lattice took 154 us with
-// a copy for each, 104 us so).
-hipError_t write_batch_descriptors(lb_batch* b)
+// a copy for each, 104 us so).  trial: two-step launches report unstable sites to words that
+// nobody reads, since they also look at the state one step ahead.
+hipError_t write_batch_descriptors(lb_batch* b, bool trial = false)
 {
     drop_batch_graphs(b);
     const int n = b->n;
@@ -1140,6 +1141,7 @@ hipError_t write_batch_descriptors(lb_batch* b)
             const lb_params& p = b->inst[b->order[j]]->p;
             host2[j] = host[j];
             host2[j].k = derive_two(p, b->fixed_rows > 0 ? b->fixed_rows : even_rows(p.ny, target));
+            if (trial) host2[j].flag = b->flags + j;
             st[j + 1] = st[j] + host2[j].k.tiles_x * host2[j].k.tiles_y;
         }
         b->two_ntotal = st[n];
@@ -1507,7 +1509,7 @@ lb_status lb_batch_tune(lb_batch* b, int32_t trial_steps, int32_t* rows_out)
     // at_once = 1: single-step launches, 2: two-step launches.
     auto time_launches = [&](int at_once, double& sec) -> hipError_t {
         int steps = 0;
-        hipError_t e = write_batch_descriptors(b);
+        hipError_t e = write_batch_descriptors(b, true);
         for (int w = 0; w < 2 && e == hipSuccess; ++w) e = batch_launch_some(b, parity, at_once, &steps);
         sec = 1e30;
         for (int rep = 0; rep < 3 && e == hipSuccess; ++rep) {
