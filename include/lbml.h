@@ -114,15 +114,16 @@ lb_status lbml_profile_extract(const float* rho, int32_t nx, int32_t ny, double 
                                void* scratch, size_t scratch_bytes, float* logrho, void* stream);
 
 /* lbml_profiles_extract: n of these (n >= 1; p: host array, copied by the call) in launches that
- * serve up to 32 fields each.  Every entry has its own scratch (lbml_profile_scratch_bytes(ny)
- * bytes, 8-byte aligned); scratch and results of different entries must not overlap; every
- * entry is checked before the first launch.  Results are bitwise those of n calls of
+ * serve up to 32 fields each.  Every entry has its own scratch (scratch_bytes of it, at least
+ * lbml_profile_scratch_bytes(ny), else LB_ENOMEM; 8-byte aligned); scratch and results of
+ * different entries must not overlap; every entry is checked before the first launch.  Results are bitwise those of n calls of
  * lbml_profile_extract.  Asynchronous on `stream`. */
 typedef struct lbml_fit {
     const float* rho;
     double cx, cy, R;
     int32_t nx, ny;
     void* scratch;
+    size_t scratch_bytes;
     float* logrho;
 } lbml_fit;
 lb_status lbml_profiles_extract(const lbml_fit* p, int32_t n, void* stream);

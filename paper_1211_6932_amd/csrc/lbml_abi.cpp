@@ -341,22 +341,6 @@ size_t lbml_profile_scratch_bytes(int32_t ny)
     return (size_t)3 * ny * lbml::kOut * sizeof(double);
 }
 
-lb_status lbml_profile_extract(const float* rho, int32_t nx, int32_t ny, double cx, double cy, double R,
-                               void* scratch, size_t scratch_bytes, float* logrho, void* stream)
-{
-    if (!rho || !logrho || !scratch) return abi_fail(LB_EINVAL, "NULL argument");
-    if (nx < 2 || ny < 2 || nx > (1 << 20) || ny > (1 << 20) || (long long)nx * ny > (1LL << 31))
-        return abi_fail(LB_EINVAL, "bad lattice size");
-    if (!std::isfinite(cx) || !std::isfinite(cy) || !std::isfinite(R) || R < 0.0 || R > 1e6)
-        return abi_fail(LB_EINVAL, "centre and radius must be finite, 0 <= R <= 1e6");
-    if (reinterpret_cast<uintptr_t>(scratch) % 8) return abi_fail(LB_EINVAL, "scratch must be 8-byte aligned");
-    if (scratch_bytes < lbml_profile_scratch_bytes(ny))
-        return abi_fail(LB_ENOMEM, "scratch smaller than lbml_profile_scratch_bytes(ny)");
-    hipError_t e = lbml::launch_profile_extract(rho, nx, ny, cx, cy, R, static_cast<double*>(scratch), logrho,
-                                                static_cast<hipStream_t>(stream));
-    return e == hipSuccess ? LB_OK : abi_hip_fail(e, "lbml_profile_extract");
-}
-
 lb_status lbml_profiles_extract(const lbml_fit* p, int32_t n, void* stream)
 {
     if (!p || n < 1) return abi_fail(LB_EINVAL, "need p and n >= 1");
@@ -368,9 +352,18 @@ lb_status lbml_profiles_extract(const lbml_fit* p, int32_t n, void* stream)
         if (!std::isfinite(f.cx) || !std::isfinite(f.cy) || !std::isfinite(f.R) || f.R < 0.0 || f.R > 1e6)
             return abi_fail(LB_EINVAL, "centre and radius must be finite, 0 <= R <= 1e6");
         if (reinterpret_cast<uintptr_t>(f.scratch) % 8) return abi_fail(LB_EINVAL, "scratch must be 8-byte aligned");
+        if (f.scratch_bytes < lbml_profile_scratch_bytes(f.ny))
+            return abi_fail(LB_ENOMEM, "scratch smaller than lbml_profile_scratch_bytes(ny)");
     }
     hipError_t e = lbml::launch_profiles_extract(p, n, static_cast<hipStream_t>(stream));
-    return e == hipSuccess ? LB_OK : abi_hip_fail(e, "lbml_profiles_extract");
+    return e == hipSuccess ? LB_OK : abi_hip_fail(e, "lbml_profile_extract");
+}
+
+lb_status lbml_profile_extract(const float* rho, int32_t nx, int32_t ny, double cx, double cy, double R,
+                               void* scratch, size_t scratch_bytes, float* logrho, void* stream)
+{
+    const lbml_fit f{rho, cx, cy, R, nx, ny, scratch, scratch_bytes, logrho};
+    return lbml_profiles_extract(&f, 1, stream);
 }
 
 lb_status lbml_profile_extract_noalloc(const float* rho, int32_t nx, int32_t ny, double cx, double cy, double R,

@@ -1120,7 +1120,7 @@ hipError_t launch_profiles_extract(const lbml_fit* p, int n, hipStream_t s)
 hipError_t launch_profile_extract(const float* rho, int nx, int ny, double cx, double cy, double R, double* part,
                                   float* logrho, hipStream_t s)
 {
-    const lbml_fit f{rho, cx, cy, R, nx, ny, part, logrho};
+    const lbml_fit f{rho, cx, cy, R, nx, ny, part, (size_t)3 * ny * kOut * sizeof(double), logrho};
     return launch_profiles_extract(&f, 1, s);
 }
 

@@ -81,7 +81,7 @@ class lbml_fit(ctypes.Structure):
     """One field's profile fit of include/lbml.h."""
     _fields_ = [("rho", ctypes.c_void_p), ("cx", ctypes.c_double), ("cy", ctypes.c_double), ("R", ctypes.c_double),
                 ("nx", ctypes.c_int32), ("ny", ctypes.c_int32), ("scratch", ctypes.c_void_p),
-                ("logrho", ctypes.c_void_p)]
+                ("scratch_bytes", ctypes.c_size_t), ("logrho", ctypes.c_void_p)]
 
 
 class lbml_placement(ctypes.Structure):
@@ -833,7 +833,7 @@ def profiles_extract(rhos, places, out, scratch, stream=0):
         raise ValueError("profiles_extract: scratch too small, or out or a field of the wrong layout")
     lbml_profiles_extract(
         [lbml_fit(rho.data_ptr(), float(cx), float(cy), float(R), rho.shape[1], rho.shape[0],
-                  scratch.data_ptr() + i * each, out.data_ptr() + i * LBML_OUT * 4)
+                  scratch.data_ptr() + i * each, each, out.data_ptr() + i * LBML_OUT * 4)
          for i, (rho, (cx, cy, R)) in enumerate(zip(rhos, places, strict=True))], stream)
     return out
 
