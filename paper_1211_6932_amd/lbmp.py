@@ -823,18 +823,34 @@ def profile_extract(rho, cx, cy, R, out=None, scratch=None, stream=0):
     return out
 
 
+def _want(name, t, dtype, shape, device=None):
+    """ValueError unless t is a tensor of this dtype and shape (None: any size) on one GPU
+    (`device` where given)."""
+    if t.dtype != dtype or t.dim() != len(shape) or any(w is not None and w != s for w, s in zip(shape, t.shape)):
+        raise ValueError(f"{name}: expected {dtype} {list(shape)}, got {t.dtype} {list(t.shape)}")
+    if t.device.type != "cuda" or (device is not None and t.device != device):
+        raise ValueError(f"{name}: expected a tensor on {device or 'a GPU'}, got {t.device}")
+
+
 def profiles_extract(rhos, places, out, scratch, stream=0):
-    """profile_extract of each of the contiguous fields rhos around places[i] = (cx, cy, R) into
-    the rows of out [n][128]; scratch: at least n times lbml_profile_scratch_bytes of the
-    tallest field."""
+    """profile_extract of each of the contiguous float32 fields rhos around places[i] = (cx, cy, R)
+    into the rows of out [n][128] (float32); scratch: at least n times lbml_profile_scratch_bytes
+    of the tallest field.  All on one GPU."""
+    import torch
+    places = list(places)
+    if len(places) != len(rhos):
+        raise ValueError("profiles_extract: need as many places as fields")
+    _want("out", out, torch.float32, (len(rhos), LBML_OUT))
+    _want("scratch", scratch, scratch.dtype, (None,) * scratch.dim(), out.device)
+    for rho in rhos:
+        _want("field", rho, torch.float32, (None, None), out.device)
     each = max(lbml_profile_scratch_bytes(rho.shape[0]) for rho in rhos)
-    if scratch.numel() * scratch.element_size() < each * len(rhos) or out.shape != (len(rhos), LBML_OUT) \
-            or not out.is_contiguous() or not all(rho.is_contiguous() for rho in rhos):
-        raise ValueError("profiles_extract: scratch too small, or out or a field of the wrong layout")
+    if scratch.numel() * scratch.element_size() < each * len(rhos) or not all(t.is_contiguous() for t in (out, scratch, *rhos)):
+        raise ValueError("profiles_extract: scratch too small, or a tensor that is not contiguous")
     lbml_profiles_extract(
         [lbml_fit(rho.data_ptr(), float(cx), float(cy), float(R), rho.shape[1], rho.shape[0],
                   scratch.data_ptr() + i * each, each, out.data_ptr() + i * LBML_OUT * 4)
-         for i, (rho, (cx, cy, R)) in enumerate(zip(rhos, places, strict=True))], stream)
+         for i, (rho, (cx, cy, R)) in enumerate(zip(rhos, places))], stream)
     return out
 
 
@@ -860,9 +876,10 @@ def profile_to_rho0_mass(logrho, R, cx, cy, nx, ny, mass, out=None, shift=None, 
 
 
 def profiles_to_rho0_mass(logrho, placements, stream=0):
-    """profile_to_rho0_mass of each row of a device tensor logrho [n][128], placements: n of
-    (R, cx, cy, nx, ny, mass).  Returns (fields, shifts [n][2]); empty for n = 0."""
+    """profile_to_rho0_mass of each row of a device tensor logrho [n][128] (float32), placements:
+    n of (R, cx, cy, nx, ny, mass).  Returns (fields, shifts [n][2]); empty for n = 0."""
     import torch
+    _want("logrho", logrho, torch.float32, (None, LBML_OUT))
     if logrho.stride(-1) != 1 or len(placements) != len(logrho):
         raise ValueError("need n profiles contiguous in the last dimension and n placements")
     fields = [torch.empty((int(ny), int(nx)), dtype=torch.float32, device=logrho.device)
