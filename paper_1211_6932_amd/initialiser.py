@@ -301,7 +301,8 @@ def learned_rho0(model, ws, anchored=True):
     prof = predict(model, ws, anchored)
     fields, shifts = lbmp.profiles_to_rho0_mass(
         prof, [(w.info["R0"], w.info["cx"], w.info["cy"], w.params["nx"], w.params["ny"],
-                float(w.rho0.astype(np.float32).sum(dtype=np.float64))) for w in ws])
+                float(w.rho0.astype(np.float32).sum(dtype=np.float64))) for w in ws],
+        stream=torch.cuda.current_stream(prof.device).cuda_stream)  # predict's
     torch.cuda.synchronize()
     return fields, shifts[:, 0].tolist()
 
