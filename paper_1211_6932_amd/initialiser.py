@@ -129,7 +129,9 @@ def relaxed_profiles(batch, ws, members, centres=None):
     import torch
     out = torch.empty((len(ws), N_OUT), dtype=torch.float32, device=batch.device)
     each = max(lbmp.lbml_profile_scratch_bytes(w.params["ny"]) for w in ws)
-    together = max(1, min(32, len(ws), (64 << 20) // each))  # fits per call
+    sites = max(w.params["nx"] * w.params["ny"] for w in ws)
+    # fits per call: bounded by the scratch and by the density fields that wait for their fit
+    together = max(1, min(32, len(ws), (64 << 20) // max(each, 4 * sites)))
     scratch = torch.empty(together * each, dtype=torch.uint8, device=batch.device)
     todo = list(zip(members, ws))
     for a in range(0, len(todo), together):
