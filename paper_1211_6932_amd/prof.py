@@ -23,6 +23,7 @@ import sys
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 # the kernel sources and the build script that fixes their compiler flags
 KERNEL_SOURCES = ["paper_1211_6932_amd/csrc/d2q9_core.hpp", "paper_1211_6932_amd/csrc/d2q9_two.hpp",
+                  "paper_1211_6932_amd/csrc/d2q9_region.hpp", "paper_1211_6932_amd/csrc/d2q9_launch.hpp",
                   "paper_1211_6932_amd/csrc/d2q9_kernels.hip", "paper_1211_6932_amd/build.py"]
 COPY_BYTES = 1 << 30
 
@@ -67,23 +68,31 @@ def _counter_by_kernel(d, counter):
 
 
 def _is_step_kernel(name):
-    """A time-step kernel: d2q9_two (two steps), d2q9_strip<store, walls, MODE = 0, psi form>,
-    or the two-columns-per-lane d2q9_pair<walls, psi form>."""
-    if re.search(r"d2q9_(pair|two)(<|I)", name):  # the profiler may leave this name mangled
+    """A time-step kernel of a single lattice: d2q9_two (two steps), d2q9_region (several),
+    d2q9_strip<store, walls, MODE = 0, psi form>, d2q9_mr<walls, MODE = 0, psi form> (24-site
+    stencil), or the two-columns-per-lane d2q9_pair<walls, psi form>."""
+    if re.search(r"d2q9_(pair|two|region)(<|I)", name):  # the profiler may leave these names mangled
         return True
-    m = re.search(r"d2q9_strip<(\d+), (true|false), (\d+), (\d+)>", name)
-    return bool(m) and m.group(3) == "0"
+    m = re.search(r"d2q9_strip<\d+, (?:true|false), (\d+), \d+>|d2q9_mr<(?:true|false), (\d+), \d+>", name)
+    return bool(m) and (m.group(1) or m.group(2)) == "0"
+
+
+def _step_counter(vals):
+    """Counter values of the step kernel's launches.  Where several step kernels ran (a step
+    left over runs in another one than the rest) the one with the most launches."""
+    step = [v for k, v in vals.items() if _is_step_kernel(k)]
+    return max(step, key=lambda v: (len(v), sum(v))) if step else []
 
 
 def traffic(fetch_dir, write_dir, store, sites):
     res = {}
     for counter, d, key in (("FETCH_SIZE", fetch_dir, "read"), ("WRITE_SIZE", write_dir, "write")):
         vals = _counter_by_kernel(d, counter)
-        step = [v for k, v in vals.items() if _is_step_kernel(k)]
+        step = _step_counter(vals)
         copy = [v for k, v in vals.items() if "copy_probe" in k]
         if not step or not copy:
             raise RuntimeError(f"{counter}: step or copy-probe dispatches missing in {d}")
-        step_kib = statistics.median(step[0])
+        step_kib = statistics.median(step)
         copy_kib = statistics.median(copy[0])
         scale = COPY_BYTES / (copy_kib * 1024.0)
         res[key] = dict(counter_kib_per_launch=step_kib, copy_counter_kib=copy_kib, scale=scale,
