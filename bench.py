@@ -124,6 +124,18 @@ def cpu_baseline(w, budget_s=15.0):
     }
 
 
+def tuning_summary(rows, seconds, store):
+    """Strip heights that lb_batch_tune reports, and of which launches: a batch stepped two at a
+    time has another height for those launches, which the tuner sets but does not report."""
+    if rows is None:
+        return None
+    per_launch = STEPS_PER_LAUNCH.get(store, 1)
+    return {"seconds": round(seconds, 3),
+            "rows_of": "the step launches" if per_launch == 1 else
+            f"single-step launches (an odd last step; the timed launches take {per_launch} steps)",
+            "rows_histogram": {str(r): rows.count(r) for r in sorted(set(rows))}}
+
+
 def bench_batch(args):
     import numpy as np
     import torch
@@ -142,9 +154,10 @@ def bench_batch(args):
     t0 = time.perf_counter()
     rows = b.tune(trial_steps=8) if not args.no_tune else None
     t_tune = time.perf_counter() - t0
-    if rows is not None:
-        log(f"tuned strip heights in {t_tune:.2f} s: " +
-            ", ".join(f"{r} rows x {rows.count(r)}" for r in sorted(set(rows))))
+    tuning = tuning_summary(rows, t_tune, args.store)
+    if tuning is not None:
+        log(f"tuned in {t_tune:.2f} s; strip heights of {tuning['rows_of']}: " +
+            ", ".join(f"{r} rows x {n}" for r, n in tuning["rows_histogram"].items()))
     b.step(args.warmup)
     b.stream.synchronize()
     log(f"timed {args.steps} steps (stepwise)")
@@ -201,8 +214,7 @@ def bench_batch(args):
         "per_lattice_stepwise": {"p50_s": round(wall, 4), "p99_s": round(wall, 4),
                                  "note": "every lattice completes with the last launch"},
         "per_lattice_persistent": per_lattice,
-        "tuning": None if rows is None else {"seconds": round(t_tune, 3),
-                                             "rows_histogram": {str(r): rows.count(r) for r in sorted(set(rows))}},
+        "tuning": tuning,
         "checks": {"unstable_lattices": int(n_unstable),
                    "unstable": [dict(i=i, side=ws[i].params["nx"], a=ws[i].params["a"],
                                      t_over_tc=round(ws[i].info["t_over_tc"], 3), R0=round(ws[i].info["R0"], 1))
