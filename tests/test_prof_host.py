@@ -1,10 +1,5 @@
 """The counter summaries follow the kernel that a run was mostly made of, and become stale with
-<<<<<<< Updated upstream
 every source that the step kernels are built from."""
-=======
-every source that the step kernels are built from; the batch benchmark says which launches
-its strip heights belong to."""
->>>>>>> Stashed changes
 import os
 import re
 
@@ -50,14 +45,3 @@ def test_the_hash_covers_what_the_step_kernels_include():
         seen.add(f)
         todo += re.findall(r'#include "([\w.]+)"', open(os.path.join(CSRC, f)).read())
     assert {os.path.join("paper_1211_6932_amd", "csrc", f) for f in seen} <= set(prof.KERNEL_SOURCES)
-<<<<<<< Updated upstream
-=======
-
-
-def test_tuning_summary_names_the_launches():
-    import bench
-    assert bench.tuning_summary(None, 1.0, "f32") is None
-    one, two = (bench.tuning_summary([2, 3, 3], 1.0, s) for s in ("f16local", "f32"))
-    assert one["rows_of"] == "the step launches" and "single-step" in two["rows_of"]
-    assert one["rows_histogram"] == {"2": 1, "3": 2}
->>>>>>> Stashed changes
