@@ -32,6 +32,10 @@ lb_status hip_fail(hipError_t e, const char* what)
     return fail(LB_EHIP, std::string(what) + ": " + hipGetErrorString(e));
 }
 
+// Host memory ran out inside an entry point that keeps tables (a short message: storing it
+// must not allocate).
+lb_status no_memory() { return fail(LB_ENOMEM, "out of memory"); }
+
 constexpr size_t kAlign = 256;
 constexpr int kMinStripRows = 3;
 constexpr int kBatchPersistentRows = 24;  // measured best (one workgroup walks a whole lattice)
@@ -1299,35 +1303,44 @@ lb_status lb_batch_init(lb_batch** out, const lb_params* p, int32_t n, void* wor
         return hip_fail(ee, "hipEventCreate");
     }
     size_t off = L.total;
-    b->inst.assign(n, nullptr);
-    for (int i = 0; i < n; ++i) {
-        const size_t bytes = layout_of(p[i]).total;
-        st = init_ctx(&b->inst[i], p + i, ws + off, bytes, rho0[i], ux0 ? ux0[i] : nullptr,
-                      uy0 ? uy0[i] : nullptr, stream, false);
-        if (st != LB_OK) {
-            const std::string msg = g_last_error;
-            lb_batch_destroy(b);
-            return fail(st, "lattice " + std::to_string(i) + ": " + msg);
+    auto drop = [&] {
+        lb_batch_destroy(b);
+        b = nullptr;
+    };
+    try {
+        b->inst.assign(n, nullptr);
+        for (int i = 0; i < n; ++i) {
+            const size_t bytes = layout_of(p[i]).total;
+            st = init_ctx(&b->inst[i], p + i, ws + off, bytes, rho0[i], ux0 ? ux0[i] : nullptr,
+                          uy0 ? uy0[i] : nullptr, stream, false);
+            if (st != LB_OK) {
+                const std::string msg = g_last_error;
+                drop();
+                return fail(st, "lattice " + std::to_string(i) + ": " + msg);
+            }
+            off += bytes;
         }
-        off += bytes;
+        b->group_rows[0] = b->group_rows[1] = default_batch_rows(b->store);
+        order_batch(b);
+        hipError_t e = write_batch_descriptors(b);
+        std::vector<int> flags;
+        if (e == hipSuccess) e = read_batch_flags(b, flags);
+        if (e != hipSuccess) {
+            drop();
+            return hip_fail(e, "batch descriptors");
+        }
+        for (int i = 0; i < n; ++i) {
+            if (!(flags[i] & lbmp::kFlagBadInput)) continue;
+            drop();
+            return fail(LB_EINVAL, "lattice " + std::to_string(i) + ": rho0/u0 out of range");
+        }
+        *out = b;
+        g_last_error.clear();
+        return LB_OK;
+    } catch (const std::bad_alloc&) {
+        drop();
+        return no_memory();
     }
-    b->group_rows[0] = b->group_rows[1] = default_batch_rows(b->store);
-    order_batch(b);
-    hipError_t e = write_batch_descriptors(b);
-    std::vector<int> flags;
-    if (e == hipSuccess) e = read_batch_flags(b, flags);
-    if (e != hipSuccess) {
-        lb_batch_destroy(b);
-        return hip_fail(e, "batch descriptors");
-    }
-    for (int i = 0; i < n; ++i) {
-        if (!(flags[i] & lbmp::kFlagBadInput)) continue;
-        lb_batch_destroy(b);
-        return fail(LB_EINVAL, "lattice " + std::to_string(i) + ": rho0/u0 out of range");
-    }
-    *out = b;
-    g_last_error.clear();
-    return LB_OK;
 }
 
 lb_status lb_batch_step(lb_batch* b, int64_t nsteps)
@@ -1395,7 +1408,7 @@ lb_status lb_batch_diagnostics(lb_batch* b, int32_t i, const lb_region* in, cons
 }
 
 lb_status lb_batch_diagnostics_all(lb_batch* b, const lb_region* in, const lb_region* outr, lb_diag* d)
-{
+try {
     if (!b || !in || !outr || !d) return fail(LB_EINVAL, "NULL argument");
     if (b->poisoned) return fail(LB_ESTATE, "batch poisoned by an earlier failure");
     const int n = b->n;
@@ -1426,6 +1439,8 @@ lb_status lb_batch_diagnostics_all(lb_batch* b, const lb_region* in, const lb_re
         }
     }
     return bad ? fail(LB_EUNSTABLE, std::to_string(bad) + " lattice(s) flagged an unstable site") : LB_OK;
+} catch (const std::bad_alloc&) {
+    return no_memory();
 }
 
 lb_status lb_batch_get_state(lb_batch* b, int32_t i, void* dst)
@@ -1436,7 +1451,7 @@ lb_status lb_batch_get_state(lb_batch* b, int32_t i, void* dst)
 }
 
 lb_status lb_batch_check(lb_batch* b, int32_t* unstable)
-{
+try {
     if (!b) return fail(LB_EINVAL, "batch is NULL");
     std::vector<int> flags;
     const hipError_t e = read_batch_flags(b, flags);
@@ -1453,10 +1468,12 @@ lb_status lb_batch_check(lb_batch* b, int32_t* unstable)
     }
     if (unstable) *unstable = count;
     return count ? fail(LB_EUNSTABLE, std::to_string(count) + " lattice(s) flagged an unstable site") : LB_OK;
+} catch (const std::bad_alloc&) {
+    return no_memory();
 }
 
 lb_status lb_batch_times(lb_batch* b, double* seconds)
-{
+try {
     if (!b || !seconds) return fail(LB_EINVAL, "NULL argument");
     if (b->mode == LB_BATCH_STEPWISE) {
         float ms = 0.0f;
@@ -1479,10 +1496,12 @@ lb_status lb_batch_times(lb_batch* b, double* seconds)
     for (int j = 0; j < b->n; ++j) t0 = std::min(t0, h[2 * j]);
     for (int j = 0; j < b->n; ++j) seconds[b->order[j]] = (double)(h[2 * j + 1] - t0) / (khz * 1e3);
     return LB_OK;
+} catch (const std::bad_alloc&) {
+    return no_memory();
 }
 
 lb_status lb_batch_set_launch(lb_batch* b, int32_t mode, int32_t strip_rows)
-{
+try {
     if (!b) return fail(LB_EINVAL, "batch is NULL");
     if (mode != LB_BATCH_STEPWISE && mode != LB_BATCH_PERSISTENT) return fail(LB_EINVAL, "unknown batch mode");
     if (strip_rows < 0 || strip_rows > kMaxStripRows) return fail(LB_EINVAL, "strip_rows must lie in [0, 64]");
@@ -1492,10 +1511,13 @@ lb_status lb_batch_set_launch(lb_batch* b, int32_t mode, int32_t strip_rows)
     hipError_t e = write_batch_descriptors(b);
     if (e != hipSuccess) return hip_fail(e, "batch descriptors");
     return LB_OK;
+} catch (const std::bad_alloc&) {
+    b->poisoned = true;  // the descriptors may not be those of the settings
+    return no_memory();
 }
 
 lb_status lb_batch_tune(lb_batch* b, int32_t trial_steps, int32_t* rows_out)
-{
+try {
     if (!b) return fail(LB_EINVAL, "batch is NULL");
     if (b->poisoned) return fail(LB_ESTATE, "batch poisoned by an earlier failure");
     if (trial_steps < 1 || trial_steps > 1000) return fail(LB_EINVAL, "trial_steps must lie in [1, 1000]");
@@ -1570,6 +1592,9 @@ lb_status lb_batch_tune(lb_batch* b, int32_t trial_steps, int32_t* rows_out)
     if (rows_out)
         for (int i = 0; i < b->n; ++i) rows_out[i] = b->rows[i];
     return LB_OK;
+} catch (const std::bad_alloc&) {
+    b->poisoned = true;  // the descriptors may not be those of the settings
+    return no_memory();
 }
 
 lb_status lb_batch_destroy(lb_batch* b)
