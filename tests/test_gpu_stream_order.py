@@ -113,3 +113,21 @@ def test_learned_starts(caller, monkeypatch):
     monkeypatch.setattr(I, "predict", lambda model, w, anchored=True: late(torch.zeros_like(prof), prof))
     got = I.learned_rho0(None, ws)
     assert got[1] == want[1] and all(torch.equal(a, b) for a, b in zip(got[0], want[0]))
+
+
+def test_while_the_caller_captures():
+    """A call on the library's own stream while the caller's stream is being captured neither joins
+    nor breaks the capture."""
+    print("[gpu-case] stream order: capture", flush=True)
+    p, rho, _ = fields()
+    sim = B.Sim(p, rho)
+    want = sim.moments()
+    x = torch.ones(8, device="cuda")
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, capture_error_mode="relaxed"):
+        y = x + 1.0
+        got = sim.step(0).moments()
+    g.replay()
+    torch.cuda.synchronize()
+    assert bool((y == 2.0).all()) and all(torch.equal(a, b) for a, b in zip(got, want))
