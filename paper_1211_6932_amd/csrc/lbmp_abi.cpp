@@ -387,25 +387,33 @@ int region_steps(const lb_params& p)
 }
 
 // Times in us of a step by strips and of a launch of `steps` steps by regions:
-//   strips   s0 + fill min(1, workgroups / resident) + rounds (s1 + s2 rows), the workgroups
-//            taking turns in `rounds` of as many as are resident at once;
-//   regions  r0 + r1 steps + load (r2 + r3 steps), + r4 where some unit has two regions.
+//   strips   s0 + fill (workgroups per unit, at most as many as are resident and two) +
+//            rounds (s1 + s2 rows), the workgroups taking turns in `rounds` of the resident ones;
+//   regions  r0 + r1 steps + load (r2 + r3 steps) + r4 where some unit has two regions, for FP16
+//            dest (whose registers with walls leave room for one region at a time) also for
+//            each further one.
 // Fitted on 250 lattices of each kind (3e3 to 4e6 sites, sides 8 to 125000, walls and
-// periodic): strips within 8 % and rather too low, regions within 9 %, so that a launch by
+// periodic): strips within 8 % and rather too low, regions within 8 %, so that a launch by
 // regions is a gain where these say so (of 3500 choices 20 lost more than 2 %, none more than
-// 8 %; by the numbers of sites alone 360 did, up to 2.5 times).  Strips against regions, us per
-// step: FP16 1984 x 1024 17.5 / 22.1, 992 x 2048 16.0 / 24.1 (one full round of strips), 2048 x
-// 1024 25.7 / 21.8 (two, the second nearly empty); FP32 37500 x 8 6.6 / 9.9, FP16 125000 x 8
-// 14 / 31 (regions mostly off the lattice); 24 sites 1876 x 1823 48.8 / 53.9.  Single steps: FP16
-// local 525 x 505 8.3 / 11.1, 724^2 15.0 / 12.2; 24 sites 641 x 640 9.2 / 12.3, 724^2 16.1 / 13.8.
-struct LaunchCost { double s0, fill, s1, s2, r0, r1, r2, r3, r4; };
+// 8 %; by the numbers of sites alone 360 did, up to 2.5 times).  Strips against regions, us per step:
+// FP16 1984 x 1024 17.5 / 22.1, 992 x 2048 16.0 / 24.1 (one full round of strips), 2048 x 1024 25.7
+// / 21.8 (two, the second nearly empty); FP32 37500 x 8 6.6 / 9.9, FP16 125000 x 8 14 / 31 (regions
+// mostly off the lattice); 24 sites 1876 x 1823 48.8 / 53.9.  Single steps: FP16 local 525 x 505
+// 8.3 / 11.1, 724^2 15.0 / 12.2; 24 sites 641 x 640 9.2 / 12.3, 724^2 16.1 / 13.8.
+struct LaunchCost {
+    double s0, fill, s1, s2, r0, r1, r2, r3, r4;
+    double turns = 1.0;  // times r4 counts at most
+};
 LaunchCost launch_cost(const lb_params& p, bool pair)
 {
     if (p.stencil == LB_STENCIL_MULTIRANGE) return {1.2, 1.2, 2.35, 2.2, 3.5, 1.1, 3.85, 0.0, 0.4};
-    if (p.store == LB_STORE_F32) return {0.7, 1.0, 0.8, 2.25, 2.95, 1.07, 6.24, -0.31, 0.64};
-    if (p.store == LB_STORE_F16_DEST)
-        return pair ? LaunchCost{1.1, 0.0, 3.15, 0.37, 2.7, 1.3, 6.85, -0.92, 5.2}
-                    : LaunchCost{-0.8, 0.0, 4.8, 0.2, 2.7, 1.3, 6.85, -0.92, 5.2};
+    if (p.store == LB_STORE_F32) return {0.7, 1.0, 0.8, 2.25, 2.65, 1.07, 6.24, -0.31, 0.64};
+    if (p.store == LB_STORE_F16_DEST) {
+        LaunchCost c{1.0, 0.8, 3.15, 0.37, 2.58, 1.245, 6.27, -0.89, 5.7, 8.0};
+        if (!pair) c.s0 = -0.95, c.s1 = 4.8, c.s2 = 0.2;
+        if (p.bc == LB_BC_PERIODIC) c.r1 = 1.19, c.r2 = 6.32, c.r3 = -0.865, c.r4 = 3.47;
+        return c;
+    }
     if (p.store == LB_STORE_F16_OFFSET || p.store == LB_STORE_BF16_OFFSET)
         return {1.6, 1.2, 2.2, 1.3, 4.4, 0.67, 2.2, 0.55, 1.5};
     return {1.0, 1.2, 3.2, 1.7, 4.75, 0.8, 2.75, 0.45, 0.9};
@@ -421,17 +429,17 @@ bool region_pays(const lb_params& p, int steps, int rows, long long resident, in
     // but the flattest (600 x 250 5.1 / 3.7, 4687 x 64 6.4 / 5.6, 9375 x 32 6.5 / 7.2)
     if (p.store == LB_STORE_F32 && p.stencil == LB_STENCIL_NEAREST && steps > 1)
         return p.ny >= 64 || (long long)p.nx * p.ny <= 600LL * ncu;
-    // 24 sites, well beyond the last-level cache: the strips slow down, the regions do not
-    // (1160 x 3206, 268 MB, 53.2 / 60.1; 2048 x 2048, 302 MB, 82 / 64)
-    if (p.stencil == LB_STENCIL_MULTIRANGE && steps > 1 && 2 * layout_of(p).buf_bytes > (size_t)272 << 20) return true;
+    // 24 sites, beyond the last-level cache: the strips slow down, the regions do not
+    // (1160 x 3206, 255 MiB, 53.2 / 60.1; 1868 x 2040, 262 MiB, 68.7 / 60.9; 2048 x 2048 82 / 64)
+    if (p.stencil == LB_STENCIL_MULTIRANGE && steps > 1 && 2 * layout_of(p).buf_bytes > kLastLevelCache) return true;
     const LaunchCost c = launch_cost(p, pair);
     const int tile = pair ? lbmp::kPairTileW : tile_width(p);
     const long long strips = (long long)((p.nx + tile - 1) / tile) * ((p.ny + rows - 1) / rows);
     const long long groups = (strips + waves - 1) / waves;
-    const double strip = c.s0 + c.fill * std::min(1.0, (double)groups / resident) +
+    const double strip = c.s0 + c.fill * std::min(std::min(2.0, (double)resident / ncu), (double)groups / ncu) +
                          (double)((groups + resident - 1) / resident) * (c.s1 + c.s2 * rows);
     const double load = region_load(p, steps, ncu);
-    const double region = c.r0 + c.r1 * steps + load * (c.r2 + c.r3 * steps) + (load > 1.0 ? c.r4 : 0.0);
+    const double region = c.r0 + c.r1 * steps + load * (c.r2 + c.r3 * steps) + c.r4 * std::min(c.turns, std::ceil(load) - 1.0);
     return region * (steps == 1 ? 1.06 : 1.0) <= steps * strip;  // single steps are the closest
 }
 
