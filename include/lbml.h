@@ -87,8 +87,9 @@ lb_status lbml_train_step(lbml_net* net, const float* x, const float* base, cons
  * Adam and bf16 refresh); the step index, learning rate and Adam's bias
  * correction come from a schedule kept on the device.  The result is bitwise
  * that of `steps` calls of lbml_train_step on the gathered rows.  B: multiple of
- * 32, at most max_batch.  The net's stream must not be the null stream.  The indices are checked first
- * (LB_EINVAL, nothing trained, if one is out of range).  steps = 0 returns LB_OK
+ * 32, at most max_batch.  The net's stream must not be the null stream (LB_EINVAL;
+ * no launch of the loop needs that, the refusal is kept as part of the interface).  The
+ * indices are checked first (LB_EINVAL, nothing trained, if one is out of range).  steps = 0 returns LB_OK
  * at once (the array arguments may then be NULL).  Synchronises the stream. */
 lb_status lbml_train_steps(lbml_net* net, const float* x_all, const float* base_all, const float* target_all,
                            int32_t rows, const int32_t* idx, const float* lr, int32_t steps, int32_t B, float* loss);

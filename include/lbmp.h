@@ -205,8 +205,9 @@ lb_status lb_set_state(lb_ctx* ctx, const void* src, int64_t t);
  * strips in y times the rest in x); graph_chunk = steps per captured graph
  * (even, >= 2).  For each: a positive value sets it, 0 keeps the current
  * value, -1 (strip_rows, band only) restores the automatic choice, which is
- * strips of some height or, on small lattices and with the 24-site stencil,
- * regions of 32 x 32 sites (a positive strip_rows asks for strips).  Results do
+ * strips of some height or, for each number of steps per launch, regions of
+ * 32 x 32 sites where these are estimated to be no slower: on small lattices and
+ * with the 24-site stencil (a positive strip_rows asks for strips).  Results do
  * not depend on any of them (bitwise). */
 lb_status lb_set_launch(lb_ctx* ctx, int32_t strip_rows, int32_t band, int32_t graph_chunk);
 

@@ -80,7 +80,7 @@ struct StepConst {
     int nx, ny, pitch;          // pitch in elements
     int tiles_x, tiles_y, strip_rows;
     int paced;                  // single steps: the waves of a workgroup keep to one row (pace)
-    int back;                   // single steps: workgroups in descending order
+    int back;                   // single steps: this launch's workgroups in descending order (launch_block)
     int band;                   // strips per tile band: consecutive tiles walk down `band` strips, then right
     long long row_stride;       // elements of the storage type per lattice row (9 or 11 pitches)
     float b4;                   // b / 4
@@ -643,8 +643,9 @@ __device__ __forceinline__ int logical_block(int b, int nb, bool back = false)
     return start + (back ? last - idx : idx);
 }
 
-// The same for a launch of single steps: where the state exceeds the last-level cache, every
-// other launch takes each XCD's run from its end and so begins with what the one before wrote
+// The same for a launch of single steps: where the two buffers exceed the last-level cache
+// (FP32: and a state is at most 512 MiB, see derive_single), every other launch takes each
+// XCD's run from its end and so begins with what the one before wrote
 // last, while that cache still holds it (8192 x 4096, one direction and alternating: FP16 275
 // and 263 us, FP16 dest 268 and 262 us, FP16 local 381 and 374 us; two steps per launch: 249
 // and 249 us).  The runs stay on their XCDs: swapping them loses what is in the L2s (FP16 dest

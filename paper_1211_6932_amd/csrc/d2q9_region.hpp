@@ -18,7 +18,8 @@ namespace lbmp {
 // price of computing the overlap several times on compute units that had nothing to do.
 // Measured on 128 x 128 sites, FP32, per step: 4.07 us by strips of two steps per launch,
 // 2.03 us with 6 steps per region launch (12.2 us: about 4 us for the launch and the load,
-// the rest the 12 exchanges through LDS, each a barrier of 16 wavefronts).
+// the rest the 11 exchanges through LDS, two a step but for the last step's populations,
+// each a barrier of 16 wavefronts).
 //
 // Registers: 64 per lane, so that two workgroups share a compute unit (512 x 512 in 3 steps:
 // 5.8 us per step, 6.5 us with 128 registers; a lattice with one region per unit loses 5 %).

@@ -18,7 +18,8 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 // C[M][N] (FP32, row stride ldc) = sum_k A(m, k) B(k, n) with A(m, k) at
 // A[m * sam + k * sak] and B(k, n) at B[k * sbk + n * sbn] (bf16).  One
 // wavefront per 16 x 16 tile of C, K consumed 32 at a time by
-// v_mfma_f32_16x16x32_bf16: lane l holds row (or column) l % 16 and the eight
+// v_mfma_f32_16x16x32_bf16 (behind lbml_gemm_bf16 alone: the network's kernels below multiply
+// operands in fragment order): lane l holds row (or column) l % 16 and the eight
 // consecutive k values 8 (l / 16) .. 8 (l / 16) + 7 of each operand; the
 // accumulator holds rows 4 (l / 16) .. 4 (l / 16) + 3 of column l % 16.
 // AV / BV: the operand is contiguous in k (sak == 1 / sbk == 1) with 16-byte
@@ -80,8 +81,8 @@ __global__ void fill_zero(unsigned int* __restrict__ p, size_t n)
 // batch per workgroup through every layer, forward and, in training, back to the first
 // layer's pre-activation gradients; mlp_grads forms every weight and bias gradient from what
 // that left behind and, in a training loop, applies Adam to them on the spot.  512 rows:
-// 11.8 + 8.8 us, where one launch per operation (32 of them) took 115 us and the gaps (159 us a
-// training step, now 21.5 us).
+// 11.1 + 6.2 us in a training loop, where one launch per operation (32 of them) took 115 us and
+// the gaps (159 us a training step, now 21.5 us).
 // Products use the matrix cores as gemm_bf16 does (same operand orientation, one accumulator
 // over k in steps of 32), whichever launch they are in.
 
@@ -308,7 +309,11 @@ constexpr int kTiles3 = (kOut / 16) * (kHidden / 16), kTiles12 = (kHidden / 16) 
 constexpr int kTilesAll = kTiles3 + 2 * kTiles12 + kTiles0;
 constexpr int kBiases = 3 * kHidden + kOut;
 constexpr int kGradWaves = kTilesAll + kBiases / 64 + 1;
-constexpr int kGradAhead = 16;   // steps of 32 rows of the batch whose operands are in flight
+// Steps of 32 rows of the batch in one block of straight code.  Its 96 registers do not hold 16
+// steps' operands: the first product waits for eight loads, and about ten are in flight.  Rows
+// beyond a multiple of 512 take one step at a time (64 rows 3.6 us, 160 4.4, 480 8.1, 512 8.2,
+// 1024 13.8; gradients only).
+constexpr int kGradAhead = 16;
 constexpr int kBiasAhead = 4;    // the same for the bias gradients
 constexpr int kBiasLd = 32 + 8;
 
