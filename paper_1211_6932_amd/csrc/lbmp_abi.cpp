@@ -1062,7 +1062,9 @@ int lattice_rows(const lb_batch* b, int i)
 // 4); as long as every strip can be resident 4 spread more evenly.
 int batch_two_waves(long long strips) { return strips > 16LL * compute_units() ? lbmp::kTwoWavesWide : lbmp::kTwoWaves; }
 
-// Strip height of the two-step launches of a batch: the cheapest for all its strips (two_cost).
+// Strip height of the two-step launches of a batch: the cheapest for all its strips (two_cost),
+// of which the tallest are the longest walk (200 lattices of 32 x 32 have strips of 7 rows at a
+// height of 6: 7.5 us per step where that was priced as 6, 6.2 us at 4; 350 of 12 x 12 6.0 / 5.2).
 int batch_two_rows(const lb_batch* b)
 {
     const int ncu = compute_units();
@@ -1070,12 +1072,14 @@ int batch_two_rows(const lb_batch* b)
     double least = 1e300;
     for (int h = 2; h <= 20; ++h) {
         long long strips = 0;
+        int tallest = 0;
         for (int i = 0; i < b->n; ++i) {
             const lb_params& p = b->inst[i]->p;
             const int rows = even_rows(p.ny, h);
+            tallest = std::max(tallest, rows);
             strips += (long long)((p.nx + lbmp::kTwoTileW - 1) / lbmp::kTwoTileW) * ((p.ny + rows - 1) / rows);
         }
-        const double cost = two_cost(h, strips, batch_two_waves(strips), ncu);
+        const double cost = two_cost(tallest, strips, batch_two_waves(strips), ncu);
         if (cost < least) {
             least = cost;
             best = h;
