@@ -436,8 +436,15 @@ bool region_pays(const lb_params& p, int steps, int rows, long long resident, in
     const int tile = pair ? lbmp::kPairTileW : tile_width(p);
     const long long strips = (long long)((p.nx + tile - 1) / tile) * ((p.ny + rows - 1) / rows);
     const long long groups = (strips + waves - 1) / waves;
-    const double strip = c.s0 + c.fill * std::min(std::min(2.0, (double)resident / ncu), (double)groups / ncu) +
-                         (double)((groups + resident - 1) / resident) * (c.s1 + c.s2 * rows);
+    double strip = c.s0 + c.fill * std::min(std::min(2.0, (double)resident / ncu), (double)groups / ncu) +
+                   (double)((groups + resident - 1) / resident) * (c.s1 + c.s2 * rows);
+    // strips with walls take about 7 % longer (periodic and walls: FP16 916 x 517 7.5 and 8.2 us,
+    // FP16 local 1021 x 509 14.3 and 15.0, 24 sites 15.0 and 16.1); for FP16 dest that is in the
+    // constants, and a single step of source density or of 24 sites would lose by it (FP16 local
+    // 151 x 1000 8.1 by strips, 9.0 by regions)
+    const bool closest = steps == 1 && p.store != LB_STORE_F16_OFFSET && p.store != LB_STORE_BF16_OFFSET &&
+                         (p.store != LB_STORE_F32 || p.stencil == LB_STENCIL_MULTIRANGE);
+    if (p.bc == LB_BC_WALLS_Y && p.store != LB_STORE_F16_DEST && !closest) strip *= 1.07;
     const double load = region_load(p, steps, ncu);
     const double region = c.r0 + c.r1 * steps + load * (c.r2 + c.r3 * steps) + c.r4 * std::min(c.turns, std::ceil(load) - 1.0);
     return region * (steps == 1 ? 1.06 : 1.0) <= steps * strip;  // single steps are the closest
